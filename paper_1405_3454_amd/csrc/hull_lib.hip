@@ -1598,6 +1598,22 @@ static int run_learned_dirs(hull_ctx *ctx, const Plan &p, hipStream_t st, const 
     return HULL_OK;
 }
 
+// Extreme survivor of each set along the 64 candidate directions into the
+// workspace's cand table (survivors in surv / surv_off); also clears the label
+// counters in up0.  lo0 holds the partials: lo0 and up0 each have at least
+// 16 KiB per set (two tiles of list entries), 16 partials of 64 directions.
+static_assert(LAB_SPLIT * NCAND * sizeof(CandPart) <= 2 * TILE * 8, "the partials fit the chain's buffer");
+static int run_cand_extremes(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x, const float *y,
+                             int64_t S) {
+    const unsigned split = lab_split(S, ctx->cus);
+    auto *part = W<CandPart>(p, p.lo0);
+    LAUNCH(K_LABELS, k_cand_extremes<<<dim3((unsigned)S, split), LAB_THREADS, 0, st>>>(
+        x, y, W<Poly>(p, p.polys), W<uint32_t>(p, p.surv), W<int64_t>(p, p.surv_off), part));
+    LAUNCH(K_LABELS, k_cand_pick<<<(unsigned)S, NCAND, 0, st>>>(part, (int)split, W<uint32_t>(p, p.cand),
+                                                               W<uint32_t>(p, p.up0)));
+    return HULL_OK;
+}
+
 static int init_cand_table() {
     static std::once_flag once;
     static hipError_t err = hipSuccess;
@@ -1754,10 +1770,12 @@ int hull_labels_batched(hull_ctx *ctx, const float *x, const float *y, const int
     uint32_t *surv = W<uint32_t>(p, p.surv);
     int64_t *so = W<int64_t>(p, p.surv_off);
     RC(run_discard(ctx, p, st, x, y, n_total, offsets, 0, S, slot_count(ctx, false), surv, so, nullptr));
-    uint32_t *cand = W<uint32_t>(p, p.cand);
-    LAUNCH(K_LABELS, k_cand_extremes<<<(unsigned)S, 256, 0, st>>>(x, y, offsets, 0, S, cand));
-    LAUNCH(K_LABELS, k_labels<<<(unsigned)S, 256, 0, st>>>(x, y, offsets, 0, S, W<Poly>(p, p.polys),
-                                                          cand, surv, so, gain));
+    RC(run_cand_extremes(ctx, p, st, x, y, S));
+    uint32_t *cand = W<uint32_t>(p, p.cand), *cnt = W<uint32_t>(p, p.up0);
+    LAUNCH(K_LABELS, k_labels<<<dim3((unsigned)S, lab_split(S, ctx->cus)), LAB_THREADS, 0, st>>>(
+        x, y, W<Poly>(p, p.polys), cand, surv, so, cnt));
+    LAUNCH(K_LABELS, k_label_gain<<<(unsigned)((S * NCAND + 255) / 256), 256, 0, st>>>(offsets, 0, S, cnt,
+                                                                                       gain));
     return HULL_OK;
 }
 
@@ -1778,10 +1796,9 @@ int hull_label_targets_batched(hull_ctx *ctx, const float *x, const float *y,
     uint32_t *surv = W<uint32_t>(p, p.surv);
     int64_t *so = W<int64_t>(p, p.surv_off);
     RC(run_discard(ctx, p, st, x, y, n_total, offsets, 0, S, slot_count(ctx, false), surv, so, nullptr));
-    uint32_t *cand = W<uint32_t>(p, p.cand);
-    LAUNCH(K_LABELS, k_cand_extremes<<<(unsigned)S, 256, 0, st>>>(x, y, offsets, 0, S, cand));
+    RC(run_cand_extremes(ctx, p, st, x, y, S));
     LAUNCH(K_LABELS, k_label_targets<<<(unsigned)S, 256, 0, st>>>(
-        x, y, offsets, 0, S, W<Poly>(p, p.polys), cand, surv, so, rounds, target, order));
+        x, y, offsets, 0, S, W<Poly>(p, p.polys), W<uint32_t>(p, p.cand), surv, so, rounds, target, order));
     return HULL_OK;
 }
 

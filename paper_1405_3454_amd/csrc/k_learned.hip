@@ -363,173 +363,445 @@ __global__ void k_top8(const float *__restrict__ scores, int64_t S, int gap,
 }
 
 // ---------------------------------------------------------------------------
-// Training labels.
+// Training labels, from the fixed filter's survivors of each set.
+//
+// A survivor is not strictly inside some edges of the base polygon: its
+// "out" mask, usually one bit.  The mask says which of the 64 directions the
+// survivor matters for, so both passes below sort their survivors by it (a
+// chunk at a time, in LDS) and a wave then walks the few directions of its
+// batch's class with the edge and direction constants uniform over the wave.
+// They are bound by vector instructions: about 16 edge tests per survivor and
+// 6-8 directions instead of 64.  (The former passes walked every point eight
+// times with one block per set, and 64 polygons of up to 17 edges per
+// survivor: 1391 and 6689 us for 256 mixtures of 2^16 points, now 143 and 46;
+// without the heights below 568 and 46.)
+constexpr int LAB_THREADS = 512;
+constexpr int LAB_WAVES = LAB_THREADS / WAVE;
+constexpr int LAB_PER = 4;
+constexpr int LAB_CHUNK = LAB_THREADS * LAB_PER;
+constexpr int LAB_CLASSES = FIXED_SLOTS + 1;          // one edge each; the rest
+constexpr int LAB_SPLIT = 16;                         // most blocks per set
+constexpr int LAB_NOTES = 1024;
+constexpr int LAB_BINS = LAB_THREADS / FIXED_SLOTS;   // height bins along a base edge
+// Blocks per set: eight per CU in all, since sets differ in survivors by a
+// factor of ten and with fewer most CUs wait for a few (256 sets, both passes:
+// 274, 250, 208 and 253 us with three, four, eight and sixteen per CU); more
+// sets than that have one each.
+constexpr int LAB_BLOCKS_PER_CU = 8;
+static unsigned lab_split(int64_t S, int cus) {
+    const int64_t k = (LAB_BLOCKS_PER_CU * (int64_t)cus + S - 1) / S;
+    return (unsigned)(k < 1 ? 1 : k > LAB_SPLIT ? LAB_SPLIT : k);
+}
+
+// Partial extreme of one direction over a block's share of a set.
+struct CandPart {
+    double v;
+    uint32_t i;
+    uint32_t pad;
+};
+
+struct LabShared {
+    float x[LAB_CHUNK], y[LAB_CHUNK];
+    uint32_t id[LAB_CHUNK];
+    uint16_t out[LAB_CHUNK];
+    uint32_t cnt[LAB_CLASSES];                        // survivors of each class in the chunk
+    uint32_t start[LAB_CLASSES + 1];                  // the classes' first entries
+    uint32_t batch[LAB_CLASSES + 1];                  // and first batches of 64
+};
+
+// Heights below which a survivor outside one edge only cannot matter: for edge
+// e and a survivor whose foot lies in bin b of the edge, -E < h[e][b].
+struct LabHeights {
+    double h[FIXED_SLOTS][LAB_BINS];
+    double ex[FIXED_SLOTS], ey[FIXED_SLOTS], c[FIXED_SLOTS];
+    double u0[FIXED_SLOTS], scale[FIXED_SLOTS];       // bin = (ex px + ey py - u0) scale
+};
+
+// Load survivors [c0, c1) (at most LAB_CHUNK) into L, grouped by class, less
+// those that H (if given) leaves out.  Every thread of the block calls it;
+// L.cnt holds the class counts after.
+__device__ __forceinline__ void lab_chunk(LabShared &L, const float *__restrict__ x,
+                                          const float *__restrict__ y, const uint32_t *__restrict__ surv,
+                                          int64_t c0, int64_t c1, const Poly &P, int m,
+                                          const LabHeights *H) {
+    const int tid = threadIdx.x;
+    __syncthreads();                                  // the previous chunk is done with L
+    if (tid < LAB_CLASSES) L.cnt[tid] = 0;
+    float px[LAB_PER], py[LAB_PER];
+    uint32_t id[LAB_PER], out[LAB_PER], rank[LAB_PER];
+    int cls[LAB_PER];
+#pragma unroll
+    for (int q = 0; q < LAB_PER; q++) {
+        const int64_t j = c0 + tid + q * LAB_THREADS;
+        id[q] = j < c1 ? surv[j] : NONE;
+    }
+#pragma unroll
+    for (int q = 0; q < LAB_PER; q++) {
+        px[q] = id[q] != NONE ? x[id[q]] : 0.0f;
+        py[q] = id[q] != NONE ? y[id[q]] : 0.0f;
+        out[q] = 0;
+    }
+    for (int e = 0; e < m; e++) {
+        const double ex = P.ex[e], ey = P.ey[e], ec = P.c[e];
+#pragma unroll
+        for (int q = 0; q < LAB_PER; q++)
+            if (!(edge_eval(ex, ey, ec, (double)px[q] * GRIDD, (double)py[q] * GRIDD) > 0)) out[q] |= 1u << e;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < LAB_PER; q++) {
+        cls[q] = __popc(out[q]) == 1 ? __ffs((int)out[q]) - 1 : FIXED_SLOTS;
+        if (H && cls[q] < FIXED_SLOTS) {
+            const int e = cls[q];
+            const double gx = (double)px[q] * GRIDD, gy = (double)py[q] * GRIDD;
+            const double b = (fma(H->ex[e], gx, H->ey[e] * gy) - H->u0[e]) * H->scale[e];
+            if (b >= 0 && b < LAB_BINS && -edge_eval(H->ex[e], H->ey[e], H->c[e], gx, gy) < H->h[e][(int)b])
+                id[q] = NONE;
+        }
+        const bool has = id[q] != NONE;
+        // lanes of the same class: one LDS addition per class and wave
+        uint64_t same = __ballot(has);
+#pragma unroll
+        for (int b = 0; b < 5; b++) {
+            const uint64_t bit = __ballot((cls[q] >> b) & 1);
+            same &= ((cls[q] >> b) & 1) ? bit : ~bit;
+        }
+        uint32_t base = 0;
+        const int lead = has ? __ffsll((unsigned long long)same) - 1 : 0;
+        if (has && lead == lane_id()) base = atomicAdd(&L.cnt[cls[q]], (uint32_t)__popcll(same));
+        rank[q] = __shfl(base, lead) + (uint32_t)__popcll(same & lanemask_lt());
+    }
+    __syncthreads();
+    if (tid <= LAB_CLASSES) {
+        uint32_t at = 0, b = 0;
+        for (int c = 0; c < LAB_CLASSES; c++) {
+            const uint32_t n = L.cnt[c];
+            at += c < tid ? n : 0;
+            b += c < tid ? (n + WAVE - 1) / WAVE : 0;
+        }
+        L.start[tid] = at;
+        L.batch[tid] = b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < LAB_PER; q++) {
+        if (id[q] == NONE) continue;
+        const uint32_t at = L.start[cls[q]] + rank[q];
+        L.x[at] = px[q];
+        L.y[at] = py[q];
+        L.id[at] = id[q];
+        L.out[at] = (uint16_t)out[q];
+    }
+    __syncthreads();
+}
+
+// Batch b of a chunk: up to 64 survivors of one class.  Returns false past
+// the last batch.
+__device__ __forceinline__ bool lab_batch(const LabShared &L, int b, int *cls, int *at, int *len) {
+    const int lane = lane_id();
+    const int c = __popcll(__ballot(lane < LAB_CLASSES && b >= (int)L.batch[min(lane, LAB_CLASSES - 1) + 1]));
+    if (c >= LAB_CLASSES) return false;
+    const int rel = (b - (int)L.batch[c]) * WAVE;
+    *cls = c;
+    *at = (int)L.start[c] + rel;
+    *len = min(WAVE, (int)L.cnt[c] - rel);
+    return true;
+}
+
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v |= (uint64_t)__shfl_xor((unsigned long long)v, o);
+    return uniform_u64(v);
+}
+
 // (1) Extreme point of every set along each of the 64 candidate directions
-//     (argmax of c*x + s*y, lowest index on ties); one block per set, eight
-//     directions per pass.
-__global__ __launch_bounds__(256) void k_cand_extremes(const float *__restrict__ x,
-                                                       const float *__restrict__ y,
-                                                       const int64_t *__restrict__ off,
-                                                       int64_t n1, int64_t S,
-                                                       uint32_t *__restrict__ cand) {
-    __shared__ double rv[4][8];
-    __shared__ uint32_t ri[4][8];
+//     (argmax of c*x + s*y, lowest index on ties), one partial per block.
+//     Only survivors can be one: a point strictly inside the base polygon lies
+//     at least 2^-49 inside each of its edges, more than the roundings of two
+//     values (2^-51), so it neither beats nor ties the best vertex.  The same
+//     bound holds edge by edge: a survivor strictly inside both edges at the
+//     base vertex that is extreme along d is not extreme along d.  So edge j's
+//     class visits the directions whose extreme base vertex (or one within
+//     2^-40 of it) is an end of edge j.
+//     The block shares one best value per direction, raised by an LDS maximum
+//     and started at the best base vertex; a survivor that reaches the best
+//     when it is seen is noted in a list, from which the lowest index of each
+//     final best is taken.  Should the list run over (thousands of copies of
+//     an extreme point), the survivors are walked once more for it.  A best
+//     per wave, found with cross-lane reductions, took as long.
+//     A thin set's long edges end at vertices that are extreme along most of
+//     the directions, so their class (most of the survivors) visits them all.
+//     There a height per bin of the edge leaves out the survivors that stay
+//     2^-45 below every direction's best so far (unit coordinates; the
+//     arithmetic errs by less than 2^-50): of the class, few remain.  The
+//     heights are taken at the start, after the first 512 survivors of a
+//     block and whenever the chunks done are four times as many.
+__global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
+    const float *__restrict__ x, const float *__restrict__ y, const Poly *__restrict__ polys,
+    const uint32_t *__restrict__ surv, const int64_t *__restrict__ surv_off, CandPart *__restrict__ part) {
+    __shared__ LabShared L;
+    __shared__ uint64_t dirs[LAB_CLASSES];
+    __shared__ double bv[NCAND];                      // best value, and its lowest index
+    __shared__ uint32_t bi[NCAND];
+    __shared__ double cc[NCAND], ss[NCAND];
+    __shared__ double nv[LAB_NOTES];                  // noted survivors: value, index, direction
+    __shared__ uint32_t ni[LAB_NOTES];
+    __shared__ uint8_t nd[LAB_NOTES];
+    __shared__ uint32_t notes;
+    __shared__ LabHeights H;
     const int64_t s = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const int64_t a = set_begin(off, s), e = set_end(off, n1, s);
-    for (int d0 = 0; d0 < NCAND; d0 += 8) {
-        double bv[8];
-        uint32_t bi[8];
-        double cc[8], ss[8];
-#pragma unroll
-        for (int q = 0; q < 8; q++) {
-            bv[q] = -INFINITY;
-            bi[q] = NONE;
-            cc[q] = dCandCos[d0 + q];
-            ss[q] = dCandSin[d0 + q];
+    const Poly &P = polys[s];
+    const int m = P.m < 3 ? 0 : P.m;                  // no interior: every direction for every survivor
+    if (w == 0) {
+        const int d = lane;
+        cc[d] = dCandCos[d];
+        ss[d] = dCandSin[d];
+        double best = -INFINITY;
+        for (int k = 0; k < m; k++)
+            best = fmax(best, proj_dir(cc[d], ss[d], P.vx[k] * (1.0 / GRIDD), P.vy[k] * (1.0 / GRIDD)));
+        uint32_t edges = 0;
+        for (int k = 0; k < m; k++) {
+            const double v = proj_dir(cc[d], ss[d], P.vx[k] * (1.0 / GRIDD), P.vy[k] * (1.0 / GRIDD));
+            if (v >= best - 0x1p-40) edges |= (1u << k) | (1u << (k ? k - 1 : m - 1));
         }
-        for (int64_t i = a + tid; i < e; i += blockDim.x) {
-            double xd = x[i], yd = y[i];
-#pragma unroll
-            for (int q = 0; q < 8; q++) {
-                double v = proj_dir(cc[q], ss[q], xd, yd);
-                if (v > bv[q]) { bv[q] = v; bi[q] = (uint32_t)i; }
+        bv[d] = best;
+        bi[d] = NONE;
+        if (d == 0) notes = 0;
+        for (int c = 0; c < LAB_CLASSES; c++) {
+            const uint64_t b = __ballot((edges >> c) & 1);
+            if (lane == 0) dirs[c] = b;
+        }
+    }
+    const int64_t sa = surv_off[s], sb = surv_off[s + 1];
+    const int64_t share = (sb - sa + gridDim.y - 1) / gridDim.y;
+    const int64_t ba = min(sb, sa + share * blockIdx.y), bb = min(sb, ba + share);
+    if (tid < m) {
+        const double ex = P.ex[tid], ey = P.ey[tid];
+        H.ex[tid] = ex;
+        H.ey[tid] = ey;
+        H.c[tid] = P.c[tid];
+        H.u0[tid] = fma(ex, (double)P.vx[tid], ey * (double)P.vy[tid]);
+        H.scale[tid] = LAB_BINS / fma(ex, ex, ey * ey);
+    }
+    auto heights = [&]() {
+        __syncthreads();                              // bv raised by every wave
+        const int e = tid / LAB_BINS, b = tid % LAB_BINS;
+        if (e < m) {
+            const double ex = H.ex[e], ey = H.ey[e], l2 = fma(ex, ex, ey * ey);
+            const double wx = P.vx[e] * (1.0 / GRIDD), wy = P.vy[e] * (1.0 / GRIDD);
+            double h = INFINITY;
+            for (uint64_t dm = dirs[e]; dm; dm &= dm - 1) {
+                const int d = __builtin_ctzll(dm);
+                const double de = (cc[d] * ex + ss[d] * ey) * (1.0 / GRIDD);       // along the edge
+                const double dn = (cc[d] * ey - ss[d] * ex) * (1.0 / GRIDD);       // outward
+                const double t = de > 0 ? (b + 1.0) / LAB_BINS : (double)b / LAB_BINS;
+                const double g = bv[d] - 0x1p-45 - proj_dir(cc[d], ss[d], wx, wy) - t * de;
+                if (!(g > 0)) h = 0;
+                else if (dn > 0) h = fmin(h, g * __builtin_amdgcn_rcp(dn));
+            }
+            H.h[e][b] = h * l2 * (1.0 - 0x1p-16);     // the reciprocals err by less
+        }
+    };
+    // walk(f): f(direction, value, index, lane in use) for the survivors of
+    // the block's share that can matter and the directions of their class
+    auto walk = [&](bool refresh, auto &&f) {
+        int64_t done = 0, next = 0;
+        for (int64_t c0 = ba, c1; c0 < bb; c0 = c1, done++) {
+            c1 = min(bb, c0 + (c0 == ba ? LAB_THREADS : LAB_CHUNK));
+            if (refresh && done == next) {
+                heights();
+                next = next ? next * 4 : 1;
+            }
+            lab_chunk(L, x, y, surv, c0, c1, P, m, &H);
+            int cls, at, len;
+            for (int b = w; lab_batch(L, b, &cls, &at, &len); b += LAB_WAVES) {
+                const bool has = lane < len;
+                const int i = at + min(lane, len - 1);
+                const double xd = L.x[i], yd = L.y[i];
+                const uint32_t id = L.id[i];
+                uint64_t dm;
+                if (m == 0) dm = ~uint64_t(0);
+                else if (cls < FIXED_SLOTS) dm = uniform_u64(dirs[cls]);
+                else {
+                    dm = 0;
+                    for (uint32_t o = L.out[i]; o; o &= o - 1) dm |= dirs[__ffs((int)o) - 1];
+                    dm = wave_or_u64(dm);
+                }
+                while (dm) {
+                    const int d = __builtin_ctzll(dm);
+                    dm &= dm - 1;
+                    f(d, proj_dir(cc[d], ss[d], xd, yd), id, has);
+                }
             }
         }
-#pragma unroll
-        for (int q = 0; q < 8; q++) {
-            double v = bv[q];
-            uint32_t i = bi[q];
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                double v2 = __shfl_xor(v, o);
-                uint32_t i2 = __shfl_xor(i, o);
-                if (i2 != NONE && (i == NONE || v2 > v || (v2 == v && i2 < i))) { v = v2; i = i2; }
-            }
-            if (lane == 0) { rv[w][q] = v; ri[w][q] = i; }
+    };
+    walk(true, [&](int d, double v, uint32_t id, bool has) {
+        bool hit = has && v >= bv[d];
+        if (!__ballot(hit)) return;
+        if (hit) atomicMax(&bv[d], v);
+        wave_sync();
+        hit = hit && v >= bv[d];
+        const uint64_t who = __ballot(hit);
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&notes, (uint32_t)__popcll(who));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(who & lanemask_lt());
+        if (hit && at < LAB_NOTES) {
+            nv[at] = v;
+            ni[at] = id;
+            nd[at] = (uint8_t)d;
         }
-        __syncthreads();
-        if (tid < 8) {
-            double v = rv[0][tid];
-            uint32_t i = ri[0][tid];
-            for (int ww = 1; ww < (int)(blockDim.x >> 6); ww++) {
-                double v2 = rv[ww][tid];
-                uint32_t i2 = ri[ww][tid];
-                if (i2 != NONE && (i == NONE || v2 > v || (v2 == v && i2 < i))) { v = v2; i = i2; }
+    });
+    __syncthreads();
+    if (notes <= LAB_NOTES) {
+        for (uint32_t i = tid; i < notes; i += LAB_THREADS)
+            if (nv[i] == bv[nd[i]]) atomicMin(&bi[nd[i]], ni[i]);
+    } else {
+        heights();
+        walk(false, [&](int d, double v, uint32_t id, bool has) {
+            if (has && v == bv[d]) atomicMin(&bi[d], id);
+        });
+    }
+    __syncthreads();
+    // a block whose share does not reach the best base vertex reports none
+    if (tid < NCAND) part[(s * gridDim.y + blockIdx.y) * NCAND + tid] = CandPart{bv[tid], bi[tid], 0};
+}
+
+// The extreme of each direction from a set's partials (NONE for an empty
+// set), and cleared counters for k_labels.  One wave per set.
+__global__ void k_cand_pick(const CandPart *__restrict__ part, int split, uint32_t *__restrict__ cand,
+                            uint32_t *__restrict__ cnt) {
+    const int64_t s = blockIdx.x;
+    const int d = threadIdx.x;
+    double v = -INFINITY;
+    uint32_t i = NONE;
+    for (int b = 0; b < split; b++) {
+        const CandPart q = part[(s * split + b) * NCAND + d];
+        if (q.i == NONE) continue;
+        if (q.v > v || (q.v == v && q.i < i)) { v = q.v; i = q.i; }
+    }
+    cand[s * NCAND + d] = i;
+    cnt[s * NCAND + d] = 0;
+}
+
+// (2) cnt[s][d] += #{survivors of the block's share strictly inside
+//     hull(base polygon + e_d)}.  That polygon keeps the base edges that e_d
+//     is strictly inside of and replaces the others (a run of neighbours) by
+//     two edges through e_d; an e_d outside no edge adds nothing.  So a
+//     survivor is inside it iff e_d replaces every edge in its out mask and
+//     it is strictly inside the two new edges.  A base polygon of two
+//     vertices makes a triangle with e_d: three new edges, no base edges.
+__global__ __launch_bounds__(LAB_THREADS) void k_labels(
+    const float *__restrict__ x, const float *__restrict__ y, const Poly *__restrict__ polys,
+    const uint32_t *__restrict__ cand, const uint32_t *__restrict__ surv,
+    const int64_t *__restrict__ surv_off, uint32_t *__restrict__ cnt) {
+    __shared__ LabShared L;
+    __shared__ uint64_t dirs[LAB_CLASSES];            // directions whose e_d replaces edge c
+    __shared__ uint64_t usable;                       // directions that enlarge the polygon
+    __shared__ double ne[3][3][NCAND];                // the new edges' ex, ey, c
+    __shared__ uint32_t wcnt[LAB_WAVES][NCAND];
+    const int64_t s = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const Poly &P = polys[s];
+    const int m = P.m < 3 ? 0 : P.m;
+    if (w == 0) {
+        const int d = lane;
+        const uint32_t e = cand[s * NCAND + d];
+        const double gx = e != NONE ? (double)x[e] * GRIDD : 0, gy = e != NONE ? (double)y[e] * GRIDD : 0;
+        uint32_t gone = 0;
+        bool ok = false;
+        double qx[4], qy[4];                          // the new edges run qx[0] -> qx[1] -> ..
+        int nq = 0;
+        if (e != NONE && m) {
+            int first = 0, last = 0;
+            uint32_t neg = 0;
+            for (int k = 0; k < m; k++) {
+                const double E = edge_eval(P.ex[k], P.ey[k], P.c[k], gx, gy);
+                if (E < 0) neg |= 1u << k;
+                if (!(E > 0)) gone |= 1u << k;
             }
-            cand[s * NCAND + d0 + tid] = i;
+            ok = neg != 0;
+            for (int k = 0; k < m; k++) {
+                const bool in = (gone >> k) & 1;
+                if (in && !((gone >> (k ? k - 1 : m - 1)) & 1)) first = k;
+                if (in && !((gone >> (k + 1 < m ? k + 1 : 0)) & 1)) last = k + 1 < m ? k + 1 : 0;
+            }
+            qx[0] = P.vx[first]; qy[0] = P.vy[first];
+            qx[1] = gx; qy[1] = gy;
+            qx[2] = P.vx[last]; qy[2] = P.vy[last];
+            nq = 2;
+        } else if (e != NONE && P.m == 2) {
+            const double ax = P.vx[0], ay = P.vy[0], bx = P.vx[1], by = P.vy[1];
+            const double o = orient(ax, ay, bx, by, gx, gy);
+            ok = o != 0;
+            qx[0] = qx[3] = ax; qy[0] = qy[3] = ay;
+            qx[1] = o > 0 ? bx : gx; qy[1] = o > 0 ? by : gy;
+            qx[2] = o > 0 ? gx : bx; qy[2] = o > 0 ? gy : by;
+            nq = 3;
         }
-        __syncthreads();
+        if (!ok) gone = 0;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const bool has = ok && k < nq;
+            const double ddx = has ? qx[k + 1] - qx[k] : 0, ddy = has ? qy[k + 1] - qy[k] : 0;
+            ne[k][0][d] = ddx;
+            ne[k][1][d] = ddy;
+            ne[k][2][d] = has ? fma(ddy, qx[k], -(ddx * qy[k])) : 1.0;
+        }
+        for (int c = 0; c < LAB_CLASSES; c++) {
+            const uint64_t b = __ballot((gone >> c) & 1);
+            if (lane == 0) dirs[c] = b;
+        }
+        const uint64_t u = __ballot(ok);
+        if (lane == 0) usable = u;
+    }
+    const int64_t sa = surv_off[s], sb = surv_off[s + 1];
+    uint32_t mine = 0;                                // lane d: the wave's count for direction d
+    for (int64_t c0 = sa + (int64_t)blockIdx.y * LAB_CHUNK; c0 < sb; c0 += (int64_t)gridDim.y * LAB_CHUNK) {
+        lab_chunk(L, x, y, surv, c0, min(sb, c0 + LAB_CHUNK), P, m, nullptr);
+        int cls, at, len;
+        for (int b = w; lab_batch(L, b, &cls, &at, &len); b += LAB_WAVES) {
+            const bool has = lane < len;
+            const int i = at + min(lane, len - 1);
+            const double px = (double)L.x[i] * GRIDD, py = (double)L.y[i] * GRIDD;
+            uint64_t lm = usable;                     // the lane's directions
+            if (cls < FIXED_SLOTS) lm = dirs[cls];
+            else
+                for (uint32_t o = L.out[i]; o; o &= o - 1) lm &= dirs[__ffs((int)o) - 1];
+            if (!has) lm = 0;
+            uint64_t dm = cls < FIXED_SLOTS ? uniform_u64(lm) : wave_or_u64(lm);
+            while (dm) {
+                const int d = __builtin_ctzll(dm);
+                dm &= dm - 1;
+                bool in = (lm >> d) & 1;
+                in = in && edge_eval(ne[0][0][d], ne[0][1][d], ne[0][2][d], px, py) > 0 &&
+                     edge_eval(ne[1][0][d], ne[1][1][d], ne[1][2][d], px, py) > 0;
+                if (m == 0) in = in && edge_eval(ne[2][0][d], ne[2][1][d], ne[2][2][d], px, py) > 0;
+                const uint32_t c = (uint32_t)__popcll(__ballot(in));
+                mine += lane == d ? c : 0;
+            }
+        }
+    }
+    wcnt[w][lane] = mine;
+    __syncthreads();
+    if (tid < NCAND) {
+        uint32_t c = 0;
+        for (int ww = 0; ww < LAB_WAVES; ww++) c += wcnt[ww][tid];
+        if (c) atomicAdd(&cnt[s * NCAND + tid], c);
     }
 }
 
-// (2) gain[s][d] = #{base survivors strictly inside hull(base polygon + e_d)}
-//     / n.  One block per set; thread d < 64 builds the enlarged polygon of
-//     direction d (Andrew's chain over the base vertices plus e_d), then all
-//     threads count survivors against each polygon.
-constexpr int LPV = FIXED_SLOTS + 1;   // vertices of an enlarged polygon
-
-__global__ __launch_bounds__(256) void k_labels(const float *__restrict__ x,
-                                                const float *__restrict__ y,
-                                                const int64_t *__restrict__ off, int64_t n1,
-                                                int64_t S, const Poly *__restrict__ polys,
-                                                const uint32_t *__restrict__ cand,
-                                                const uint32_t *__restrict__ surv,
-                                                const int64_t *__restrict__ surv_off,
-                                                float *__restrict__ gain) {
-    __shared__ double bx[FIXED_SLOTS], by[FIXED_SLOTS];      // base vertices sorted by (x, y)
-    __shared__ uint32_t bid[FIXED_SLOTS];
-    __shared__ int nb;
-    __shared__ double ex[NCAND][LPV], ey[NCAND][LPV], ec[NCAND][LPV];
-    __shared__ int ne[NCAND];
-    __shared__ uint32_t pcnt[4][NCAND];
-    const int64_t s = blockIdx.x;
-    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const int64_t a = set_begin(off, s), n = set_end(off, n1, s) - a;
-    const Poly &P = polys[s];
-    if (tid == 0) {
-        int m = P.m;
-        for (int i = 0; i < m; i++) {
-            uint32_t id = P.verts[i];
-            double gx = (double)x[id] * GRIDD, gy = (double)y[id] * GRIDD;
-            int p = i;
-            while (p > 0 && (bx[p - 1] > gx || (bx[p - 1] == gx && by[p - 1] > gy))) {
-                bx[p] = bx[p - 1]; by[p] = by[p - 1]; bid[p] = bid[p - 1];
-                p--;
-            }
-            bx[p] = gx; by[p] = gy; bid[p] = id;
-        }
-        nb = m;
-    }
-    __syncthreads();
-    if (tid < NCAND) {
-        const int d = tid;
-        double px[LPV], py[LPV];
-        int k = 0;
-        uint32_t e = n > 0 ? cand[s * NCAND + d] : NONE;
-        double gx = 0, gy = 0;
-        bool ins = e != NONE;
-        if (ins) { gx = (double)x[e] * GRIDD; gy = (double)y[e] * GRIDD; }
-        for (int i = 0; i < nb; i++) {   // merge e_d into the sorted base vertices, no repeats
-            if (ins && (gx < bx[i] || (gx == bx[i] && gy <= by[i]))) {
-                if (!(gx == bx[i] && gy == by[i])) { px[k] = gx; py[k] = gy; k++; }
-                ins = false;
-            }
-            px[k] = bx[i]; py[k] = by[i]; k++;
-        }
-        if (ins) { px[k] = gx; py[k] = gy; k++; }
-        int st[2 * LPV + 2];
-        int h = 0;
-        if (k >= 3) {
-            for (int j = 0; j < k; j++) {
-                while (h >= 2 && orient(px[st[h - 2]], py[st[h - 2]], px[st[h - 1]], py[st[h - 1]],
-                                        px[j], py[j]) <= 0)
-                    h--;
-                st[h++] = j;
-            }
-            int lo = h + 1;
-            for (int j = k - 2; j >= 0; j--) {
-                while (h >= lo && orient(px[st[h - 2]], py[st[h - 2]], px[st[h - 1]], py[st[h - 1]],
-                                         px[j], py[j]) <= 0)
-                    h--;
-                st[h++] = j;
-            }
-            h--;
-        }
-        if (h < 3) h = 0;
-        for (int i = 0; i < h; i++) {
-            int p0 = st[i], p1 = st[(i + 1) % h];
-            double ddx = px[p1] - px[p0], ddy = py[p1] - py[p0];
-            ex[d][i] = ddx;
-            ey[d][i] = ddy;
-            ec[d][i] = fma(ddy, px[p0], -(ddx * py[p0]));
-        }
-        ne[d] = h;
-    }
-    __syncthreads();
-    const int64_t sa = surv_off[s], sb = surv_off[s + 1];
-    for (int d = 0; d < NCAND; d++) {
-        const int m = ne[d];
-        uint32_t c = 0;
-        if (m >= 3) {
-            for (int64_t j = sa + tid; j < sb; j += blockDim.x) {
-                uint32_t id = surv[j];
-                double qx = (double)x[id] * GRIDD, qy = (double)y[id] * GRIDD;
-                bool in = true;
-                for (int i = 0; i < m && in; i++) in = edge_eval(ex[d][i], ey[d][i], ec[d][i], qx, qy) > 0;
-                c += in;
-            }
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
-        if (lane == 0) pcnt[w][d] = c;
-    }
-    __syncthreads();
-    if (tid < NCAND) {
-        uint32_t c = 0;
-        for (int ww = 0; ww < (int)(blockDim.x >> 6); ww++) c += pcnt[ww][tid];
-        gain[s * NCAND + tid] = n > 0 ? (float)((double)c / (double)n) : 0.0f;
-    }
+// gain[s][d] = cnt[s][d] / n_s (0 for an empty set).
+__global__ void k_label_gain(const int64_t *__restrict__ off, int64_t n1, int64_t S,
+                             const uint32_t *__restrict__ cnt, float *__restrict__ gain) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, s = i / NCAND;
+    if (s >= S) return;
+    const int64_t n = set_end(off, n1, s) - set_begin(off, s);
+    gain[i] = n > 0 ? (float)((double)cnt[i] / (double)n) : 0.0f;
 }
 
 // Greedy joint training targets (this project's extension).  One block per
