@@ -413,8 +413,29 @@ struct LabShared {
 // e and a survivor whose foot lies in bin b of the edge, -E < h[e][b].
 struct LabHeights {
     double h[FIXED_SLOTS][LAB_BINS];
-    double ex[FIXED_SLOTS], ey[FIXED_SLOTS], c[FIXED_SLOTS];
     double u0[FIXED_SLOTS], scale[FIXED_SLOTS];       // bin = (ex px + ey py - u0) scale
+};
+
+// The base polygon's edges (E > 0: strictly inside).  A polygon of two
+// vertices counts as two edges, there and back, that nothing is inside of;
+// with fewer vertices all points are one, and there are no edges.
+struct LabEdges {
+    double ex[FIXED_SLOTS], ey[FIXED_SLOTS], c[FIXED_SLOTS];
+    __device__ __forceinline__ int load(const Poly &P) {      // every thread; sync before use
+        const int k = threadIdx.x, m = P.m;
+        if (m >= 3) {
+            if (k < m) { ex[k] = P.ex[k]; ey[k] = P.ey[k]; c[k] = P.c[k]; }
+            return m;
+        }
+        if (m == 2 && k < 2) {
+            const double ax = P.vx[k], ay = P.vy[k];
+            const double ddx = P.vx[1 - k] - ax, ddy = P.vy[1 - k] - ay;
+            ex[k] = ddx;
+            ey[k] = ddy;
+            c[k] = fma(ddy, ax, -(ddx * ay));
+        }
+        return m == 2 ? 2 : 0;
+    }
 };
 
 // Load survivors [c0, c1) (at most LAB_CHUNK) into L, grouped by class, less
@@ -422,7 +443,7 @@ struct LabHeights {
 // L.cnt holds the class counts after.
 __device__ __forceinline__ void lab_chunk(LabShared &L, const float *__restrict__ x,
                                           const float *__restrict__ y, const uint32_t *__restrict__ surv,
-                                          int64_t c0, int64_t c1, const Poly &P, int m,
+                                          int64_t c0, int64_t c1, const LabEdges &E, int m,
                                           const LabHeights *H) {
     const int tid = threadIdx.x;
     __syncthreads();                                  // the previous chunk is done with L
@@ -442,7 +463,7 @@ __device__ __forceinline__ void lab_chunk(LabShared &L, const float *__restrict_
         out[q] = 0;
     }
     for (int e = 0; e < m; e++) {
-        const double ex = P.ex[e], ey = P.ey[e], ec = P.c[e];
+        const double ex = E.ex[e], ey = E.ey[e], ec = E.c[e];
 #pragma unroll
         for (int q = 0; q < LAB_PER; q++)
             if (!(edge_eval(ex, ey, ec, (double)px[q] * GRIDD, (double)py[q] * GRIDD) > 0)) out[q] |= 1u << e;
@@ -454,8 +475,8 @@ __device__ __forceinline__ void lab_chunk(LabShared &L, const float *__restrict_
         if (H && cls[q] < FIXED_SLOTS) {
             const int e = cls[q];
             const double gx = (double)px[q] * GRIDD, gy = (double)py[q] * GRIDD;
-            const double b = (fma(H->ex[e], gx, H->ey[e] * gy) - H->u0[e]) * H->scale[e];
-            if (b >= 0 && b < LAB_BINS && -edge_eval(H->ex[e], H->ey[e], H->c[e], gx, gy) < H->h[e][(int)b])
+            const double b = (fma(E.ex[e], gx, E.ey[e] * gy) - H->u0[e]) * H->scale[e];
+            if (b >= 0 && b < LAB_BINS && -edge_eval(E.ex[e], E.ey[e], E.c[e], gx, gy) < H->h[e][(int)b])
                 id[q] = NONE;
         }
         const bool has = id[q] != NONE;
@@ -553,10 +574,11 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     __shared__ uint8_t nd[LAB_NOTES];
     __shared__ uint32_t notes;
     __shared__ LabHeights H;
+    __shared__ LabEdges E;
     const int64_t s = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const Poly &P = polys[s];
-    const int m = P.m < 3 ? 0 : P.m;                  // no interior: every direction for every survivor
+    const int m = E.load(P);
     if (w == 0) {
         const int d = lane;
         cc[d] = dCandCos[d];
@@ -581,10 +603,7 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     const int64_t share = (sb - sa + gridDim.y - 1) / gridDim.y;
     const int64_t ba = min(sb, sa + share * blockIdx.y), bb = min(sb, ba + share);
     if (tid < m) {
-        const double ex = P.ex[tid], ey = P.ey[tid];
-        H.ex[tid] = ex;
-        H.ey[tid] = ey;
-        H.c[tid] = P.c[tid];
+        const double ex = E.ex[tid], ey = E.ey[tid];
         H.u0[tid] = fma(ex, (double)P.vx[tid], ey * (double)P.vy[tid]);
         H.scale[tid] = LAB_BINS / fma(ex, ex, ey * ey);
     }
@@ -592,7 +611,7 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
         __syncthreads();                              // bv raised by every wave
         const int e = tid / LAB_BINS, b = tid % LAB_BINS;
         if (e < m) {
-            const double ex = H.ex[e], ey = H.ey[e], l2 = fma(ex, ex, ey * ey);
+            const double ex = E.ex[e], ey = E.ey[e], l2 = fma(ex, ex, ey * ey);
             const double wx = P.vx[e] * (1.0 / GRIDD), wy = P.vy[e] * (1.0 / GRIDD);
             double h = INFINITY;
             for (uint64_t dm = dirs[e]; dm; dm &= dm - 1) {
@@ -617,7 +636,7 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
                 heights();
                 next = next ? next * 4 : 1;
             }
-            lab_chunk(L, x, y, surv, c0, c1, P, m, &H);
+            lab_chunk(L, x, y, surv, c0, c1, E, m, &H);
             int cls, at, len;
             for (int b = w; lab_batch(L, b, &cls, &at, &len); b += LAB_WAVES) {
                 const bool has = lane < len;
@@ -693,82 +712,66 @@ __global__ void k_cand_pick(const CandPart *__restrict__ part, int split, uint32
 //     is strictly inside of and replaces the others (a run of neighbours) by
 //     two edges through e_d; an e_d outside no edge adds nothing.  So a
 //     survivor is inside it iff e_d replaces every edge in its out mask and
-//     it is strictly inside the two new edges.  A base polygon of two
-//     vertices makes a triangle with e_d: three new edges, no base edges.
+//     it is strictly inside the two new edges.
 __global__ __launch_bounds__(LAB_THREADS) void k_labels(
     const float *__restrict__ x, const float *__restrict__ y, const Poly *__restrict__ polys,
     const uint32_t *__restrict__ cand, const uint32_t *__restrict__ surv,
     const int64_t *__restrict__ surv_off, uint32_t *__restrict__ cnt) {
     __shared__ LabShared L;
     __shared__ uint64_t dirs[LAB_CLASSES];            // directions whose e_d replaces edge c
-    __shared__ uint64_t usable;                       // directions that enlarge the polygon
-    __shared__ double ne[3][3][NCAND];                // the new edges' ex, ey, c
+    __shared__ double ne[2][3][NCAND];                // the new edges' ex, ey, c
+    __shared__ LabEdges E;
     __shared__ uint32_t wcnt[LAB_WAVES][NCAND];
     const int64_t s = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const Poly &P = polys[s];
-    const int m = P.m < 3 ? 0 : P.m;
+    const int m = E.load(P);
+    __syncthreads();
     if (w == 0) {
         const int d = lane;
         const uint32_t e = cand[s * NCAND + d];
-        const double gx = e != NONE ? (double)x[e] * GRIDD : 0, gy = e != NONE ? (double)y[e] * GRIDD : 0;
-        uint32_t gone = 0;
-        bool ok = false;
-        double qx[4], qy[4];                          // the new edges run qx[0] -> qx[1] -> ..
-        int nq = 0;
-        if (e != NONE && m) {
-            int first = 0, last = 0;
-            uint32_t neg = 0;
+        uint32_t gone = 0, neg = 0;
+        int first = 0, last = 0;                      // e_d joins the ends of the run it replaces
+        double gx = 0, gy = 0;
+        if (e != NONE) {
+            gx = (double)x[e] * GRIDD;
+            gy = (double)y[e] * GRIDD;
             for (int k = 0; k < m; k++) {
-                const double E = edge_eval(P.ex[k], P.ey[k], P.c[k], gx, gy);
-                if (E < 0) neg |= 1u << k;
-                if (!(E > 0)) gone |= 1u << k;
+                const double v = edge_eval(E.ex[k], E.ey[k], E.c[k], gx, gy);
+                if (v < 0) neg |= 1u << k;
+                if (!(v > 0)) gone |= 1u << k;
             }
-            ok = neg != 0;
             for (int k = 0; k < m; k++) {
-                const bool in = (gone >> k) & 1;
-                if (in && !((gone >> (k ? k - 1 : m - 1)) & 1)) first = k;
-                if (in && !((gone >> (k + 1 < m ? k + 1 : 0)) & 1)) last = k + 1 < m ? k + 1 : 0;
+                const int prev = k ? k - 1 : m - 1, next = k + 1 < m ? k + 1 : 0;
+                if (!((gone >> k) & 1)) continue;
+                if (!((gone >> prev) & 1)) first = k;
+                if (!((gone >> next) & 1)) last = next;
             }
-            qx[0] = P.vx[first]; qy[0] = P.vy[first];
-            qx[1] = gx; qy[1] = gy;
-            qx[2] = P.vx[last]; qy[2] = P.vy[last];
-            nq = 2;
-        } else if (e != NONE && P.m == 2) {
-            const double ax = P.vx[0], ay = P.vy[0], bx = P.vx[1], by = P.vy[1];
-            const double o = orient(ax, ay, bx, by, gx, gy);
-            ok = o != 0;
-            qx[0] = qx[3] = ax; qy[0] = qy[3] = ay;
-            qx[1] = o > 0 ? bx : gx; qy[1] = o > 0 ? by : gy;
-            qx[2] = o > 0 ? gx : bx; qy[2] = o > 0 ? gy : by;
-            nq = 3;
         }
-        if (!ok) gone = 0;
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            const bool has = ok && k < nq;
-            const double ddx = has ? qx[k + 1] - qx[k] : 0, ddy = has ? qy[k + 1] - qy[k] : 0;
-            ne[k][0][d] = ddx;
-            ne[k][1][d] = ddy;
-            ne[k][2][d] = has ? fma(ddy, qx[k], -(ddx * qy[k])) : 1.0;
-        }
+        if (!neg) gone = 0;
+        const double ux = m ? P.vx[first] : 0, uy = m ? P.vy[first] : 0;
+        const double vx = m ? P.vx[last] : 0, vy = m ? P.vy[last] : 0;
+        ne[0][0][d] = gx - ux;
+        ne[0][1][d] = gy - uy;
+        ne[0][2][d] = fma(gy - uy, ux, -((gx - ux) * uy));
+        ne[1][0][d] = vx - gx;
+        ne[1][1][d] = vy - gy;
+        ne[1][2][d] = fma(vy - gy, gx, -((vx - gx) * gy));
         for (int c = 0; c < LAB_CLASSES; c++) {
             const uint64_t b = __ballot((gone >> c) & 1);
             if (lane == 0) dirs[c] = b;
         }
-        const uint64_t u = __ballot(ok);
-        if (lane == 0) usable = u;
     }
     const int64_t sa = surv_off[s], sb = surv_off[s + 1];
     uint32_t mine = 0;                                // lane d: the wave's count for direction d
     for (int64_t c0 = sa + (int64_t)blockIdx.y * LAB_CHUNK; c0 < sb; c0 += (int64_t)gridDim.y * LAB_CHUNK) {
-        lab_chunk(L, x, y, surv, c0, min(sb, c0 + LAB_CHUNK), P, m, nullptr);
+        lab_chunk(L, x, y, surv, c0, min(sb, c0 + LAB_CHUNK), E, m, nullptr);
         int cls, at, len;
         for (int b = w; lab_batch(L, b, &cls, &at, &len); b += LAB_WAVES) {
             const bool has = lane < len;
             const int i = at + min(lane, len - 1);
             const double px = (double)L.x[i] * GRIDD, py = (double)L.y[i] * GRIDD;
-            uint64_t lm = usable;                     // the lane's directions
+            uint64_t lm = m ? ~uint64_t(0) : 0;       // the lane's directions
             if (cls < FIXED_SLOTS) lm = dirs[cls];
             else
                 for (uint32_t o = L.out[i]; o; o &= o - 1) lm &= dirs[__ffs((int)o) - 1];
@@ -780,7 +783,6 @@ __global__ __launch_bounds__(LAB_THREADS) void k_labels(
                 bool in = (lm >> d) & 1;
                 in = in && edge_eval(ne[0][0][d], ne[0][1][d], ne[0][2][d], px, py) > 0 &&
                      edge_eval(ne[1][0][d], ne[1][1][d], ne[1][2][d], px, py) > 0;
-                if (m == 0) in = in && edge_eval(ne[2][0][d], ne[2][1][d], ne[2][2][d], px, py) > 0;
                 const uint32_t c = (uint32_t)__popcll(__ballot(in));
                 mine += lane == d ? c : 0;
             }
