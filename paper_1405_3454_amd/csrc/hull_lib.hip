@@ -1516,7 +1516,8 @@ static int learned_ensure(hull_ctx *ctx, int64_t B, hipStream_t st) {
         HIPCHECK(hipMalloc(&L.wb, Q_TOTAL * sizeof(bf16_t)));
     }
     if (Bp > L.bcap) {
-        void *old[] = {L.X, L.H1, L.H2, L.dS, L.dZ2, L.dZ1, L.scores, L.part};
+        void *old[] = {L.X, L.H1, L.H2, L.dS, L.dZ2, L.XT, L.H1T, L.H2T, L.dST, L.dZ2T, L.dZ1T, L.scores,
+                       L.part};
         for (void *q : old)
             if (q) HIPCHECK(hipFree(q));
         HIPCHECK(hipMalloc(&L.X, Bp * HBINS * sizeof(bf16_t)));
@@ -1524,7 +1525,12 @@ static int learned_ensure(hull_ctx *ctx, int64_t B, hipStream_t st) {
         HIPCHECK(hipMalloc(&L.H2, Bp * L2 * sizeof(bf16_t)));
         HIPCHECK(hipMalloc(&L.dS, Bp * NOUT * sizeof(bf16_t)));
         HIPCHECK(hipMalloc(&L.dZ2, Bp * L2 * sizeof(bf16_t)));
-        HIPCHECK(hipMalloc(&L.dZ1, Bp * L1 * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.XT, Bp * HBINS * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.H1T, Bp * L1 * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.H2T, Bp * L2 * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.dST, Bp * NOUT * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.dZ2T, Bp * L2 * sizeof(bf16_t)));
+        HIPCHECK(hipMalloc(&L.dZ1T, Bp * L1 * sizeof(bf16_t)));
         HIPCHECK(hipMalloc(&L.scores, Bp * NOUT * sizeof(float)));
         HIPCHECK(hipMalloc(&L.part, Bp * sizeof(float)));
         L.bcap = Bp;
@@ -1532,14 +1538,17 @@ static int learned_ensure(hull_ctx *ctx, int64_t B, hipStream_t st) {
     return HULL_OK;
 }
 
-template <int MODE>
-static int gemm(hull_ctx *ctx, hipStream_t st, const bf16_t *A, int64_t sam, int64_t sak,
-                const bf16_t *B, int64_t sbk, int64_t sbn, int M, int N, int K, const float *bias,
-                const bf16_t *mask, bf16_t *Cb, float *Cf, int ldc) {
-    if (M % GBM || N % GBN || K % GBK) return HULL_EINVAL;
-    dim3 grid(N / GBN, M / GBM);
-    LAUNCH(K_MLP, k_gemm<MODE><<<grid, 256, 0, st>>>(A, sam, sak, B, sbk, sbn, M, N, K, bias, mask,
-                                                     Cb, Cf, ldc));
+static int gemm(hull_ctx *ctx, hipStream_t st, const GemmJob &a, const GemmJob *b = nullptr) {
+    GemmJobs J{};
+    J.n = b ? 2 : 1;
+    J.j[0] = a;
+    if (b) J.j[1] = *b;
+    int tiles = 0;
+    for (int i = 0; i < J.n; i++) {
+        if (J.j[i].K % GKS) return HULL_EINVAL;
+        tiles += J.j[i].tm * J.j[i].tn;
+    }
+    LAUNCH(K_MLP, k_gemm<<<tiles, 256, 0, st>>>(J));
     return HULL_OK;
 }
 
@@ -1549,39 +1558,69 @@ static int gemm(hull_ctx *ctx, hipStream_t st, const bf16_t *A, int64_t sam, int
         if (rc_) return rc_;     \
     } while (0)
 
-// scores (float32 [Bp][64]) of histogram rows hist[B][1024] into L.scores
-static int mlp_forward(hull_ctx *ctx, hipStream_t st, const bf16_t *hist, int64_t B) {
-    LearnedState &L = ctx->learned;
+static int padded_rows(int64_t B) { return (int)std::max<int64_t>(64, (B + 63) / 64 * 64); }
+
+// The network's input as the products read it: hist itself, or a copy where
+// it is not 16-byte aligned.
+static int mlp_input(hull_ctx *ctx, hipStream_t st, const bf16_t *hist, int64_t B, const bf16_t **X) {
     RC(learned_ensure(ctx, B, st));
-    const int Bp = (int)std::max<int64_t>(64, (B + 63) / 64 * 64);
-    LAUNCH(K_MLP, k_pad_rows<<<256, 256, 0, st>>>(hist, B, Bp, HBINS, L.X));
-    RC(gemm<G_RELU_BF16>(ctx, st, L.X, HBINS, 1, L.wb + Q_W1, 1, HBINS, Bp, L1, HBINS,
-                         L.params + P_B1, nullptr, L.H1, nullptr, L1));
-    RC(gemm<G_RELU_BF16>(ctx, st, L.H1, L1, 1, L.wb + Q_W2, 1, L1, Bp, L2, L1, L.params + P_B2,
-                         nullptr, L.H2, nullptr, L2));
-    RC(gemm<G_BIAS_F32>(ctx, st, L.H2, L2, 1, L.wb + Q_W3, 1, L2, Bp, NOUT, L2, L.params + P_B3,
-                        nullptr, nullptr, L.scores, NOUT));
+    *X = hist;
+    if ((uintptr_t)hist & 15) {
+        LAUNCH(K_MLP, k_copy_rows<<<256, 256, 0, st>>>(hist, B * HBINS, ctx->learned.X));
+        *X = ctx->learned.X;
+    }
     return HULL_OK;
 }
 
-// gradients of every parameter into L.grads, from L.dS (bf16 [Bp][64]) and
-// the activations of the last forward pass
-static int mlp_backward(hull_ctx *ctx, hipStream_t st, int64_t B) {
+// scores (float32 [B][64]) of the histogram rows X[B][1024]
+static int mlp_forward(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B, float *scores) {
     LearnedState &L = ctx->learned;
-    const int Bp = (int)std::max<int64_t>(64, (B + 63) / 64 * 64);
-    RC(gemm<G_F32>(ctx, st, L.dS, 1, NOUT, L.H2, L2, 1, NOUT, L2, Bp, nullptr, nullptr, nullptr,
-                   L.grads + P_W3, L2));
-    LAUNCH(K_MLP, k_colsum<<<1, 64, 0, st>>>(L.dS, Bp, NOUT, L.grads + P_B3));
-    RC(gemm<G_MASK_BF16>(ctx, st, L.dS, NOUT, 1, L.wb + Q_W3, L2, 1, Bp, L2, NOUT, nullptr, L.H2,
-                         L.dZ2, nullptr, L2));
-    RC(gemm<G_F32>(ctx, st, L.dZ2, 1, L2, L.H1, L1, 1, L2, L1, Bp, nullptr, nullptr, nullptr,
-                   L.grads + P_W2, L1));
-    LAUNCH(K_MLP, k_colsum<<<(L2 + 255) / 256, 256, 0, st>>>(L.dZ2, Bp, L2, L.grads + P_B2));
-    RC(gemm<G_MASK_BF16>(ctx, st, L.dZ2, L2, 1, L.wb + Q_W2, L1, 1, Bp, L1, L2, nullptr, L.H1,
-                         L.dZ1, nullptr, L1));
-    RC(gemm<G_F32>(ctx, st, L.dZ1, 1, L1, L.X, HBINS, 1, L1, HBINS, Bp, nullptr, nullptr, nullptr,
-                   L.grads + P_W1, HBINS));
-    LAUNCH(K_MLP, k_colsum<<<(L1 + 255) / 256, 256, 0, st>>>(L.dZ1, Bp, L1, L.grads + P_B1));
+    const int Bp = padded_rows(B), tb = Bp / GT;
+    GemmJob g{};
+    g.A = X; g.lda = HBINS; g.B = L.wb + Q_W1; g.ldb = HBINS; g.K = HBINS;
+    g.tm = tb; g.tn = L1 / GT; g.mode = G_RELU_BF16; g.arows = (int)B;
+    g.bias = L.params + P_B1; g.Cb = L.H1; g.CT = L.H1T;
+    RC(gemm(ctx, st, g));
+    g.A = L.H1; g.lda = L1; g.B = L.wb + Q_W2; g.ldb = L1; g.K = L1; g.tn = L2 / GT; g.arows = Bp;
+    g.bias = L.params + P_B2; g.Cb = L.H2; g.CT = L.H2T;
+    RC(gemm(ctx, st, g));
+    g.A = L.H2; g.lda = L2; g.B = L.wb + Q_W3; g.ldb = L2; g.K = L2; g.tn = NOUT / GT; g.mode = G_BIAS_F32;
+    g.bias = L.params + P_B3; g.Cb = g.CT = nullptr; g.Cf = scores; g.crows = (int)B;
+    return gemm(ctx, st, g);
+}
+
+// gradients of every parameter into grads, from L.dS (bf16 [Bp][64]), its
+// transpose, the input's transpose L.XT and the activations of the last
+// forward pass; products that do not need each other share a launch
+static int mlp_backward(hull_ctx *ctx, hipStream_t st, int64_t B, float *grads) {
+    LearnedState &L = ctx->learned;
+    const int Bp = padded_rows(B), tb = Bp / GT;
+    GemmJob w{}, z{};
+    w.mode = G_F32;
+    z.mode = G_MASK_BF16;
+    z.tm = tb;
+    z.arows = Bp;
+    w.A = L.dST; w.lda = Bp; w.B = L.H2T; w.ldb = Bp; w.K = Bp; w.tm = NOUT / GT; w.tn = L2 / GT;
+    w.arows = w.crows = NOUT; w.Cf = grads + P_W3; w.asum = grads + P_B3;
+    z.A = L.dS; z.lda = NOUT; z.B = L.wb + Q_W3T; z.ldb = NOUT; z.K = NOUT; z.tn = L2 / GT;
+    z.mask = L.H2; z.Cb = L.dZ2; z.CT = L.dZ2T;
+    RC(gemm(ctx, st, w, &z));
+    w.A = L.dZ2T; w.B = L.H1T; w.tm = L2 / GT; w.tn = L1 / GT; w.arows = w.crows = L2;
+    w.Cf = grads + P_W2; w.asum = grads + P_B2;
+    z.A = L.dZ2; z.lda = L2; z.B = L.wb + Q_W2T; z.ldb = L2; z.K = L2; z.tn = L1 / GT;
+    z.mask = L.H1; z.Cb = nullptr; z.CT = L.dZ1T;
+    RC(gemm(ctx, st, w, &z));
+    w.A = L.dZ1T; w.B = L.XT; w.tm = L1 / GT; w.tn = HBINS / GT; w.arows = w.crows = L1;
+    w.Cf = grads + P_W1; w.asum = grads + P_B1;
+    return gemm(ctx, st, w);
+}
+
+// the transposes the backward pass reads (dscores: also dS from it)
+static int mlp_backward_prep(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B, const float *dscores) {
+    LearnedState &L = ctx->learned;
+    const int Bp = padded_rows(B);
+    LAUNCH(K_MLP, k_backward_prep<<<dim3(HBINS / 64 + (dscores ? 1 : 0), Bp / 64), 256, 0, st>>>(
+        X, B, Bp, L.XT, dscores, L.dS, L.dST));
     return HULL_OK;
 }
 
@@ -1592,7 +1631,9 @@ static int run_learned_dirs(hull_ctx *ctx, const Plan &p, hipStream_t st, const 
     if (!ctx->learned.loaded) return HULL_ENOMODEL;
     bf16_t *hist = W<bf16_t>(p, p.learn);
     LAUNCH(K_HIST32, k_hist32<<<(unsigned)S, HIST_THREADS, 0, st>>>(x, y, off, n1, S, hist, nullptr));
-    RC(mlp_forward(ctx, st, hist, S));
+    const bf16_t *X = nullptr;
+    RC(mlp_input(ctx, st, hist, S, &X));
+    RC(mlp_forward(ctx, st, X, S, ctx->learned.scores));
     LAUNCH(K_MLP, k_top8<<<(unsigned)((S + 3) / 4), 256, 0, st>>>(ctx->learned.scores, S, ctx->dir_gap, nullptr,
                                                                  W<double>(p, p.setdirs)));
     return HULL_OK;
@@ -1638,9 +1679,12 @@ int hull_mlp_set_params(hull_ctx *ctx, const float *params, int64_t count) {
     HIPCHECK(hipMemcpy(L.params, params, P_TOTAL * sizeof(float), hipMemcpyHostToDevice));
     HIPCHECK(hipMemset(L.m1, 0, P_TOTAL * sizeof(float)));
     HIPCHECK(hipMemset(L.m2, 0, P_TOTAL * sizeof(float)));
-    LAUNCH(K_MLP, k_to_bf16<<<1024, 256, 0, st>>>(L.params + P_W1, (int64_t)L1 * HBINS, L.wb + Q_W1));
-    LAUNCH(K_MLP, k_to_bf16<<<1024, 256, 0, st>>>(L.params + P_W2, (int64_t)L2 * L1, L.wb + Q_W2));
-    LAUNCH(K_MLP, k_to_bf16<<<256, 256, 0, st>>>(L.params + P_W3, (int64_t)NOUT * L2, L.wb + Q_W3));
+    LAUNCH(K_MLP, k_to_bf16<<<1024, 256, 0, st>>>(L.params + P_W1, (int64_t)L1 * HBINS, L.wb + Q_W1, 0,
+                                                   nullptr));
+    LAUNCH(K_MLP, k_to_bf16<<<1024, 256, 0, st>>>(L.params + P_W2, (int64_t)L2 * L1, L.wb + Q_W2, L1,
+                                                   L.wb + Q_W2T));
+    LAUNCH(K_MLP, k_to_bf16<<<256, 256, 0, st>>>(L.params + P_W3, (int64_t)NOUT * L2, L.wb + Q_W3, L2,
+                                                  L.wb + Q_W3T));
     HIPCHECK(hipDeviceSynchronize());
     L.step = 0;
     L.loaded = true;
@@ -1696,10 +1740,9 @@ int hull_mlp_forward(hull_ctx *ctx, const uint16_t *hist, int64_t B, float *scor
     if (!ctx->learned.loaded) return HULL_ENOMODEL;
     hipStream_t st = (hipStream_t)stream;
     HIPCHECK(hipSetDevice(ctx->device));
-    RC(mlp_forward(ctx, st, hist, B));
-    HIPCHECK(hipMemcpyAsync(scores, ctx->learned.scores, B * NOUT * sizeof(float),
-                            hipMemcpyDeviceToDevice, st));
-    return HULL_OK;
+    const bf16_t *X = nullptr;
+    RC(mlp_input(ctx, st, hist, B, &X));
+    return mlp_forward(ctx, st, X, B, scores);
 }
 
 int hull_mlp_backward(hull_ctx *ctx, const uint16_t *hist, const float *dscores, int64_t B,
@@ -1708,13 +1751,11 @@ int hull_mlp_backward(hull_ctx *ctx, const uint16_t *hist, const float *dscores,
     if (!ctx->learned.loaded) return HULL_ENOMODEL;
     hipStream_t st = (hipStream_t)stream;
     HIPCHECK(hipSetDevice(ctx->device));
-    RC(mlp_forward(ctx, st, hist, B));
-    LearnedState &L = ctx->learned;
-    const int Bp = (int)std::max<int64_t>(64, (B + 63) / 64 * 64);
-    LAUNCH(K_MLP, k_pad_f32_bf16<<<256, 256, 0, st>>>(dscores, B, Bp, NOUT, L.dS));
-    RC(mlp_backward(ctx, st, B));
-    HIPCHECK(hipMemcpyAsync(grads, L.grads, P_TOTAL * sizeof(float), hipMemcpyDeviceToDevice, st));
-    return HULL_OK;
+    const bf16_t *X = nullptr;
+    RC(mlp_input(ctx, st, hist, B, &X));
+    RC(mlp_forward(ctx, st, X, B, ctx->learned.scores));
+    RC(mlp_backward_prep(ctx, st, X, B, dscores));
+    return mlp_backward(ctx, st, B, grads);
 }
 
 int hull_mlp_train_step(hull_ctx *ctx, const uint16_t *hist, const float *gain, int64_t B, float lr,
@@ -1723,12 +1764,15 @@ int hull_mlp_train_step(hull_ctx *ctx, const uint16_t *hist, const float *gain, 
     if (!ctx->learned.loaded) return HULL_ENOMODEL;
     hipStream_t st = (hipStream_t)stream;
     HIPCHECK(hipSetDevice(ctx->device));
-    RC(mlp_forward(ctx, st, hist, B));
+    const bf16_t *X = nullptr;
+    RC(mlp_input(ctx, st, hist, B, &X));
     LearnedState &L = ctx->learned;
-    const int Bp = (int)std::max<int64_t>(64, (B + 63) / 64 * 64);
-    LAUNCH(K_MLP, k_loss<<<(unsigned)Bp, 64, 0, st>>>(L.scores, gain, B, Bp, L.dS, L.part));
+    RC(mlp_forward(ctx, st, X, B, L.scores));
+    const int Bp = padded_rows(B);
+    LAUNCH(K_MLP, k_loss<<<(unsigned)Bp, 64, 0, st>>>(L.scores, gain, B, Bp, L.dS, L.dST, L.part));
     LAUNCH(K_MLP, k_loss_sum<<<1, 64, 0, st>>>(L.part, B, loss));
-    RC(mlp_backward(ctx, st, B));
+    RC(mlp_backward_prep(ctx, st, X, B, nullptr));
+    RC(mlp_backward(ctx, st, B, L.grads));
     L.step++;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.0f - std::pow(b1, (float)L.step), c2 = 1.0f - std::pow(b2, (float)L.step);

@@ -59,9 +59,11 @@ constexpr int L1 = 512, L2 = 512, NOUT = NCAND;
 constexpr int64_t P_W1 = 0, P_B1 = P_W1 + (int64_t)L1 * HBINS, P_W2 = P_B1 + L1,
                   P_B2 = P_W2 + (int64_t)L2 * L1, P_W3 = P_B2 + L2, P_B3 = P_W3 + (int64_t)NOUT * L2,
                   P_TOTAL = P_B3 + NOUT;
-// bf16 copies of the weight matrices: W1b | W2b | W3b
+// bf16 copies of the weight matrices: W1b | W2b | W3b, and the transposes of
+// the last two, which the backward products read along their rows
 constexpr int64_t Q_W1 = 0, Q_W2 = Q_W1 + (int64_t)L1 * HBINS, Q_W3 = Q_W2 + (int64_t)L2 * L1,
-                  Q_TOTAL = Q_W3 + (int64_t)NOUT * L2;
+                  Q_W2T = Q_W3 + (int64_t)NOUT * L2, Q_W3T = Q_W2T + (int64_t)L1 * L2,
+                  Q_TOTAL = Q_W3T + (int64_t)L2 * NOUT;
 
 typedef uint16_t bf16_t;   // storage of bfloat16 values
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -161,116 +163,180 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist32(const float *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// C[M x N] = A[M x K] * B[K x N] in bf16 on MFMA (16x16x32), fp32 accumulate,
-// with element (m, k) of A at A[m*sam + k*sak] and (k, n) of B at
-// B[k*sbk + n*sbn].  M and N multiples of 64, K of 32.  Block: 64 x 64 tile,
-// four waves of 32 x 32 (2 x 2 MFMA tiles each).  Epilogue by MODE.
+// The network's products: C[M x N] = A[M x K] * B[N x K]^T in bf16 on MFMA
+// (16x16x32), fp32 accumulation; A and B with K along their rows (row strides
+// lda, ldb), M and N multiples of 32, K of 32.  A block makes a 32 x 32 tile,
+// each of its four waves a 16 x 16 one over the whole of K, step by step into
+// one accumulator (the results are rounded to bf16 for the next layer, so the
+// order of the sums is kept), with the operands loaded straight into the
+// lanes that feed them to MFMA, eight steps ahead.  The products here are
+// small (512 x 512 x 1024 at a batch of 512), so what bounds them is the
+// latency of the loads along K and the launches, not the matrix cores: small
+// tiles put a 512 x 512 product on all 256 CUs, loads far ahead hide the
+// latency, and independent products share a launch.  (64 x 64 tiles with K
+// staged through LDS 32 at a time, one product a launch, took 17 us for the
+// first layer; forward, then forward and backward, with their helpers at a
+// batch of 512: 320 us, now 88 us.)
 enum GemmMode { G_RELU_BF16 = 0, G_BIAS_F32 = 1, G_MASK_BF16 = 2, G_F32 = 3 };
-constexpr int GBM = 64, GBN = 64, GBK = 32, GPAD = 8;
+constexpr int GT = 32;                       // tile side
+constexpr int GKS = 32;                      // K per MFMA step
+constexpr int GAHEAD = 8;                    // steps loaded together (4: 86 us, 16: 97 us for the same)
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_gemm(const bf16_t *__restrict__ A, int64_t sam, int64_t sak,
-                                              const bf16_t *__restrict__ B, int64_t sbk, int64_t sbn,
-                                              int M, int N, int K, const float *__restrict__ bias,
-                                              const bf16_t *__restrict__ mask,
-                                              bf16_t *__restrict__ Cb, float *__restrict__ Cf,
-                                              int ldc) {
-    __shared__ __attribute__((aligned(16))) bf16_t As[GBM][GBK + GPAD];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[GBN][GBK + GPAD];   // n-major
-    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
-    const int wm = w >> 1, wn = w & 1;
-    f32x4 acc[2][2];
+struct GemmJob {
+    const bf16_t *A, *B;
+    int lda, ldb, K;
+    int tm, tn;              // tiles along M and N
+    int mode;
+    int arows;               // rows of A in memory; the others count as zeros
+    int crows;               // rows of C to write (G_BIAS_F32, G_F32)
+    const float *bias;       // G_RELU_BF16, G_BIAS_F32: [N]
+    const bf16_t *mask;      // G_MASK_BF16: C is 0 where mask [M][N] is not positive
+    bf16_t *Cb, *CT;         // bf16 results [M][N] and transposed [N][M] (either may be null)
+    float *Cf;               // fp32 results [M][N]
+    float *asum;             // sums over K of A's rows (bias gradients), or null
+};
+struct GemmJobs {
+    GemmJob j[2];
+    int n;
+};
+
+__global__ __launch_bounds__(256) void k_gemm(GemmJobs jobs) {
+    constexpr int TP = GT + 4;
+    __shared__ __attribute__((aligned(8))) uint16_t tile16[GT * TP];
+    int tile = blockIdx.x;
+    const int first = jobs.j[0].tm * jobs.j[0].tn;
+    const bool second = tile >= first;
+    if (second) tile -= first;
+    const GemmJob &J = jobs.j[second ? 1 : 0];
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = tile / J.tn * GT, n0 = tile % J.tn * GT;
+    const int wm = (w >> 1) * 16, wn = (w & 1) * 16;
+    const int steps = J.K / GKS;
+    const int r = lane & 15, k8 = (lane >> 4) * 8;
+    const bool sums = J.asum && n0 + wn == 0;
+    float as = 0.f;
+    const bool live = m0 + wm + r < J.arows;
+    const bf16_t *pa = J.A + (int64_t)(live ? m0 + wm + r : 0) * J.lda + k8;
+    const bf16_t *pb = J.B + (int64_t)(n0 + wn + r) * J.ldb + k8;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    bf16x8 a[2][GAHEAD], b[2][GAHEAD];
+    auto load = [&](int s0, bf16x8 *va, bf16x8 *vb) {
 #pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int lr = tid >> 2, lk = (tid & 3) * 8;     // loader: row / column and 8 k's
-    for (int k0 = 0; k0 < K; k0 += GBK) {
-        {
-            const bf16_t *pa = A + (int64_t)(m0 + lr) * sam + (int64_t)(k0 + lk) * sak;
-            if (sak == 1) {
-                *reinterpret_cast<uint4 *>(&As[lr][lk]) = *reinterpret_cast<const uint4 *>(pa);
-            } else {
-#pragma unroll
-                for (int t = 0; t < 8; t++) As[lr][lk + t] = pa[t * sak];
-            }
-            const bf16_t *pb = B + (int64_t)(k0 + lk) * sbk + (int64_t)(n0 + lr) * sbn;
-            if (sbk == 1) {
-                *reinterpret_cast<uint4 *>(&Bs[lr][lk]) = *reinterpret_cast<const uint4 *>(pb);
-            } else {
-#pragma unroll
-                for (int t = 0; t < 8; t++) Bs[lr][lk + t] = pb[t * sbk];
-            }
+        for (int d = 0; d < GAHEAD; d++) {
+            const int k = min(s0 + d, steps - 1) * GKS;      // past the end: the last step again
+            va[d] = *reinterpret_cast<const bf16x8 *>(pa + k);
+            vb[d] = *reinterpret_cast<const bf16x8 *>(pb + k);
         }
-        __syncthreads();
-        bf16x8 af[2], bfr[2];
+    };
+    auto multiply = [&](int s0, const bf16x8 *va, const bf16x8 *vb) {
 #pragma unroll
-        for (int i = 0; i < 2; i++) {
-            af[i] = *reinterpret_cast<const bf16x8 *>(&As[wm * 32 + i * 16 + (lane & 15)][(lane >> 4) * 8]);
-            bfr[i] = *reinterpret_cast<const bf16x8 *>(&Bs[wn * 32 + i * 16 + (lane & 15)][(lane >> 4) * 8]);
+        for (int d = 0; d < GAHEAD; d++) {
+            if (s0 + d >= steps) break;
+            const bf16x8 av = live ? va[d] : bf16x8{};
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, vb[d], acc, 0, 0, 0);
+            if (sums)
+#pragma unroll
+                for (int t = 0; t < 8; t++) as += (float)av[t];
         }
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-            for (int j = 0; j < 2; j++)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
+    };
+    load(0, a[0], b[0]);
+    for (int s0 = 0; s0 < steps; s0 += 2 * GAHEAD) {
+        if (s0 + GAHEAD < steps) load(s0 + GAHEAD, a[1], b[1]);
+        multiply(s0, a[0], b[0]);
+        if (s0 + GAHEAD >= steps) break;
+        if (s0 + 2 * GAHEAD < steps) load(s0 + 2 * GAHEAD, a[0], b[0]);
+        multiply(s0 + GAHEAD, a[1], b[1]);
     }
+    if (sums) {
+        as += __shfl_xor(as, 16);
+        as += __shfl_xor(as, 32);
+        if (lane < 16) J.asum[m0 + wm + lane] = as;
+    }
+    // lane: column n0 + n, rows m0 + m .. m0 + m + 3
+    const int n = wn + r, m = wm + (lane >> 4) * 4;
+    const int ldc = J.tn * GT;
+    const int64_t o = (int64_t)(m0 + m) * ldc + n0 + n;
+    float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+    if (J.mode == G_RELU_BF16 || J.mode == G_BIAS_F32) {
+        const float bias = J.bias[n0 + n];
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+        for (int q = 0; q < 4; q++) v[q] += bias;
+    }
+    if (J.mode == G_BIAS_F32 || J.mode == G_F32) {
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int q = 0; q < 4; q++)
+            if (m0 + m + q < J.crows) J.Cf[o + (int64_t)q * ldc] = v[q];
+        return;
+    }
+    uint16_t c[4];
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int m = m0 + wm * 32 + i * 16 + (lane >> 4) * 4 + r;
-                const int n = n0 + wn * 32 + j * 16 + (lane & 15);
-                float v = acc[i][j][r];
-                const int64_t o = (int64_t)m * ldc + n;
-                if (MODE == G_RELU_BF16) Cb[o] = f2bf(fmaxf(v + bias[n], 0.0f));
-                else if (MODE == G_BIAS_F32) Cf[o] = v + bias[n];
-                else if (MODE == G_MASK_BF16) Cb[o] = bf2f(mask[o]) > 0.0f ? f2bf(v) : (bf16_t)0;
-                else Cf[o] = v;
-            }
+    for (int q = 0; q < 4; q++) {
+        if (J.mode == G_RELU_BF16) c[q] = f2bf(fmaxf(v[q], 0.0f));
+        else c[q] = bf2f(J.mask[o + (int64_t)q * ldc]) > 0.0f ? f2bf(v[q]) : (uint16_t)0;
+    }
+    if (J.CT)
+        *reinterpret_cast<ushort4 *>(J.CT + (int64_t)(n0 + n) * (J.tm * GT) + m0 + m) =
+            make_ushort4(c[0], c[1], c[2], c[3]);
+    if (!J.Cb) return;
+#pragma unroll
+    for (int q = 0; q < 4; q++) tile16[(m + q) * TP + n] = c[q];
+    __syncthreads();
+    const int tr = tid >> 3, tc = (tid & 7) * 4;         // four neighbours of one row per thread
+    *reinterpret_cast<ushort4 *>(J.Cb + (int64_t)(m0 + tr) * ldc + n0 + tc) =
+        *reinterpret_cast<const ushort4 *>(&tile16[tr * TP + tc]);
 }
 
-// Column sums of a bf16 matrix X[rows][cols] (bias gradients), fp32.
-__global__ void k_colsum(const bf16_t *__restrict__ X, int rows, int cols, float *__restrict__ out) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float acc = 0.0f;
-    for (int r = 0; r < rows; r++) acc += bf2f(X[(int64_t)r * cols + c]);
-    out[c] = acc;
+// float32 -> bf16 copy (weights after an update, or inputs); with cols > 0
+// also the transpose of the [n / cols][cols] matrix
+__global__ void k_to_bf16(const float *__restrict__ src, int64_t n, bf16_t *__restrict__ dst, int cols,
+                          bf16_t *__restrict__ dstT) {
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
+         i += int64_t(gridDim.x) * blockDim.x) {
+        const bf16_t v = f2bf(src[i]);
+        dst[i] = v;
+        if (cols) dstT[(i % cols) * (n / cols) + i / cols] = v;
+    }
 }
 
-// float32 -> bf16 copy (weights after an update, or inputs)
-__global__ void k_to_bf16(const float *__restrict__ src, int64_t n, bf16_t *__restrict__ dst) {
+// Histogram rows into the network's input matrix, for arrays that are not
+// 16-byte aligned.
+__global__ void k_copy_rows(const bf16_t *__restrict__ src, int64_t n, bf16_t *__restrict__ dst) {
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
          i += int64_t(gridDim.x) * blockDim.x)
-        dst[i] = f2bf(src[i]);
+        dst[i] = src[i];
 }
 
-// Copy (and zero-pad) histogram rows into the network's input matrix.
-__global__ void k_pad_rows(const bf16_t *__restrict__ src, int64_t rows, int64_t rows_pad, int cols,
-                           bf16_t *__restrict__ dst) {
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < rows_pad * cols;
-         i += int64_t(gridDim.x) * blockDim.x)
-        dst[i] = (i / cols) < rows ? src[i] : (bf16_t)0;
-}
-
-// float32 rows -> zero-padded bf16 rows
-__global__ void k_pad_f32_bf16(const float *__restrict__ src, int64_t rows, int64_t rows_pad,
-                               int cols, bf16_t *__restrict__ dst) {
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < rows_pad * cols;
-         i += int64_t(gridDim.x) * blockDim.x)
-        dst[i] = (i / cols) < rows ? f2bf(src[i]) : (bf16_t)0;
+// What the backward products read along the batch: the histograms'
+// transpose XT [1024][Bp] and, from float32 output gradients (if given), dS
+// [Bp][64] in bf16 and its transpose.  Rows past the batch are zeros.  A
+// block turns a 64 x 64 tile through LDS; the last column of blocks does dS.
+__global__ __launch_bounds__(256) void k_backward_prep(const bf16_t *__restrict__ X, int64_t B, int Bp,
+                                                       bf16_t *__restrict__ XT, const float *__restrict__ d,
+                                                       bf16_t *__restrict__ dS, bf16_t *__restrict__ dST) {
+    __shared__ bf16_t t[64][66];
+    const int b0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+    const bool grad = blockIdx.x == HBINS / 64;
+    const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    for (int r = r0; r < 64; r += 4) {
+        const int64_t b = b0 + r;
+        bf16_t v = 0;
+        if (b < B) v = grad ? f2bf(d[b * NOUT + c]) : X[b * HBINS + c0 + c];
+        if (grad) dS[b * NOUT + c] = v;
+        t[r][c] = v;
+    }
+    __syncthreads();
+    for (int r = r0; r < 64; r += 4) {
+        if (grad) dST[(int64_t)r * Bp + b0 + c] = t[c][r];
+        else XT[(int64_t)(c0 + r) * Bp + b0 + c] = t[c][r];
+    }
 }
 
 // Loss: targets t = gain / max(gain) per set (0 when no direction gains),
 // L = mean over sets and directions of (score - t)^2.  dS = dL/dscore (bf16
 // for the backward products); per-set partial losses for a fixed-order sum.
 __global__ void k_loss(const float *__restrict__ scores, const float *__restrict__ gain, int64_t B,
-                       int64_t Bp, bf16_t *__restrict__ dS, float *__restrict__ part) {
+                       int64_t Bp, bf16_t *__restrict__ dS, bf16_t *__restrict__ dST,
+                       float *__restrict__ part) {
     const int64_t b = blockIdx.x;
     const int d = threadIdx.x;   // 64 threads
     float s = 0.0f, t = 0.0f;
@@ -283,12 +349,13 @@ __global__ void k_loss(const float *__restrict__ scores, const float *__restrict
         s = scores[b * NOUT + d];
     }
     float diff = b < B ? s - t : 0.0f;
-    dS[b * NOUT + d] = f2bf(2.0f * diff / (float)(B * NOUT));
+    const bf16_t g16 = f2bf(2.0f * diff / (float)(B * NOUT));
+    dS[b * NOUT + d] = g16;
+    dST[(int64_t)d * Bp + b] = g16;
     float sq = diff * diff;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o);
     if (d == 0) part[b] = sq;
-    (void)Bp;
 }
 
 __global__ void k_loss_sum(const float *__restrict__ part, int64_t B, float *__restrict__ loss) {
@@ -317,6 +384,10 @@ __global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float
         else if (i >= P_W2 && i < P_B2) q = Q_W2 + (i - P_W2);
         else if (i >= P_W3 && i < P_B3) q = Q_W3 + (i - P_W3);
         if (q >= 0) wb[q] = f2bf(wi);
+        int64_t qt = -1;  // and in the transposes
+        if (i >= P_W2 && i < P_B2) qt = Q_W2T + ((i - P_W2) % L1) * L2 + (i - P_W2) / L1;
+        else if (i >= P_W3 && i < P_B3) qt = Q_W3T + ((i - P_W3) % L2) * NOUT + (i - P_W3) / L2;
+        if (qt >= 0) wb[qt] = f2bf(wi);
     }
 }
 
@@ -984,8 +1055,9 @@ struct LearnedState {
     int64_t step = 0;          // Adam step counter
     float *params = nullptr, *grads = nullptr, *m1 = nullptr, *m2 = nullptr;
     bf16_t *wb = nullptr;      // bf16 weight matrices
-    bf16_t *X = nullptr, *H1 = nullptr, *H2 = nullptr, *dS = nullptr, *dZ2 = nullptr,
-           *dZ1 = nullptr;
+    bf16_t *X = nullptr, *H1 = nullptr, *H2 = nullptr, *dS = nullptr, *dZ2 = nullptr;
+    // transposes, [columns][rows]
+    bf16_t *XT = nullptr, *H1T = nullptr, *H2T = nullptr, *dST = nullptr, *dZ2T = nullptr, *dZ1T = nullptr;
     float *scores = nullptr, *part = nullptr;
 };
 
@@ -994,8 +1066,8 @@ static size_t learned_ws_bytes(int64_t S) {
 }
 
 static void learned_free(LearnedState &L) {
-    void *ps[] = {L.params, L.grads, L.m1, L.m2, L.wb, L.X, L.H1, L.H2, L.dS, L.dZ2, L.dZ1,
-                  L.scores, L.part};
+    void *ps[] = {L.params, L.grads, L.m1, L.m2, L.wb, L.X, L.H1, L.H2, L.dS, L.dZ2, L.XT, L.H1T, L.H2T,
+                  L.dST, L.dZ2T, L.dZ1T, L.scores, L.part};
     for (void *p : ps)
         if (p) (void)hipFree(p);
     L = LearnedState();
