@@ -16,6 +16,7 @@
 #include "k_learned.hip"
 #include "k_refine.hip"
 #include "k_hull3d.hip"
+#include "k_small.hip"
 
 using namespace hg;
 
@@ -181,7 +182,7 @@ static Plan make_plan(int64_t n, int64_t S, int64_t W) {
         return r;
     };
     p.tcap = n / TILE + 2 * S + 2;
-    p.u0cap = n / CHAIN_C + 2;
+    p.u0cap = n / CHAIN_C + n / SM_CAP + 2;
     p.nwave = W;
     // list entries: the discard pass's regions (q = ceil(T / W) tiles of
     // points per wave) end by T * TILE
@@ -843,6 +844,50 @@ static int prepare(hull_ctx *ctx, int64_t n, int64_t S, hipStream_t st, Plan *p)
     return rc;
 }
 
+// Inputs that one block per set takes from the points to the hull (k_small).
+// One set: up to 8192 points, which always fit the block's LDS (square, disk,
+// annulus, circle at 8192: 30, 37, 49 and 341 us against 98, 103, 106 and 381
+// with the launches of the general path; at 16384 points a circle, all of
+// them hull vertices, takes 809 us against 434).  Several sets: the host knows
+// the total only, so the bound keeps a set that holds most of it small (64
+// sets of 500 to 8000 points 55 us against 232, 500 of 500 points 50 against
+// 241; one of 30000 points and one of ten 98 us against 161, but one of 240000
+// and fifteen of 1000 would take 557 against 189).
+constexpr int64_t SMALL_ONE = SM_CAP, SMALL_PER_SET = 4096, SMALL_BATCH = 1 << 18;
+static bool small_input(int64_t n_total, int64_t S, bool learned) {
+    if (learned || S > SM_SETS) return false;
+    return n_total <= (S == 1 ? SMALL_ONE : std::min(SMALL_BATCH, SMALL_ONE + SMALL_PER_SET * S));
+}
+
+static int run_small(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x, const float *y,
+                     int64_t n_total, const int64_t *off, int64_t n1, int64_t S, bool nofilter, bool refine,
+                     uint32_t *hull, int64_t *hoff_out, int64_t *h_out) {
+    SmallWs ws;
+    ws.idx = W<uint32_t>(p, p.surv);
+    ws.key = W<uint64_t>(p, p.keys0);
+    ws.edge = W<uint16_t>(p, p.hkeys);
+    ws.cidx = W<uint32_t>(p, p.cidx);
+    ws.ckey = W<uint64_t>(p, p.ckeys);
+    ws.sortA = W<uint64_t>(p, p.keysA);
+    ws.sortB = W<uint64_t>(p, p.keysB);
+    ws.lo[0] = W<uint64_t>(p, p.lo0);
+    ws.lo[1] = W<uint64_t>(p, p.lo1);
+    ws.up[0] = W<uint64_t>(p, p.up0);
+    ws.up[1] = W<uint64_t>(p, p.up1);
+    ws.ccnt = W<uint32_t>(p, p.ccnt);
+    ws.u0cap = p.u0cap;
+    ws.hull = W<uint32_t>(p, p.hpos);
+    ws.hcnt = W<uint32_t>(p, p.hcnt);
+    ws.scnt = W<int32_t>(p, p.bounds);
+    LAUNCH(K_FINAL, k_small<SM_THREADS><<<(unsigned)S, SM_THREADS, 0, st>>>(x, y, n_total, phase_of(x), off, n1, ctx->preset,
+                                                             ctx->dirs, nofilter, refine, ws, hull, h_out,
+                                                             ctx->counts));
+    if (off)
+        LAUNCH(K_FINAL, k_small_out<<<(unsigned)std::min<int64_t>(64, (S + 3) / 4), 256, 0, st>>>(
+            off, S, ws.hcnt, ws.scnt, ws.hull, hoff_out, hull, ctx->counts));
+    return HULL_OK;
+}
+
 // Full method for S sets (off == nullptr: one set of n1 points).
 static int run_compute(hull_ctx *ctx, hipStream_t st, const float *x, const float *y,
                        int64_t n_total, const int64_t *off, int64_t n1, int64_t S, int flags,
@@ -864,6 +909,9 @@ static int run_compute(hull_ctx *ctx, hipStream_t st, const float *x, const floa
     const bool refine = !(flags & (HULL_NOREFINE | HULL_NOFILTER));
     const int64_t *cnt = ctx->counts;
     int64_t *segcnt = W<int64_t>(p, p.segcnt);
+    if (small_input(n_total, S, learned) && (off ? hoff_out != nullptr : h_out != nullptr))
+        return run_small(ctx, p, st, x, y, n_total, off, n1, S, flags & HULL_NOFILTER, refine, hull, hoff_out,
+                         h_out);
     // one set: the farthest keys of refinement round 0's children start cleared
     const bool one_ref = S == 1 && refine;
     LAUNCH(K_MISC, k_counts_init<<<1, 64, 0, st>>>(

@@ -154,22 +154,14 @@ __device__ int serial_chain(uint64_t *st, int n) {
     return h;
 }
 
-__global__ __launch_bounds__(256) void k_chain_chunks(const uint64_t *__restrict__ keys,
-                                                      const int64_t *__restrict__ cnt_ptr,
-                                                      uint64_t *__restrict__ lo,
-                                                      uint64_t *__restrict__ up,
-                                                      uint32_t *__restrict__ lo_cnt,
-                                                      uint32_t *__restrict__ up_cnt,
-                                                      int *__restrict__ big) {
-    __shared__ Chain0Lds lds[4];
-    Chain0Lds &L = lds[threadIdx.x >> 6];
+// Chunks wave, wave + nw, ... of the cnt sorted keys.
+__device__ __forceinline__ void chain_chunks(const uint64_t *__restrict__ keys, int64_t cnt,
+                                             uint64_t *__restrict__ lo, uint64_t *__restrict__ up,
+                                             uint32_t *__restrict__ lo_cnt, uint32_t *__restrict__ up_cnt,
+                                             Chain0Lds &L, int64_t wave, int64_t nw) {
     const int lane = lane_id();
     const uint64_t lt = lanemask_lt();
-    const int64_t cnt = *cnt_ptr;
-    if (big && blockIdx.x == 0 && threadIdx.x == 0) *big = 0;   // raised by k_chain_sets
     const int64_t U = (cnt + CHAIN_C - 1) / CHAIN_C;
-    const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nw = (int64_t(gridDim.x) * blockDim.x) >> 6;
     if (U == 0 && wave == 0 && lane == 0) {   // no candidates: the chains are empty
         lo_cnt[0] = 0;
         up_cnt[0] = 0;
@@ -181,8 +173,9 @@ __global__ __launch_bounds__(256) void k_chain_chunks(const uint64_t *__restrict
     bool valid[4];
     const int64_t p = a + 4 * lane;
     if (p + 4 <= e) {
-        const ulonglong2 *q = reinterpret_cast<const ulonglong2 *>(keys + p);
-        ulonglong2 v0 = q[0], v1 = q[1];
+        typedef uint64_t u64x2 __attribute__((ext_vector_type(2), aligned(8)));
+        const u64x2 *q = reinterpret_cast<const u64x2 *>(keys + p);
+        const u64x2 v0 = q[0], v1 = q[1];
         k[0] = v0.x; k[1] = v0.y; k[2] = v1.x; k[3] = v1.y;
 #pragma unroll
         for (int i = 0; i < 4; i++) valid[i] = true;
@@ -274,6 +267,20 @@ __global__ __launch_bounds__(256) void k_chain_chunks(const uint64_t *__restrict
     }
     wave_sync();       // the next chunk reuses the wave's LDS
     }
+}
+
+__global__ __launch_bounds__(256) void k_chain_chunks(const uint64_t *__restrict__ keys,
+                                                      const int64_t *__restrict__ cnt_ptr,
+                                                      uint64_t *__restrict__ lo,
+                                                      uint64_t *__restrict__ up,
+                                                      uint32_t *__restrict__ lo_cnt,
+                                                      uint32_t *__restrict__ up_cnt,
+                                                      int *__restrict__ big) {
+    __shared__ Chain0Lds lds[4];
+    if (big && blockIdx.x == 0 && threadIdx.x == 0) *big = 0;   // raised by k_chain_sets
+    const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nw = (int64_t(gridDim.x) * blockDim.x) >> 6;
+    chain_chunks(keys, *cnt_ptr, lo, up, lo_cnt, up_cnt, lds[threadIdx.x >> 6], wave, nw);
 }
 
 // Index of the first element of src[lo..hi) whose set equals set(src[hi-1]).
@@ -634,6 +641,31 @@ __device__ __forceinline__ bool block_group(const uint32_t *__restrict__ cin, in
     return tot > MERGE_CAP || (nonempty <= 1 && tot > BLOCK_COPY_MIN);
 }
 
+// One kind's groups of a level: the wave's share wave, wave + nw, ... of
+// those a wave takes, then the block's share block, block + nblocks, ... of
+// the others.  Every thread of the block calls it.
+__device__ __forceinline__ void chain_merge(bool upper, const uint64_t *__restrict__ in,
+                                            const uint32_t *__restrict__ cin, int64_t U, int64_t R, int lev,
+                                            uint64_t *__restrict__ out, uint32_t *__restrict__ cout,
+                                            int64_t wave, int64_t nw, int64_t block, int64_t nblocks,
+                                            uint64_t *__restrict__ buf, int64_t *__restrict__ goff,
+                                            int *__restrict__ ne, int64_t *__restrict__ pref,
+                                            int64_t *__restrict__ psrc, int64_t *sh) {
+    const int64_t V = (U + CHAIN_G - 1) / CHAIN_G;
+    for (int64_t v = wave; v < V; v += nw) {        // groups the count actually has
+        if (block_group(cin, U, v)) continue;
+        if (!upper) merge_group<false>(in, cin, U, R, v, lev, out, cout, buf, goff, ne, pref, psrc);
+        else merge_group<true>(in, cin, U, R, v, lev, out, cout, buf, goff, ne, pref, psrc);
+        wave_sync();
+    }
+    __syncthreads();
+    for (int64_t v = block; v < V; v += nblocks) {
+        if (!block_group(cin, U, v)) continue;     // uniform over the block
+        if (!upper) merge_group_block<false>(in, cin, U, R, v, out, cout, sh);
+        else merge_group_block<true>(in, cin, U, R, v, out, cout, sh);
+    }
+}
+
 __global__ __launch_bounds__(256) void k_chain_merge(const uint64_t *__restrict__ lo_in,
                                                      const uint64_t *__restrict__ up_in,
                                                      const uint32_t *__restrict__ lo_cin,
@@ -669,25 +701,12 @@ __global__ __launch_bounds__(256) void k_chain_merge(const uint64_t *__restrict_
         (blockIdx.y == 0 ? lo_cout : up_cout)[0] = 0;
     __shared__ int64_t moff[4][CHAIN_G + 1], mpre[4][CHAIN_G], msrc[4][CHAIN_G];
     __shared__ int mne[4][CHAIN_G];
-    uint64_t *buf = mbuf[threadIdx.x >> 6];
-    int64_t *goff = moff[threadIdx.x >> 6];
-    const uint32_t *cin = blockIdx.y == 0 ? lo_cin : up_cin;
-    for (int64_t v = wave; v < V; v += nw) {        // groups the count actually has
-        if (block_group(cin, U, v)) continue;
-        const int wv = threadIdx.x >> 6;
-        if (blockIdx.y == 0)
-            merge_group<false>(lo_in, lo_cin, U, R, v, lev, lo_out, lo_cout, buf, goff, mne[wv], mpre[wv], msrc[wv]);
-        else
-            merge_group<true>(up_in, up_cin, U, R, v, lev, up_out, up_cout, buf, goff, mne[wv], mpre[wv], msrc[wv]);
-        wave_sync();
-    }
     __shared__ int64_t sh[3 + 2 * CHAIN_G];
-    __syncthreads();
-    for (int64_t v = blockIdx.x; v < V; v += gridDim.x) {
-        if (!block_group(cin, U, v)) continue;     // uniform over the block
-        if (blockIdx.y == 0) merge_group_block<false>(lo_in, lo_cin, U, R, v, lo_out, lo_cout, sh);
-        else merge_group_block<true>(up_in, up_cin, U, R, v, up_out, up_cout, sh);
-    }
+    const int wv = threadIdx.x >> 6;
+    const bool upper = blockIdx.y == 1;
+    chain_merge(upper, upper ? up_in : lo_in, upper ? up_cin : lo_cin, U, R, lev, upper ? up_out : lo_out,
+                upper ? up_cout : lo_cout, wave, nw, blockIdx.x, gridDim.x, mbuf[wv], moff[wv], mne[wv],
+                mpre[wv], msrc[wv], sh);
 }
 
 // Several sets: after the chunk chains, each set's keys are one range

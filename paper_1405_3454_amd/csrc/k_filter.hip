@@ -492,6 +492,165 @@ __device__ __forceinline__ double edge_eval(double ex, double ey, double c, doub
     return fma(ex, py, fma(-ey, px, c));
 }
 
+// Polygon of the slot points sl[MAX_SLOTS] (NONE: empty) into P, by the
+// block's first wave; every thread calls it.  ts: the set's tiles, which size
+// its rows.  The step is a chain of latencies, so its points stay in the
+// lanes' registers: neighbours in a chain are found in the chain's lane mask
+// and read across the wave (position lists in LDS, with barriers between,
+// took 13k cycles for 16 slots, this 9k).
+struct PolyScratch {
+    double gx[MAX_SLOTS], gy[MAX_SLOTS];   // slot points (grid units), then sorted
+    uint32_t gi[MAX_SLOTS];
+    double vx[MAX_SLOTS], vy[MAX_SLOTS];   // polygon vertices
+    uint32_t vi[MAX_SLOTS];
+};
+
+// One pruning pass over the points of a chain (lane l's point is in it when
+// bit l of mask is set, in lane order): drops the points that their two
+// neighbours make no strict vertex of the lower (upper) chain.
+template <bool UPPER>
+__device__ __forceinline__ uint64_t poly_prune(uint64_t mask, double ax, double ay) {
+    const int lane = lane_id();
+    const uint64_t below = mask & lanemask_lt(), above = mask & ~lanemask_lt() & ~(uint64_t(1) << lane);
+    const int pv = below ? 63 - __clzll((long long)below) : lane;
+    const int nx = above ? __ffsll((unsigned long long)above) - 1 : lane;
+    const double px = __shfl(ax, pv), py = __shfl(ay, pv), qx = __shfl(ax, nx), qy = __shfl(ay, nx);
+    const double o = orient(px, py, ax, ay, qx, qy);
+    const bool drop = below && above && (UPPER ? o >= 0 : o <= 0);
+    return mask & ~__ballot(drop);
+}
+
+__device__ __forceinline__ void build_polygon(PolyScratch &G, const uint32_t *sl, const float *__restrict__ x,
+                                              const float *__restrict__ y, int64_t ts, Poly &P) {
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    if (w == 0) {
+        // the slot points sorted by (x, y, index, slot): a rank per lane;
+        // empty slots sort last
+        const uint32_t gi = lane < MAX_SLOTS ? sl[lane] : NONE;
+        const bool valid = gi != NONE;
+        double ax = valid ? grid_of(x[gi]) : 1e300, ay = valid ? grid_of(y[gi]) : 1e300;
+        if (lane < MAX_SLOTS) {
+            G.gx[lane] = ax;
+            G.gy[lane] = ay;
+            G.gi[lane] = gi;
+        }
+        wave_sync();
+        int rank = 0;
+        // (bitwise logic: with && the loads of by and bj wait in branches for
+        // the comparison before them, 400 cycles a step)
+#pragma unroll 4
+        for (int j = 0; j < MAX_SLOTS; j++) {
+            const double bx = G.gx[j], by = G.gy[j];
+            const uint32_t bj = G.gi[j];
+            const int lx = bx < ax, ex = bx == ax, ly = by < ay, ey = by == ay;
+            const int li = (int)(bj < gi) | ((int)(bj == gi) & (int)(j < lane));
+            rank += lx | (ex & (ly | (ey & li)));
+        }
+        const int k = __popcll(__ballot(valid));
+        wave_sync();
+        if (valid) {
+            G.gx[rank] = ax;
+            G.gy[rank] = ay;
+            G.gi[rank] = gi;
+        }
+        wave_sync();
+        uint32_t ai = NONE;
+        ax = ay = 0.0;
+        if (lane < k) {
+            ax = G.gx[lane];
+            ay = G.gy[lane];
+            ai = G.gi[lane];
+        }
+        // Andrew's chains: repeated coordinates dropped (the lowest index
+        // comes first), then both chains pruned in parallel: a point on or
+        // beyond the segment of its two neighbours is no strict vertex, and
+        // once a pass drops nothing each chain turns strictly one way at every
+        // point (each earlier pass drops a point)
+        const double bx = __shfl_up(ax, 1), by = __shfl_up(ay, 1);
+        const uint64_t uniq = __ballot(lane < k && (lane == 0 || ax != bx || ay != by));
+        const int u = __popcll(uniq);
+        uint64_t ml = uniq, mu = uniq;
+#pragma unroll 1
+        for (int pass = 0; pass < 2 * MAX_SLOTS; pass++) {
+            const uint64_t l2 = poly_prune<false>(ml, ax, ay), u2 = poly_prune<true>(mu, ax, ay);
+            if (l2 == ml && u2 == mu) break;
+            ml = l2;
+            mu = u2;
+        }
+        // counter-clockwise from the lowest point: the lower chain, then the
+        // upper chain's interior backwards
+        const uint64_t lt = lanemask_lt();
+        const int nl = __popcll(ml), nu = __popcll(mu), ru = __popcll(mu & lt);
+        const int h = u <= 1 ? u : nl + nu - 2;
+        int pos = -1;
+        if ((ml >> lane) & 1) pos = __popcll(ml & lt);
+        else if (((mu >> lane) & 1) && ru > 0 && ru < nu - 1) pos = nl + (nu - 2 - ru);
+        if (pos >= 0) {
+            G.vx[pos] = ax;
+            G.vy[pos] = ay;
+            G.vi[pos] = ai;
+        }
+        wave_sync();
+        // lane e: vertex e and the edge from it to vertex e + 1
+        const int e = lane;
+        const bool ev = e < h && h >= 3;
+        int ya = 0;
+        if (e < MAX_SLOTS) {
+            const double vx = e < h ? G.vx[e] : 0.0, vy = e < h ? G.vy[e] : 0.0;
+            P.verts[e] = e < h ? G.vi[e] : NONE;
+            P.vx[e] = (int32_t)vx;
+            P.vy[e] = (int32_t)vy;
+            if (ev) {
+                const int bb = e + 1 < h ? e + 1 : 0;
+                const double ex = G.vx[bb] - vx, ey = G.vy[bb] - vy;
+                P.ex[e] = ex;
+                P.ey[e] = ey;
+                P.c[e] = fma(ey, vx, -(ex * vy));
+                ya = (int)vy;
+            } else {
+                P.ex[e] = 0.0;
+                P.ey[e] = 0.0;
+                P.c[e] = 1.0;
+            }
+        }
+        // the vertices' y-range (grid units, below 2^24)
+        const int ylo = (int)wave_min_u32(ev ? (uint32_t)ya : 0xFFFFFFFFu);
+        const int yhi = 0x7FFFFFFF - (int)wave_min_u32(ev ? (uint32_t)(0x7FFFFFFF - ya) : 0xFFFFFFFFu);
+        if (lane == 0) {
+            P.m = h;
+            if (h < 3) {
+                P.c[0] = -1.0;    // nothing strictly inside
+                P.yspan = -1;
+                P.ky_lo = 0;
+                P.shift = 0;
+                P.ymin = 1;
+                P.ymax = 0;
+            } else {
+                // the rows stop a thin sliver (1/1024 of the height) short of
+                // the top and bottom vertices, where the polygon narrows to a
+                // point or an edge and a row could hold no quick-accept span;
+                // points in the slivers take the exact test
+                const int d = (yhi - ylo) >> 10;
+                P.ymin = ylo;
+                P.ymax = yhi;
+                P.ky_lo = ylo + d;
+                P.yspan = (yhi - d) - (ylo + d);
+                // rows for the set's size: 8 per tile of points, 16 to
+                // SPAN_ROWS (a small set gains nothing from a fine table it
+                // would spend longer building and loading than using; one row
+                // per two tiles made the 4096-set batch's discard pass 10 %
+                // slower for 40 us less building)
+                int rows = 16;
+                while (rows < SPAN_ROWS && rows < 8 * ts) rows <<= 1;
+                int sh = 0;
+                while ((P.yspan >> sh) >= rows) sh++;
+                P.shift = sh;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 constexpr int POLY_THREADS = 512;
 constexpr int POLY_SPLIT = 16;     // blocks per set sharing the extremes pass's partials
 
@@ -519,13 +678,7 @@ __global__ __launch_bounds__(POLY_THREADS) void k_polygon(
     __shared__ SlotBest wbest[POLY_THREADS / WAVE][MAX_SLOTS];
     __shared__ SlotBest spart[POLY_SPLIT][MAX_SLOTS];  // the set's shares (last block)
     __shared__ uint32_t sl[MAX_SLOTS];
-    __shared__ double gx[MAX_SLOTS], gy[MAX_SLOTS];   // slot points (grid units)
-    __shared__ double sx[MAX_SLOTS], sy[MAX_SLOTS];   // sorted by (x, y, index, slot)
-    __shared__ uint32_t si[MAX_SLOTS];
-    __shared__ int st[2 * MAX_SLOTS + 2];
-    __shared__ int lc[MAX_SLOTS], uc[MAX_SLOTS], hcount;   // lower / upper chain positions
-    __shared__ double vx[MAX_SLOTS], vy[MAX_SLOTS];   // polygon vertices
-    __shared__ int nvalid;
+    __shared__ PolyScratch G;
     __shared__ bool last;
     __shared__ Poly P;
     const int64_t s = blockIdx.x;
@@ -665,160 +818,7 @@ __global__ __launch_bounds__(POLY_THREADS) void k_polygon(
         vals_out[s * NS + tid] = val;
     }
 
-    // sort the slot points by (x, y, index, slot) with a rank per thread
-    if (tid < MAX_SLOTS) {
-        uint32_t i = sl[tid];
-        gx[tid] = i != NONE ? grid_of(x[i]) : 0.0;
-        gy[tid] = i != NONE ? grid_of(y[i]) : 0.0;
-    }
-    if (w == 0) {
-        uint64_t vm = __ballot(tid < MAX_SLOTS && sl[tid < MAX_SLOTS ? tid : 0] != NONE);
-        if (tid == 0) nvalid = __popcll(vm);
-    }
-    __syncthreads();
-    if (tid < MAX_SLOTS && sl[tid] != NONE) {
-        double ax = gx[tid], ay = gy[tid];
-        uint32_t ai = sl[tid];
-        int rank = 0;
-        for (int j = 0; j < MAX_SLOTS; j++) {
-            uint32_t bj = sl[j];
-            if (bj == NONE || j == tid) continue;
-            double bx = gx[j], by = gy[j];
-            bool less = bx < ax || (bx == ax && (by < ay || (by == ay && (bj < ai ||
-                                                     (bj == ai && j < tid)))));
-            rank += less;
-        }
-        sx[rank] = ax;
-        sy[rank] = ay;
-        si[rank] = ai;
-    }
-    __syncthreads();
-
-    // Andrew's chains on the sorted slot points, by the first wave: repeated
-    // coordinates dropped (the lowest index stays first), then the lower and
-    // the upper chain pruned in parallel: a point on or beyond the segment of
-    // its two neighbours is no strict vertex, and once a pass drops nothing
-    // each list turns strictly one way at every point (at most MAX_SLOTS
-    // passes: each earlier pass drops a point)
-    if (w == 0) {
-        const uint64_t lt = lanemask_lt();
-        const int k = nvalid;
-        bool keep = false;
-        double ax = 0.0, ay = 0.0;
-        uint32_t ai = 0;
-        if (lane < k) {
-            ax = sx[lane];
-            ay = sy[lane];
-            ai = si[lane];
-            keep = lane == 0 || ax != sx[lane - 1] || ay != sy[lane - 1];
-        }
-        const uint64_t bk = __ballot(keep);
-        const int u = __popcll(bk);
-        wave_sync();
-        if (keep) {
-            const int p = __popcll(bk & lt);
-            sx[p] = ax;
-            sy[p] = ay;
-            si[p] = ai;
-            lc[p] = p;
-            uc[p] = p;
-        }
-        wave_sync();
-        int nl = u, nu = u;
-        for (int pass = 0; pass < MAX_SLOTS; pass++) {
-            bool kl = lane < nl, ku = lane < nu;
-            const int ml = kl ? lc[lane] : 0, mu = ku ? uc[lane] : 0;
-            if (lane > 0 && lane + 1 < nl) {
-                const int pa = lc[lane - 1], pc = lc[lane + 1];
-                if (orient(sx[pa], sy[pa], sx[ml], sy[ml], sx[pc], sy[pc]) <= 0) kl = false;
-            }
-            if (lane > 0 && lane + 1 < nu) {
-                const int pa = uc[lane - 1], pc = uc[lane + 1];
-                if (orient(sx[pa], sy[pa], sx[mu], sy[mu], sx[pc], sy[pc]) >= 0) ku = false;
-            }
-            const uint64_t bl = __ballot(kl), bu = __ballot(ku);
-            wave_sync();
-            if (kl) lc[__popcll(bl & lt)] = ml;
-            if (ku) uc[__popcll(bu & lt)] = mu;
-            wave_sync();
-            const int nl2 = __popcll(bl), nu2 = __popcll(bu);
-            if (nl2 == nl && nu2 == nu) break;
-            nl = nl2;
-            nu = nu2;
-        }
-        // counter-clockwise from the lowest point: the lower chain, then the
-        // upper chain's interior backwards
-        const int h = u == 0 ? 0 : (u == 1 ? 1 : nl + nu - 2);
-        if (lane < h) st[lane] = lane < nl ? lc[lane] : uc[nu - 2 - (lane - nl)];
-        if (lane == 0) hcount = h;
-    }
-    __syncthreads();
-    if (w == 0) {     // lane e: vertex e and the edge from it to vertex e + 1
-        const int h = hcount;
-        const int e = lane;
-        const bool ev = e < h && h >= 3;
-        int ya = 0;
-        if (e < MAX_SLOTS) {
-            double ax = 0.0, ay = 0.0;
-            if (e < h) {
-                ax = sx[st[e]];
-                ay = sy[st[e]];
-                vx[e] = ax;
-                vy[e] = ay;
-            }
-            P.verts[e] = e < h ? si[st[e]] : NONE;
-            P.vx[e] = e < h ? (int32_t)ax : 0;
-            P.vy[e] = e < h ? (int32_t)ay : 0;
-            if (ev) {
-                const int bb = st[(e + 1) % h];
-                const double ex = sx[bb] - ax, ey = sy[bb] - ay;
-                P.ex[e] = ex;
-                P.ey[e] = ey;
-                P.c[e] = fma(ey, ax, -(ex * ay));
-                ya = (int)ay;
-            } else {
-                P.ex[e] = 0.0;
-                P.ey[e] = 0.0;
-                P.c[e] = 1.0;
-            }
-        }
-        // the vertices' y-range (grid units, below 2^24)
-        const int ylo = (int)wave_min_u32(ev ? (uint32_t)ya : 0xFFFFFFFFu);
-        const int yhi = 0x7FFFFFFF - (int)wave_min_u32(ev ? (uint32_t)(0x7FFFFFFF - ya) : 0xFFFFFFFFu);
-        if (lane == 0) {
-            P.m = h;
-            if (h < 3) {
-                P.c[0] = -1.0;    // nothing strictly inside
-                P.yspan = -1;
-                P.ky_lo = 0;
-                P.shift = 0;
-                P.ymin = 1;
-                P.ymax = 0;
-            } else {
-                // the rows stop a thin sliver (1/1024 of the height) short of
-                // the top and bottom vertices, where the polygon narrows to a
-                // point or an edge and a row could hold no quick-accept span;
-                // points in the slivers take the exact test
-                const int d = (yhi - ylo) >> 10;
-                P.ymin = ylo;
-                P.ymax = yhi;
-                P.ky_lo = ylo + d;
-                P.yspan = (yhi - d) - (ylo + d);
-                // rows for the set's size: 8 per tile of points, 16 to
-                // SPAN_ROWS (a small set gains nothing from a fine table it
-                // would spend longer building and loading than using; one row
-                // per two tiles made the 4096-set batch's discard pass 10 %
-                // slower for 40 us less building)
-                const int64_t ts = tile_off[s + 1] - tile_off[s];
-                int rows = 16;
-                while (rows < SPAN_ROWS && rows < 8 * ts) rows <<= 1;
-                int sh = 0;
-                while ((P.yspan >> sh) >= rows) sh++;
-                P.shift = sh;
-            }
-        }
-    }
-    __syncthreads();
+    build_polygon(G, sl, x, y, tile_off[s + 1] - tile_off[s], P);
     {   // the record, a word per thread
         const uint32_t *src = reinterpret_cast<const uint32_t *>(&P);
         uint32_t *dst = reinterpret_cast<uint32_t *>(polys + s);
@@ -831,7 +831,7 @@ __global__ __launch_bounds__(POLY_THREADS) void k_polygon(
             REdge r = redge_empty();
             if (e < m) {
                 const int b = (e + 1) % m;
-                r = REdge{(int32_t)vx[e], (int32_t)vy[e], (int32_t)vx[b], (int32_t)vy[b]};
+                r = REdge{(int32_t)G.vx[e], (int32_t)G.vy[e], (int32_t)G.vx[b], (int32_t)G.vy[b]};
             }
             rtab[s * RE_CAP + e] = r;
             rfar[s * RE_CAP + e] = 0;
