@@ -215,8 +215,8 @@ static Plan make_plan(int64_t n, int64_t S, int64_t W) {
     p.hoff = take((S + 1) * 8);
     p.hkeys = take(n * 8 + 16);
     p.hpos = take(n * 4 + 16);
-    p.sstat = take(SORT_BLOCKS * RADIX * 8);                    // look-back entries of the ranges
-    p.sgst = take(SORT_MAX_PASSES * (RADIX + 1) * 4);          // digit totals, range counters
+    p.sstat = take(sort_tiles_max(n) * RADIX * 8);              // look-back entries of the tiles
+    p.sgst = take(sizeof(SortState));
     p.consts = take(8 * 8);
     p.err = take(8);
     p.setdirs = take(S * MAX_DIRS * 2 * 8);
@@ -634,22 +634,26 @@ static int run_discard_append(hull_ctx *ctx, const Plan &p, hipStream_t st, cons
     return HULL_OK;
 }
 
+// Passes over the x and set digits of the hull stage's keys.
 static int sort_passes(int64_t S) {
     int setbits = 0;
     while (setbits < 16 && (int64_t(1) << setbits) < S) setbits++;
-    return (48 + setbits + 7) / 8;
+    return (48 + setbits + 7) / 8 - Y_DIGITS;
 }
 
-// Sort keys (count at *cnt) ascending; returns the buffer holding the result.
-// Several sets (S > 1): the keys arrive grouped by set in set order, and each
-// set is sorted alone in LDS; the radix passes run only when that is not so
-// or a set is too large for it.
+// Sort keys (count at *cnt) ascending by the digits first .. first + passes -
+// 1; returns the buffer holding the result.  first = Y_DIGITS: point keys for
+// the hull stage, ordered by (set, x), runs of equal (set, x) as k_sort_ties
+// leaves them.  Several sets (S > 1): the keys arrive grouped by set in set
+// order, and each set is sorted alone in LDS; the radix passes run only when
+// that is not so or a set is too large for it.
 static int run_sort(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint64_t *keys,
-                    const int64_t *cnt, int passes, int64_t S, const uint64_t **sorted) {
+                    const int64_t *cnt, int64_t ncap, int first, int passes, int64_t S,
+                    const uint64_t **sorted) {
     if (passes > SORT_MAX_PASSES) return HULL_EINVAL;
     uint64_t *A = W<uint64_t>(p, p.keysA), *B = W<uint64_t>(p, p.keysB);
     unsigned long long *status = W<unsigned long long>(p, p.sstat);
-    uint32_t *gst = W<uint32_t>(p, p.sgst);
+    SortState *state = W<SortState>(p, p.sgst);
     int *seg = S > 1 ? reinterpret_cast<int *>(W<int64_t>(p, p.consts) + 4) : nullptr;
     const uint64_t *in = keys;
     uint64_t *out = A;
@@ -657,19 +661,32 @@ static int run_sort(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint64_t
     // small counts: sorted at once into that buffer; otherwise the passes'
     // state is cleared (and the sets' fallback flag)
     LAUNCH(K_SORT_HIST, k_sort_small<<<1 + SMALL_CLEAR_BLOCKS, SMALL_THREADS, 0, st>>>(
-        keys, cnt, fin, status, gst, seg));
+        keys, cnt, fin, status, state, seg));
+    if (ncap <= SORT_SMALL && !seg) {          // the count cannot be larger
+        *sorted = fin;
+        return HULL_OK;
+    }
     if (seg) {
         int64_t *starts = W<int64_t>(p, p.bounds);    // S + 1 entries (the final stage rewrites it)
         LAUNCH(K_SORT_HIST, k_set_starts<<<(unsigned)ctx->cus * 4, 256, 0, st>>>(keys, cnt, S, starts, seg));
         LAUNCH(K_SORT_HIST, k_sort_sets<<<(unsigned)std::min<int64_t>(S, (int64_t)ctx->cus * 2), SEG_THREADS, 0,
                                           st>>>(keys, cnt, S, starts, fin, seg));
     }
-    LAUNCH(K_SORT_HIST, k_sort_prep<<<SORT_BLOCKS, SORT_THREADS, 0, st>>>(keys, cnt, passes, gst, seg));
+    const unsigned g = (unsigned)std::min<int64_t>(SORT_BLOCKS, sort_tiles_max(ncap));
+    LAUNCH(K_SORT_HIST, k_sort_prep<<<g, SORT_THREADS, 0, st>>>(keys, cnt, first, passes, state, seg));
     for (int ps = 0; ps < passes; ps++) {
-        LAUNCH(K_SORT_SCATTER, k_sort_pass<<<SORT_BLOCKS, SORT_THREADS, 0, st>>>(
-            in, cnt, ps, gst, status, gst + SORT_MAX_PASSES * RADIX + ps, out, seg));
+        LAUNCH(K_SORT_SCATTER, k_sort_pass<<<g, SORT_THREADS, 0, st>>>(in, cnt, ps, first + ps, state, status, out,
+                                                                       seg));
         in = out;
         out = (out == A) ? B : A;
+    }
+    if (first == Y_DIGITS) {                   // `out` is free: it lists the long runs (17 keys or more each)
+        auto *runs = reinterpret_cast<LongRun *>(out);
+        uint64_t *keys_s = in == A ? A : B;
+        LAUNCH(K_SORT_SCATTER, k_sort_ties<<<(unsigned)std::min<int64_t>((int64_t)ctx->cus * 8, ncap / TIE_TILE + 1),
+                                             256, 0, st>>>(keys_s, cnt, state, runs, seg));
+        LAUNCH(K_SORT_SCATTER, k_sort_long<<<(unsigned)ctx->cus, TIE_THREADS, 0, st>>>(keys_s, cnt, state, runs,
+                                                                                      seg));
     }
     *sorted = in;
     return HULL_OK;
@@ -693,7 +710,7 @@ static int run_hull(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint32_t
                     const uint64_t *keys, const int64_t *cnt, int64_t ncap, int64_t S,
                     int64_t *hoff, uint32_t *hull, int64_t *h_out = nullptr) {
     const uint64_t *sorted = nullptr;
-    int rc = run_sort(ctx, p, st, keys, cnt, sort_passes(S), S, &sorted);
+    int rc = run_sort(ctx, p, st, keys, cnt, ncap, Y_DIGITS, sort_passes(S), S, &sorted);
     if (rc) return rc;
     uint64_t *lo[2] = {W<uint64_t>(p, p.lo0), W<uint64_t>(p, p.lo1)};
     uint64_t *up[2] = {W<uint64_t>(p, p.up0), W<uint64_t>(p, p.up1)};
@@ -736,10 +753,11 @@ static int run_hull(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint32_t
     uint32_t *hcnt = W<uint32_t>(p, p.hcnt);
     uint64_t *hkeys = W<uint64_t>(p, p.hkeys);
     uint32_t *hpos = W<uint32_t>(p, p.hpos);
+    const unsigned lookup_blocks = (unsigned)std::min<int64_t>(2048, ncap / 256 + 1);
     if (S == 1) {
         LAUNCH(K_FINAL, k_hull_final1<<<1, 1024, 0, st>>>(lo[cur], up[cur], locnt[cur], upcnt[cur],
                                                           hoff, hkeys, hpos, hull, h_out));
-        LAUNCH(K_LOOKUP, k_hull_lookup<<<2048, 256, 0, st>>>(idx, keys, cnt, S, hoff, hkeys, hpos, hull));
+        LAUNCH(K_LOOKUP, k_hull_lookup<<<lookup_blocks, 256, 0, st>>>(idx, keys, cnt, S, hoff, hkeys, hpos, hull));
         return HULL_OK;
     }
     int64_t *scount = W<int64_t>(p, p.consts) + 1;   // = S
@@ -753,7 +771,7 @@ static int run_hull(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint32_t
     LAUNCH(K_FINAL, k_hull_emit<<<dim3(256, 2), 256, 0, st>>>(lo[cur], up[cur], locnt[cur],
                                                               upcnt[cur], bounds, S, hoff, hkeys,
                                                               hpos, hull));
-    LAUNCH(K_LOOKUP, k_hull_lookup<<<2048, 256, 0, st>>>(idx, keys, cnt, S, hoff, hkeys, hpos, hull));
+    LAUNCH(K_LOOKUP, k_hull_lookup<<<lookup_blocks, 256, 0, st>>>(idx, keys, cnt, S, hoff, hkeys, hpos, hull));
     if (h_out) LAUNCH(K_MISC, k_copy_count<<<1, 64, 0, st>>>(hoff + S, h_out));
     return HULL_OK;
 }

@@ -60,6 +60,7 @@ __device__ __forceinline__ bool drop_mid(uint64_t a, uint64_t b, uint64_t c) {
 constexpr uint32_t YMIN_ID = 0x7fffffffu;   // identity of min over y < 2^24
 constexpr int32_t YMAX_ID = -1;
 constexpr int PRUNE_PASSES = 24;
+constexpr int JOIN_PASSES = 256;            // a join of long chains: a pass per point walked back
 
 struct Chain0Lds {
     uint64_t list[2][2][CHAIN_C];   // [lower, upper][ping-pong]
@@ -103,36 +104,43 @@ __device__ __forceinline__ int32_t scan_max_down(int32_t v) {
 }
 
 // One pruning pass over src[0..n) into dst; returns the kept count (uniform).
-// dst may be src: a round reads its 64 entries and their neighbours before
+// dst may be src: a step reads its U * 64 entries and their neighbours before
 // it writes, and a kept entry never moves up, so no later read is clobbered.
-template <bool UPPER>
+// The reads of a step are in flight together: U = 4 for long lists, which are
+// bound by their latency, U = 1 for a chunk's (mostly under 64 entries).
+template <bool UPPER, int U = 4>
 __device__ __forceinline__ int prune_pass(const uint64_t *src, uint64_t *dst, int n,
                                           uint64_t lt) {
     const int lane = lane_id();
     int out = 0;
-    for (int r = 0; r < n; r += WAVE) {
-        const int i = r + lane;
-        bool keep = false;
-        uint64_t me = 0;
-        if (i < n) {
-            me = src[i];
-            keep = true;
-            if (i > 0) {
-                const uint64_t pv = src[i - 1];
-                if (pv == me) {
-                    keep = false;                  // a repeated key
-                } else if (i + 1 < n) {
-                    const uint64_t nx = src[i + 1];
-                    const uint32_t sm = key_set(me);
-                    if (nx != me && key_set(pv) == sm && key_set(nx) == sm &&
-                        drop_mid<UPPER>(pv, me, nx))
-                        keep = false;
-                }
-            }
+    for (int r = 0; r < n; r += U * WAVE) {
+        uint64_t me[U], pv[U], nx[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int i = min(r + u * WAVE + lane, n - 1);
+            me[u] = src[i];
+            pv[u] = src[max(i - 1, 0)];
+            nx[u] = src[min(i + 1, n - 1)];
         }
-        const uint64_t b = __ballot(keep);
-        if (keep) dst[out + __popcll(b & lt)] = me;
-        out += __popcll(b);
+        bool keep[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int i = r + u * WAVE + lane;
+            const uint32_t sm = key_set(me[u]);
+            // a repeated key goes, and a point of one set with both its
+            // neighbours that makes no strict turn
+            const int first = i == 0, last = i + 1 >= n;
+            const int same = pv[u] == me[u];
+            const int mid = (int)(nx[u] != me[u]) & (int)(key_set(pv[u]) == sm) & (int)(key_set(nx[u]) == sm) &
+                            (int)drop_mid<UPPER>(pv[u], me[u], nx[u]);
+            keep[u] = (int)(i < n) & (first | ((same ^ 1) & (last | (mid ^ 1))));
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint64_t b = __ballot(keep[u]);
+            if (keep[u]) dst[out + __popcll(b & lt)] = me[u];
+            out += __popcll(b);
+        }
     }
     return out;
 }
@@ -243,8 +251,8 @@ __device__ __forceinline__ void chain_chunks(const uint64_t *__restrict__ keys, 
     int cur = 0, pass = 0;
     bool moved = true;
     for (; moved && pass < PRUNE_PASSES; pass++) {
-        const int ml = prune_pass<false>(L.list[0][cur], L.list[0][1 - cur], nl, lt);
-        const int mu = prune_pass<true>(L.list[1][cur], L.list[1][1 - cur], nu, lt);
+        const int ml = prune_pass<false, 1>(L.list[0][cur], L.list[0][1 - cur], nl, lt);
+        const int mu = prune_pass<true, 1>(L.list[1][cur], L.list[1][1 - cur], nu, lt);
         moved = ml != nl || mu != nu;
         nl = ml;
         nu = mu;
@@ -478,29 +486,26 @@ __device__ void merge_group(const uint64_t *__restrict__ in, const uint32_t *__r
         stage_group(in, R, u0, (int)min((int64_t)CHAIN_G, U - u0), incl, M, goff, buf);
         if (!parallel_join<UPPER>(buf, goff, (int)min((int64_t)CHAIN_G, U - u0), mine, o, &len, ne, pref,
                                   psrc)) {
-            for (int g = 0; g < CHAIN_G && u0 + g < U; g++) {
-                const int64_t m = __shfl(mine, g), og = __shfl(incl, g) - m;
-                if (m == 0) continue;
-                const uint64_t *c = buf + og;
-                int64_t b;
-                len = bridge<UPPER>(buf, len, tailseg, c, m, &b);
-                if (b < m) {
-                    int64_t ls = last_seg_start(c, b, m);
-                    int64_t newtail;
-                    if (ls > b) newtail = len + (ls - b);
-                    else newtail = (len > 0 && key_set(buf[len - 1]) == key_set(c[b])) ? tailseg : len;
-                    // move c[b..m) down to buf[len..): len <= og + b, copy forward
-                    for (int64_t i0 = 0; i0 < m - b; i0 += WAVE) {
-                        int64_t i = i0 + lane;
-                        uint64_t val = i < m - b ? c[b + i] : 0;
-                        wave_sync();
-                        if (i < m - b) buf[len + i] = val;
-                        wave_sync();
-                    }
-                    len += m - b;
-                    tailseg = newtail;
-                }
+            // chains that end up with fewer than two points (more chains than
+            // the hull has vertices): the list is pruned like a chunk.  (Joined
+            // left to right, one bridge after another, the 2^23 points' group
+            // took 172 us instead of 40.)
+            const uint64_t lt = lanemask_lt();
+            int n = (int)M;
+            bool moved = true;
+            for (int pass = 0; moved && pass < JOIN_PASSES; pass++) {
+                const int m2 = prune_pass<UPPER>(buf, buf, n, lt);
+                moved = m2 != n;
+                n = m2;
+                wave_sync();
             }
+            if (moved) {
+                int h = 0;
+                if (lane == 0) h = serial_chain<UPPER>(buf, n);
+                wave_sync();
+                n = __builtin_amdgcn_readlane(h, 0);
+            }
+            len = n;
             for (int64_t i = lane; i < len; i += WAVE) o[i] = buf[i];
         }
     } else if (M <= MERGE_CAP) {
@@ -991,6 +996,8 @@ __global__ __launch_bounds__(1024) void k_hull_final1(const uint64_t *__restrict
     }
 }
 
+constexpr int LOOKUP_BITS = 1 << 17;
+
 // Map hull keys back to point indices: every candidate (index, key) whose key
 // is a hull vertex of its set lowers that vertex's slot to its index.
 __global__ __launch_bounds__(256) void k_hull_lookup(const uint32_t *__restrict__ idx,
@@ -1002,18 +1009,57 @@ __global__ __launch_bounds__(256) void k_hull_lookup(const uint32_t *__restrict_
                                                      const uint32_t *__restrict__ hpos,
                                                      uint32_t *__restrict__ hull) {
     const int64_t n = *cnt_ptr;
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += int64_t(gridDim.x) * blockDim.x) {
-        uint64_t k = keys[i];
-        uint32_t s = key_set(k);
-        if (s >= S) continue;
-        int64_t a = hoff[s], b = hoff[s + 1];
-        if (a == b) continue;
-        int64_t r = a + count_less(hkeys, a, b, k);
+    // One set with many candidates and few vertices: two hashes of each
+    // vertex's key in LDS pass over nearly all of the others without a search
+    // (a search is ten dependent loads, and a wave waits for any lane's: one
+    // hash, one false hit in a hundred, was no faster than searching).
+    __shared__ uint32_t bits[LOOKUP_BITS / 32];
+    const int64_t nh = S == 1 ? hoff[1] : 0;
+    const bool hashed = nh > 0 && nh <= LOOKUP_BITS / 64 && n >= (int64_t)LOOKUP_BITS * 4;
+    auto hash = [](uint64_t k) { return k * 0x9E3779B97F4A7C15ull; };
+    auto bit = [](uint64_t h, int j) { return (uint32_t)(h >> (j ? 20 : 44)) & (LOOKUP_BITS - 1); };
+    if (hashed) {
+        for (int i = threadIdx.x; i < LOOKUP_BITS / 32; i += blockDim.x) bits[i] = 0;
+        __syncthreads();
+        for (int64_t i = threadIdx.x; i < nh; i += blockDim.x) {
+            const uint64_t h = hash(hkeys[i]);
+            atomicOr(&bits[bit(h, 0) >> 5], 1u << (bit(h, 0) & 31));
+            atomicOr(&bits[bit(h, 1) >> 5], 1u << (bit(h, 1) & 31));
+        }
+        __syncthreads();
+    }
+    auto look = [&](int64_t i, uint64_t k) {
+        const uint32_t s = key_set(k);
+        if (s >= S) return;
+        const int64_t a = hoff[s], b = hoff[s + 1];
+        if (a == b) return;
+        const int64_t r = a + count_less(hkeys, a, b, k);
         if (r < b && hkeys[r] == k) {
-            uint32_t p = hpos[r];
+            const uint32_t p = hpos[r];
             if (p < (uint64_t)(b - a)) atomicMin(&hull[a + p], idx[i]);
         }
+    };
+    const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, nt = int64_t(gridDim.x) * blockDim.x;
+    if (hashed) {
+        constexpr int U = 8;          // keys in flight
+        for (int64_t i0 = t0; i0 < n; i0 += U * nt) {
+            uint64_t k[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) k[u] = keys[min(i0 + u * nt, n - 1)];
+            uint32_t hit = 0;
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint64_t h = hash(k[u]);
+                const uint32_t a = bit(h, 0), b = bit(h, 1);
+                hit |= ((bits[a >> 5] >> (a & 31)) & (bits[b >> 5] >> (b & 31)) & 1u) << u;
+            }
+            if (!hit) continue;
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                if (((hit >> u) & 1) && i0 + u * nt < n) look(i0 + u * nt, k[u]);
+        }
+    } else {
+        for (int64_t i = t0; i < n; i += nt) look(i, keys[i]);
     }
 }
 

@@ -641,7 +641,7 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
         auto prune = [&](uint64_t *l, int c) {
             bool moved = true;
             for (int pass = 0; moved && pass < PRUNE_PASSES; pass++) {
-                const int c2 = kind ? prune_pass<true>(l, l, c, lt) : prune_pass<false>(l, l, c, lt);
+                const int c2 = kind ? prune_pass<true, 1>(l, l, c, lt) : prune_pass<false, 1>(l, l, c, lt);
                 moved = c2 != c;
                 c = c2;
                 wave_sync();

@@ -2,67 +2,79 @@
 // pass).  The key count is read from device memory so the whole sort can run
 // behind earlier kernels without a host round trip.
 //
-// Decomposition: the keys are cut into at most SORT_BLOCKS contiguous ranges
-// of qq tiles of SORT_TILE keys.  One kernel counts every pass's digits over
-// all keys (global digit totals, hence each digit's start in the output).
-// Then one kernel per pass: a block claims the next range (a counter, so
-// ranges are taken in order), counts its digits, publishes the counts and
-// sums those of the ranges before it by decoupled look-back (a range's entry
-// holds its own counts or, once known, the counts of all ranges up to it),
-// and scatters its keys: each tile ranked stably with wave ballots (peers =
-// lanes with the same digit) plus per-wave digit counts in LDS, so equal
-// digits keep their input order across lanes, waves, tiles and ranges.
+// One kernel counts the digits of every pass over all keys (the digits'
+// starts in each pass's output).  Then one kernel per pass, which reads each
+// key once: a block claims the next tile of keys (a counter, so tiles are
+// taken in order), holds it in registers, ranks its digits with wave ballots
+// and per-wave counters in LDS, publishes the tile's digit counts, sums those
+// of the tiles before it by decoupled look-back (a tile's entry holds its own
+// counts or, once known, the counts of all tiles up to it), and writes the
+// keys out digit by digit through LDS.  Tiles are 6144 keys (of 2^23 keys a
+// pass takes 64 us; 4096-key tiles 77, 8192-key tiles 69), 2048 for up to
+// 2^20 keys (which would otherwise occupy few CUs).  A pass is bound by its
+// scattered writes and the look-back: a copy of the keys takes 26 us; with
+// two reads of 2048-key tiles behind eight barriers each it took 102.
+//
+// The hull stage needs its keys (set, x, y) in order of (set, x) only: among
+// points of one x the chains use the lowest and the highest.  So its sort
+// skips the three passes over y, and k_sort_ties then orders each run of
+// equal (set, x): short runs in place, a long one by its lowest key, copies
+// of it, and its highest key (the keys between them are never vertices, and
+// the index lookup reads the candidates, not the sorted keys).
 #include "hg_device.h"
 
 namespace hg {
 
-constexpr int SORT_THREADS = 256;
-constexpr int SORT_ROUNDS = 8;
-constexpr int SORT_TILE = SORT_THREADS * SORT_ROUNDS;   // 2048 keys
-constexpr int SORT_BLOCKS = 512;
+constexpr int SORT_THREADS = 512;
+constexpr int SORT_WAVES = SORT_THREADS / WAVE;
+constexpr int SORT_KPT = 12, SORT_KPT_FEW = 4;          // keys per thread
+constexpr int SORT_TILE = SORT_THREADS * SORT_KPT;
+constexpr int64_t SORT_FEW = 1 << 20;                   // up to this many keys: small tiles
+constexpr int SORT_BLOCKS = 768;
 constexpr int RADIX = 256;
 constexpr int SORT_SMALL = 4096;      // up to this many keys one block sorts them (k_sort_small)
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_CLEAR_BLOCKS = 32;  // k_sort_small's blocks after the first: clear the passes' state
+constexpr int Y_DIGITS = 3;             // the low digits, which the hull stage's sort skips
 
-// Tiles per range: enough for SORT_BLOCKS ranges, and up to 8 when that
-// keeps the ranges at 64 or fewer (a shorter look-back per pass).
-__device__ __forceinline__ int64_t sort_qq(int64_t count) {
-    const int64_t tiles = (count + SORT_TILE - 1) / SORT_TILE;
-    return max((tiles + SORT_BLOCKS - 1) / SORT_BLOCKS, min((int64_t)8, (tiles + 63) / 64));
+__host__ __device__ __forceinline__ int64_t sort_tile(int64_t count) {
+    return count <= SORT_FEW ? SORT_THREADS * SORT_KPT_FEW : SORT_TILE;
+}
+__host__ __device__ __forceinline__ int64_t sort_tiles(int64_t count) {
+    return (count + sort_tile(count) - 1) / sort_tile(count);
+}
+// Most tiles of any count up to n.
+__host__ __device__ __forceinline__ int64_t sort_tiles_max(int64_t n) {
+    const int64_t few = n < SORT_FEW ? n : SORT_FEW;
+    const int64_t a = sort_tiles(few), b = sort_tiles(n);
+    return (a > b ? a : b) + 1;
 }
 
-__device__ __forceinline__ void sort_range(int64_t count, int64_t b, int64_t *lo, int64_t *hi) {
-    const int64_t qq = sort_qq(count);
-    *lo = min(count, b * qq * SORT_TILE);
-    *hi = min(count, (b + 1) * qq * SORT_TILE);
-}
-
-// Ranges of sort_range that hold keys: 0 .. sort_busy(count) - 1.
-__device__ __forceinline__ int64_t sort_busy(int64_t count) {
-    const int64_t tiles = (count + SORT_TILE - 1) / SORT_TILE;
-    const int64_t qq = sort_qq(count);
-    return qq ? (tiles + qq - 1) / qq : 0;
-}
-
-// Range look-back entries: pass tag (pass + 1) << 56 | state << 54 | value,
+// Tile look-back entries: pass tag (pass + 1) << 56 | state << 54 | value,
 // 0 = not yet written this call.
 constexpr uint64_t LB_AGG = 1ull << 54, LB_INC = 2ull << 54;
 constexpr uint64_t LB_VAL = (1ull << 54) - 1, LB_TAG = ~((1ull << 56) - 1);
 constexpr int SORT_MAX_PASSES = 8;
 
-// At most SORT_SMALL keys: block 0 sorts them in LDS (bitonic network over
-// the next power of two, padded with the largest key) and writes them where
-// the radix passes would have left them; the passes then return at once.
-// Above SORT_SMALL the other blocks clear the passes' state (the digit
-// totals, the range counters and the look-back entries of the busy ranges).
-// The sort is by key only, so equal keys are interchangeable and the result
-// is the radix sort's.
+// The passes' shared state: digit totals, tile counters, and the long runs.
+struct SortState {
+    uint32_t total[SORT_MAX_PASSES][RADIX];
+    uint32_t claim[SORT_MAX_PASSES];
+    uint32_t nlong[3], ticket;           // long runs: a wave's, a block's, everyone's
+};
+
+// At most SORT_SMALL keys: block 0 sorts them in LDS (a rank per thread up to
+// 1024 keys: 2 us where the network below takes 10; above, a bitonic network
+// over the next power of two, padded with the largest key) and writes them
+// where the radix passes would have left them; the passes then return at
+// once.  Above SORT_SMALL the other blocks clear the passes' state and the
+// look-back entries of the tiles.  The sort is by key only, so equal keys are
+// interchangeable.
 __global__ __launch_bounds__(SMALL_THREADS) void k_sort_small(const uint64_t *__restrict__ keys,
                                                               const int64_t *__restrict__ cnt_ptr,
                                                               uint64_t *__restrict__ out,
                                                               unsigned long long *__restrict__ status,
-                                                              uint32_t *__restrict__ gstate,
+                                                              SortState *__restrict__ state,
                                                               int *__restrict__ seg_fallback) {
     __shared__ uint64_t b[SORT_SMALL];
     const int64_t count = *cnt_ptr;
@@ -70,15 +82,29 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_sort_small(const uint64_t *__
     if (seg_fallback && blockIdx.x == 0 && tid == 0) *seg_fallback = 0;
     if (count > SORT_SMALL) {
         if (blockIdx.x == 0) return;
-        const int64_t nst = sort_busy(count) * RADIX;
+        const int64_t nst = sort_tiles(count) * RADIX;
         const int64_t nt = (int64_t)(gridDim.x - 1) * SMALL_THREADS;
         for (int64_t i = (int64_t)(blockIdx.x - 1) * SMALL_THREADS + tid; i < nst; i += nt) status[i] = 0;
         if (blockIdx.x == 1)
-            for (int i = tid; i < SORT_MAX_PASSES * (RADIX + 1); i += SMALL_THREADS) gstate[i] = 0;
+            for (int i = tid; i < (int)(sizeof(SortState) / 4); i += SMALL_THREADS)
+                reinterpret_cast<uint32_t *>(state)[i] = 0;
         return;
     }
     if (blockIdx.x != 0 || count <= 0) return;
     const int n = (int)count;
+    if (n <= SMALL_THREADS) {
+        const uint64_t mine = tid < n ? keys[tid] : ~0ull;
+        b[tid] = mine;
+        __syncthreads();
+        int rank = 0;
+#pragma unroll 16
+        for (int j = 0; j < n; j++) {
+            const uint64_t o = b[j];
+            rank += (int)(o < mine) | ((int)(o == mine) & (int)(j < tid));
+        }
+        if (tid < n) out[rank] = mine;
+        return;
+    }
     int m = 2;
     while (m < n) m <<= 1;
     for (int i = tid; i < m; i += SMALL_THREADS) b[i] = i < n ? keys[i] : ~0ull;
@@ -183,47 +209,47 @@ __global__ __launch_bounds__(SEG_THREADS) void k_sort_sets(const uint64_t *__res
     }
 }
 
-// Digit totals of every pass over all keys: block b counts the digits of
-// range b in LDS and adds them to gcount[pass][digit] (cleared by
-// k_sort_small).
+// Digit totals of the passes (digits first .. first + passes - 1) over all
+// keys, into state->total (cleared by k_sort_small): each block counts in LDS
+// and adds its counts at the end.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_prep(const uint64_t *__restrict__ keys,
-                                                            const int64_t *__restrict__ cnt_ptr,
-                                                            int passes, uint32_t *__restrict__ gcount,
+                                                            const int64_t *__restrict__ cnt_ptr, int first,
+                                                            int passes, SortState *__restrict__ state,
                                                             const int *__restrict__ seg_fallback) {
     __shared__ uint32_t h[SORT_MAX_PASSES][RADIX];
     const int tid = threadIdx.x;
     const int64_t count = *cnt_ptr;
     if (count <= SORT_SMALL) return;
     if (seg_fallback && *seg_fallback == 0) return;    // k_sort_sets has sorted every set
-    if ((int64_t)blockIdx.x >= sort_busy(count)) return;
-    for (int ps = 0; ps < SORT_MAX_PASSES; ps++) h[ps][tid] = 0;
+    constexpr int U = 8, STEP = SORT_THREADS * U;
+    if ((int64_t)blockIdx.x * STEP >= count) return;
+    for (int i = tid; i < passes * RADIX; i += SORT_THREADS) h[i / RADIX][i % RADIX] = 0;
     __syncthreads();
-    int64_t lo, hi;
-    sort_range(count, blockIdx.x, &lo, &hi);
-    for (int64_t base = lo; base < hi; base += SORT_TILE) {
-        uint64_t k[SORT_ROUNDS];
+    for (int64_t base = (int64_t)blockIdx.x * STEP; base < count; base += (int64_t)gridDim.x * STEP) {
+        uint64_t k[U];
 #pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++) {
+        for (int r = 0; r < U; r++) {
             const int64_t i = base + r * SORT_THREADS + tid;
-            k[r] = i < hi ? keys[i] : 0;
+            k[r] = i < count ? keys[i] : 0;
         }
 #pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++) {
-            if (base + r * SORT_THREADS + tid >= hi) continue;
-            for (int ps = 0; ps < passes; ps++) atomicAdd(&h[ps][(uint32_t)(k[r] >> (8 * ps)) & (RADIX - 1)], 1u);
+        for (int r = 0; r < U; r++) {
+            if (base + r * SORT_THREADS + tid >= count) continue;
+            for (int ps = 0; ps < passes; ps++)
+                atomicAdd(&h[ps][(uint32_t)(k[r] >> (8 * (first + ps))) & (RADIX - 1)], 1u);
         }
     }
     __syncthreads();
-    for (int ps = 0; ps < passes; ps++)
-        if (h[ps][tid]) atomicAdd(&gcount[ps * RADIX + tid], h[ps][tid]);
+    for (int i = tid; i < passes * RADIX; i += SORT_THREADS)
+        if (h[i / RADIX][i % RADIX]) atomicAdd(&state->total[i / RADIX][i % RADIX], h[i / RADIX][i % RADIX]);
 }
 
-// Sum of the digit-d counts of the ranges before range r (thread d), from
-// their look-back entries: an entry with the range's own counts (LB_AGG) is
-// added and the walk goes on, one with the counts up to and including that
-// range (LB_INC) ends it; an entry not yet written this pass is read again.
-// Ranges are claimed in order by running blocks, and each publishes its own
-// counts before it looks back, so every wait ends.
+// Sum of the digit-d counts of the tiles before tile r (thread d), from their
+// look-back entries: an entry with the tile's own counts (LB_AGG) is added
+// and the walk goes on, one with the counts up to and including that tile
+// (LB_INC) ends it; an entry not yet written this pass is read again.  Tiles
+// are claimed in order by running blocks, and each publishes its own counts
+// before it looks back, so every wait ends.
 __device__ __forceinline__ int64_t look_back(const unsigned long long *__restrict__ status, int64_t r,
                                              int d, uint64_t tag) {
     constexpr int LB = 16;
@@ -253,130 +279,298 @@ __device__ __forceinline__ int64_t look_back(const unsigned long long *__restric
     return excl;
 }
 
-// One pass: claim a range, count its digits, publish them, look back, and
-// scatter the range tile by tile.  Per tile (round r, wave w, lane l holds
-// key r*256 + w*64 + l): stable ranks from wave ballots and per (round,
-// wave, digit) counts; the tile is reordered by digit in LDS and then
-// written out run by run, so consecutive lanes write consecutive addresses.
+struct SortLds {
+    uint64_t buf[SORT_TILE];
+    uint32_t wcnt[SORT_WAVES][RADIX];    // a wave's digit counts, then its starts in the tile
+    uint32_t dstart[RADIX];              // the tile's digits' starts
+    int64_t run[RADIX];                  // digit d's output position less its start in the tile
+    uint32_t wsum[SORT_WAVES];
+    int64_t tile;
+};
+
+// One tile of at most SORT_THREADS * KPT keys.  A wave's keys are its
+// consecutive KPT * 64, row by row, so ranks in (wave, row, lane) order keep
+// the input order of equal digits.
+template <int KPT>
+__device__ __forceinline__ void sort_one_tile(SortLds &L, const uint64_t *__restrict__ in, int64_t base, int n,
+                                              int64_t t, int shift, uint64_t tag, int64_t start,
+                                              unsigned long long *__restrict__ status,
+                                              uint64_t *__restrict__ out) {
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const uint64_t lt = lanemask_lt();
+    const int o0 = w * KPT * WAVE + lane;
+    uint64_t k[KPT];
+    uint32_t rank[KPT];
+#pragma unroll
+    for (int r = 0; r < KPT; r++) {
+        const int i = o0 + r * WAVE;
+        k[r] = i < n ? in[base + i] : 0;
+    }
+    for (int i = tid; i < SORT_WAVES * RADIX; i += SORT_THREADS) L.wcnt[i / RADIX][i % RADIX] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < KPT; r++) {
+        const bool has = o0 + r * WAVE < n;
+        const uint32_t d = (uint32_t)(k[r] >> shift) & (RADIX - 1);
+        uint64_t peers = __ballot(has);
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            const bool bit = (d >> b) & 1;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        // every lane of a digit reads the wave's count, its first lane raises it
+        const uint32_t old = L.wcnt[w][d];
+        rank[r] = old + (uint32_t)__popcll(peers & lt);
+        wave_sync();
+        if (has && (peers & lt) == 0) L.wcnt[w][d] = old + (uint32_t)__popcll(peers);
+        wave_sync();
+    }
+    __syncthreads();
+    uint32_t mine = 0;                   // digit tid's keys in the tile
+    if (tid < RADIX) {
+#pragma unroll
+        for (int ww = 0; ww < SORT_WAVES; ww++) mine += L.wcnt[ww][tid];
+        __hip_atomic_store(&status[t * RADIX + tid], tag | (t ? LB_AGG : LB_INC) | mine, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    uint32_t inc = mine;                 // the digits' starts in the tile
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const uint32_t v = __shfl_up(inc, o);
+        if (lane >= o) inc += v;
+    }
+    if (lane == WAVE - 1) L.wsum[w] = inc;
+    __syncthreads();
+    if (tid < RADIX) {
+        uint32_t at = inc - mine;
+        for (int ww = 0; ww < w; ww++) at += L.wsum[ww];
+        L.dstart[tid] = at;
+#pragma unroll
+        for (int ww = 0; ww < SORT_WAVES; ww++) {
+            const uint32_t c = L.wcnt[ww][tid];
+            L.wcnt[ww][tid] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < KPT; r++)
+        if (o0 + r * WAVE < n) L.buf[L.wcnt[w][(uint32_t)(k[r] >> shift) & (RADIX - 1)] + rank[r]] = k[r];
+    if (tid < RADIX) {
+        int64_t excl = 0;
+        if (t) {
+            excl = look_back(status, t, tid, tag);
+            __hip_atomic_store(&status[t * RADIX + tid], tag | LB_INC | (uint64_t)(excl + mine), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        L.run[tid] = start + excl - (int64_t)L.dstart[tid];
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < n; i += SORT_THREADS) {
+        const uint64_t kk = L.buf[i];
+        out[L.run[(uint32_t)(kk >> shift) & (RADIX - 1)] + i] = kk;
+    }
+}
+
+// Pass `pass` by digit `digit`.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(const uint64_t *__restrict__ in,
-                                                            const int64_t *__restrict__ cnt_ptr,
-                                                            int pass, const uint32_t *__restrict__ gcount,
+                                                            const int64_t *__restrict__ cnt_ptr, int pass,
+                                                            int digit, SortState *__restrict__ state,
                                                             unsigned long long *__restrict__ status,
-                                                            uint32_t *__restrict__ claim,
                                                             uint64_t *__restrict__ out,
                                                             const int *__restrict__ seg_fallback) {
-    constexpr int NW = SORT_THREADS / WAVE;
-    __shared__ int64_t run[RADIX];                       // next output position per digit
-    __shared__ __attribute__((aligned(16))) uint16_t wcnt[SORT_ROUNDS][NW][RADIX];
-    __shared__ uint32_t dstart[RADIX + 1], dtot[RADIX], rh[RADIX];
-    __shared__ int64_t scan_sh[17];
-    __shared__ uint64_t buf[SORT_TILE];
-    __shared__ int64_t rsh;
-    const int tid = threadIdx.x, w = tid >> 6;
-    const int shift = 8 * pass;
+    __shared__ SortLds L;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const int64_t count = *cnt_ptr;
     if (count <= SORT_SMALL) return;     // k_sort_small has sorted them
     if (seg_fallback && *seg_fallback == 0) return;    // k_sort_sets has sorted every set
-    if (tid == 0) rsh = (int64_t)atomicAdd(claim, 1u);
-    const uint32_t gd = gcount[pass * RADIX + tid];      // this digit's total (in flight with the claim)
-    rh[tid] = 0;
-    __syncthreads();
-    const int64_t rr = rsh;
-    if (rr >= sort_busy(count)) return;
-    int64_t lo, hi;
-    sort_range(count, rr, &lo, &hi);
-    // the range's digit counts (a single tile keeps its keys in registers)
-    const bool one_tile = hi - lo <= SORT_TILE;
-    uint64_t k[SORT_ROUNDS];
-    for (int64_t base = lo; base < hi; base += SORT_TILE) {
-#pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++) {
-            const int64_t i = base + r * SORT_THREADS + tid;
-            k[r] = i < hi ? in[i] : 0;
-        }
-#pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++)
-            if (base + r * SORT_THREADS + tid < hi) atomicAdd(&rh[(uint32_t)(k[r] >> shift) & (RADIX - 1)], 1u);
-    }
-    __syncthreads();
-    {   // publish, look back, and the digit's first output position
-        const uint64_t tag = (uint64_t)(pass + 1) << 56;
-        const uint32_t mine = rh[tid];
-        int64_t tot;
-        const int64_t gs = block_excl_scan_i64((int64_t)gd, scan_sh, &tot);
-        unsigned long long *e = &status[rr * RADIX + tid];
-        int64_t excl = 0;
-        if (rr == 0) {
-            __hip_atomic_store(e, tag | LB_INC | mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(e, tag | LB_AGG | mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            excl = look_back(status, rr, tid, tag);
-            __hip_atomic_store(e, tag | LB_INC | (uint64_t)(excl + mine), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-        run[tid] = gs + excl;
-    }
-    __syncthreads();
-    const uint64_t lt = lanemask_lt();
-    for (int64_t base = lo; base < hi; base += SORT_TILE) {
-        const int ntile = (int)min((int64_t)SORT_TILE, hi - base);
-        {   // clear the per-(round, wave, digit) counts: 16 KB, 64 B per thread
-            uint4 *z = reinterpret_cast<uint4 *>(&wcnt[0][0][0]);
-            for (int i = tid; i < (int)(sizeof(wcnt) / sizeof(uint4)); i += SORT_THREADS)
-                z[i] = make_uint4(0, 0, 0, 0);
-        }
-        uint32_t d[SORT_ROUNDS];
-        int rank[SORT_ROUNDS], cnt[SORT_ROUNDS];
-#pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++) {
-            const int i = r * SORT_THREADS + tid;
-            const bool valid = i < ntile;
-            if (!one_tile) k[r] = valid ? in[base + i] : 0;
-            d[r] = (uint32_t)(k[r] >> shift) & (RADIX - 1);
-            uint64_t peers = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < 8; b++) {
-                bool bit = (d[r] >> b) & 1;
-                uint64_t m = __ballot(bit);
-                peers &= bit ? m : ~m;
-            }
-            rank[r] = valid ? __popcll(peers & lt) : -1;
-            cnt[r] = __popcll(peers);
-        }
+    const int64_t tiles = sort_tiles(count), tile = sort_tile(count);
+    if ((int64_t)blockIdx.x >= tiles) return;
+    // digit tid's start in the output
+    int64_t start = 0;
+    {
+        const int64_t c = tid < RADIX ? (int64_t)state->total[pass][tid] : 0;
+        const int64_t inc = wave_incl_scan_i64(c);
+        if (lane == WAVE - 1) L.run[w] = inc;
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++)
-            if (rank[r] == 0) wcnt[r][w][d[r]] = (uint16_t)cnt[r];
+        start = inc - c;
+        for (int ww = 0; ww < w; ww++) start += L.run[ww];
+    }
+    const uint64_t tag = (uint64_t)(pass + 1) << 56;
+    for (;;) {
+        __syncthreads();                 // the previous tile is done with L
+        if (tid == 0) L.tile = (int64_t)atomicAdd(&state->claim[pass], 1u);
         __syncthreads();
-        {   // digit tid: exclusive prefix over (round, wave) in key order
-            uint32_t acc = 0;
-            for (int r = 0; r < SORT_ROUNDS; r++)
-                for (int ww = 0; ww < NW; ww++) {
-                    uint32_t c = wcnt[r][ww][tid];
-                    wcnt[r][ww][tid] = (uint16_t)acc;
-                    acc += c;
+        const int64_t t = L.tile;
+        if (t >= tiles) return;
+        const int64_t base = t * tile;
+        const int n = (int)min(tile, count - base);
+        if (tile == SORT_TILE) sort_one_tile<SORT_KPT>(L, in, base, n, t, 8 * digit, tag, start, status, out);
+        else sort_one_tile<SORT_KPT_FEW>(L, in, base, n, t, 8 * digit, tag, start, status, out);
+    }
+}
+
+// Runs of equal (set, x) in keys sorted by (set, x): a run of up to TIE_SHORT
+// keys is sorted where it lies by the thread at its head; a longer one is
+// listed for k_sort_long.
+constexpr int TIE_SHORT = 16;
+constexpr int64_t TIE_WAVE = 1 << 12, TIE_BLOCK = 1 << 18;
+struct LongRun {
+    int64_t a, e;                        // keys [a, e)
+    unsigned long long lo, hi;
+};
+// The lists' parts: everyone's runs (over TIE_BLOCK keys), a block's, a wave's.
+__device__ __forceinline__ LongRun *tie_list(LongRun *runs, int64_t n, int kind) {
+    const int64_t all = n / TIE_BLOCK + 1, block = n / TIE_WAVE + 1;
+    return runs + (kind == 2 ? 0 : kind == 1 ? all : all + block);
+}
+
+// A block takes TIE_TILE keys through LDS (with the key before and the
+// TIE_SHORT after them); the runs that start in the tile are its own.
+constexpr int TIE_TILE = 2048;
+
+__global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
+                                                   const int64_t *__restrict__ cnt_ptr,
+                                                   SortState *__restrict__ state, LongRun *__restrict__ runs,
+                                                   const int *__restrict__ seg_fallback) {
+    constexpr int TW = TIE_TILE + TIE_SHORT + 2;
+    __shared__ uint64_t k[TW];                   // k[j]: key base - 1 + j
+    const int64_t n = *cnt_ptr;
+    if (n <= SORT_SMALL) return;
+    if (seg_fallback && *seg_fallback == 0) return;
+    const int tid = threadIdx.x;
+    for (int64_t base = (int64_t)blockIdx.x * TIE_TILE; base < n; base += (int64_t)gridDim.x * TIE_TILE) {
+        __syncthreads();
+        constexpr int U = (TW + 255) / 256;
+        uint64_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t i = base - 1 + tid + u * 256;
+            v[u] = i >= 0 && i < n && tid + u * 256 < TW ? keys[i] : ~0ull;       // no key's (set, x)
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (tid + u * 256 < TW) k[tid + u * 256] = v[u];
+        __syncthreads();
+        for (int t = tid; t < TIE_TILE && base + t < n; t += 256) {
+            const int j = t + 1;
+            const uint64_t g = k[j] >> (8 * Y_DIGITS);
+            if ((k[j + 1] >> (8 * Y_DIGITS)) != g || (k[j - 1] >> (8 * Y_DIGITS)) == g) continue;
+            int len = 2;
+            while (len <= TIE_SHORT && (k[j + len] >> (8 * Y_DIGITS)) == g) len++;
+            const int64_t i = base + t;
+            if (len <= TIE_SHORT) {
+                // sorted in LDS and in the list (other threads compare only
+                // the keys' (set, x), which every order of the run keeps)
+                for (int q = 1; q < len; q++) {
+                    const uint64_t c = k[j + q];
+                    int p = q;
+                    for (; p > 0 && k[j + p - 1] > c; p--) k[j + p] = k[j + p - 1];
+                    k[j + p] = c;
                 }
-            dtot[tid] = acc;
+                for (int q = 0; q < len; q++) keys[i + q] = k[j + q];
+            } else {
+                int64_t lo = i + len, hi = n;        // the first key past the run
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if ((keys[mid] >> (8 * Y_DIGITS)) == g) lo = mid + 1; else hi = mid;
+                }
+                const int kind = lo - i > TIE_BLOCK ? 2 : lo - i > TIE_WAVE ? 1 : 0;
+                tie_list(runs, n, kind)[atomicAdd(&state->nlong[kind], 1u)] = LongRun{i, lo, ~0ull, 0ull};
+            }
         }
-        __syncthreads();
-        {
-            int64_t tot;
-            int64_t ex = block_excl_scan_i64(dtot[tid], scan_sh, &tot);
-            dstart[tid] = (uint32_t)ex;
+    }
+}
+
+// The long runs: lowest key, copies of it, highest key.  Up to TIE_WAVE keys
+// a wave takes a run, up to TIE_BLOCK a block; all blocks share the extremes
+// of a longer one, and the last block to finish writes those.
+constexpr int TIE_THREADS = 512;
+
+__global__ __launch_bounds__(TIE_THREADS) void k_sort_long(uint64_t *__restrict__ keys,
+                                                           const int64_t *__restrict__ cnt_ptr,
+                                                           SortState *__restrict__ state,
+                                                           LongRun *__restrict__ runs,
+                                                           const int *__restrict__ seg_fallback) {
+    __shared__ unsigned long long lo, hi;
+    __shared__ bool last;
+    const int64_t n = *cnt_ptr;
+    if (n <= SORT_SMALL) return;
+    if (seg_fallback && *seg_fallback == 0) return;
+    const int tid = threadIdx.x, lane = lane_id();
+    // lowest and highest of keys a + t, a + t + step, ... below e, over a wave
+    auto wave_extremes = [&](int64_t a, int64_t e, int t, int step, unsigned long long *l, unsigned long long *h) {
+        unsigned long long l1 = ~0ull, h1 = 0ull;
+        for (int64_t i = a + t; i < e; i += step) {
+            const unsigned long long k = keys[i];
+            l1 = k < l1 ? k : l1;
+            h1 = k > h1 ? k : h1;
         }
-        __syncthreads();
 #pragma unroll
-        for (int r = 0; r < SORT_ROUNDS; r++)
-            if (rank[r] >= 0) buf[dstart[d[r]] + wcnt[r][w][d[r]] + rank[r]] = k[r];
+        for (int o = 32; o >= 1; o >>= 1) {
+            const unsigned long long l2 = __shfl_xor(l1, o), h2 = __shfl_xor(h1, o);
+            l1 = l2 < l1 ? l2 : l1;
+            h1 = h2 > h1 ? h2 : h1;
+        }
+        *l = l1;
+        *h = h1;
+    };
+    auto fill = [&](int64_t a, int64_t e, int t, int step, uint64_t l, uint64_t h) {
+        for (int64_t i = a + t; i < e; i += step) keys[i] = i == e - 1 ? h : l;
+    };
+    auto block_extremes = [&](int64_t a, int64_t e) {
         __syncthreads();
-        for (int i = tid; i < ntile; i += SORT_THREADS) {
-            uint64_t kk = buf[i];
-            uint32_t dd = (uint32_t)(kk >> shift) & (RADIX - 1);
-            out[run[dd] + (i - (int)dstart[dd])] = kk;
+        if (tid == 0) { lo = ~0ull; hi = 0ull; }
+        __syncthreads();
+        unsigned long long l, h;
+        wave_extremes(a, e, tid, TIE_THREADS, &l, &h);
+        if (lane == 0) {
+            atomicMin(&lo, l);
+            atomicMax(&hi, h);
         }
         __syncthreads();
-        run[tid] += dtot[tid];
-        __syncthreads();
+    };
+    const uint32_t nw = state->nlong[0], nb = state->nlong[1], na = state->nlong[2];
+    const LongRun *R = tie_list(runs, n, 0);
+    constexpr int WPB = TIE_THREADS / WAVE;
+    for (uint32_t r = blockIdx.x * WPB + (tid >> 6); r < nw; r += gridDim.x * WPB) {
+        const int64_t a = R[r].a, e = R[r].e;
+        unsigned long long l, h;
+        wave_extremes(a, e, lane, WAVE, &l, &h);
+        fill(a, e, lane, WAVE, l, h);
+    }
+    R = tie_list(runs, n, 1);
+    for (uint32_t r = blockIdx.x; r < nb; r += gridDim.x) {
+        const int64_t a = R[r].a, e = R[r].e;
+        block_extremes(a, e);
+        fill(a, e, tid, TIE_THREADS, lo, hi);
+    }
+    if (na == 0) return;
+    LongRun *H = tie_list(runs, n, 2);
+    for (uint32_t r = 0; r < na; r++) {
+        const int64_t a = H[r].a, e = H[r].e;
+        const int64_t part = (e - a + gridDim.x - 1) / gridDim.x;
+        const int64_t pa = min(e, a + part * blockIdx.x), pe = min(e, pa + part);
+        block_extremes(pa, pe);
+        if (tid == 0 && pa < pe) {
+            atomicMin(&H[r].lo, lo);
+            atomicMax(&H[r].hi, hi);
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        __threadfence();
+        last = atomicAdd(&state->ticket, 1u) == gridDim.x - 1;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!last) return;
+    for (uint32_t r = 0; r < na; r++) {
+        const uint64_t l = __hip_atomic_load(&H[r].lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t h = __hip_atomic_load(&H[r].hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        fill(H[r].a, H[r].e, tid, TIE_THREADS, l, h);
     }
 }
 
