@@ -9,12 +9,18 @@
 struct Hull3Bufs {
     char *a = nullptr, *b = nullptr;
     size_t acap = 0, bcap = 0;
+    // the rounds' status as the host reads it, one round behind
+    Hull3Ctl *seen = nullptr;            // two, pinned
+    hipEvent_t ev[2] = {nullptr, nullptr};
 };
 
 static void hull3_free(Hull3Bufs *h) {
     if (!h) return;
     if (h->a) (void)hipFree(h->a);
     if (h->b) (void)hipFree(h->b);
+    if (h->seen) (void)hipHostFree(h->seen);
+    for (hipEvent_t e : h->ev)
+        if (e) (void)hipEventDestroy(e);
     delete h;
 }
 
@@ -44,6 +50,13 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
     HIPCHECK(hipSetDevice(ctx->device));
     if (!ctx->h3) ctx->h3 = new Hull3Bufs();
     Hull3Bufs *B = ctx->h3;
+    if (!B->seen) {
+        for (hipEvent_t &e : B->ev)
+            if (!e) HIPCHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        HIPCHECK(hipHostMalloc(reinterpret_cast<void **>(&B->seen), 2 * sizeof(Hull3Ctl), hipHostMallocDefault));
+    }
+    // the last call's last status may still be on its way (on another stream)
+    for (hipEvent_t e : B->ev) HIPCHECK(hipEventSynchronize(e));
     const bool nofilter = flags & HULL_NOFILTER;
     int rc;
     Plan p;
@@ -101,7 +114,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         const size_t b_idx = tb(nc * 4 + 16), b_ca = tb(nc * 16 + 16), b_cb = tb(nc * 16 + 16),
                      b_fa = tb(nc * 4 + 16), b_fb = tb(nc * 4 + 16), b_faces = tb(fcap * sizeof(Face3)),
                      b_planes = tb(fcap * sizeof(Plane3)), b_far = tb(fcap * 8), b_vis = tb(fcap * 4),
-                     b_repl = tb(fcap * sizeof(int2)), b_claim = tb(fcap * 8),
+                     b_repl = tb(fcap * sizeof(int2)), b_claim = tb(2 * fcap * 8),
                      b_pairs = tb(PAIR_CAP * sizeof(Pair3)), b_pn = tb(PAIR_CAP * sizeof(int2)),
                      b_pv = tb((size_t)PAIR_CAP * PV_CAP * 4), b_ph = tb((size_t)PAIR_CAP * PV_CAP * 4),
                      b_corner = tb(nc * 8 + 16), b_ncorner = tb(16);
@@ -111,6 +124,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         float4 *cand[2] = {reinterpret_cast<float4 *>(hb + b_ca), reinterpret_cast<float4 *>(hb + b_cb)};
         int *cf[2] = {reinterpret_cast<int *>(hb + b_fa), reinterpret_cast<int *>(hb + b_fb)};
         unsigned long long *claim = reinterpret_cast<unsigned long long *>(hb + b_claim);
+        unsigned long long *claim_out = claim + fcap;
         Pair3 *pairs = reinterpret_cast<Pair3 *>(hb + b_pairs);
         int2 *pn = reinterpret_cast<int2 *>(hb + b_pn);
         int *pvis = reinterpret_cast<int *>(hb + b_pv);
@@ -157,43 +171,62 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
             LAUNCH(K_MISC, k3_u64_of<<<256, 256, 0, st>>>(h2, hcount, corner));
         } else {
             LAUNCH(K_MISC, k3_fill_i32<<<256, 256, 0, st>>>(vis, fcap, -1));
-            LAUNCH(K_MISC, k_fill_i64<<<256, 256, 0, st>>>(reinterpret_cast<int64_t *>(claim), fcap, 0));
+            LAUNCH(K_MISC, k_fill_i64<<<256, 256, 0, st>>>(reinterpret_cast<int64_t *>(claim), 2 * fcap, 0));
             LAUNCH(K_MISC, k3_gather<<<gs, 256, 0, st>>>(x, y, z, cidx, nc, cand[0]));
-            const unsigned gp = (unsigned)(ctx->cus * 4), gv = (unsigned)(ctx->cus * 16);
-            const unsigned ga = (unsigned)std::max<int64_t>(
-                1, std::min<int64_t>(ctx->cus * 4, (nc + 256 * AS_ITEMS - 1) / (256 * AS_ITEMS)));
-            int cur = 0;
             const bool all_serial = flags & HULL3_SERIAL;
-            bool overflow = false, serial = all_serial;
+            bool overflow = false;
+            bool was_serial[2] = {false, false};
+            // The host launches a round before it reads the status of the one
+            // before it, so the GPU never waits for it (a synchronisation a
+            // round left it idle for 30 us each); the last round launched
+            // finds no candidates.  Grids follow the last status read:
+            // candidates only get fewer, and every kernel loops.
+            int64_t cands = nc, nf = 4;
+            int cur = 0;
+            bool serial = all_serial;
             for (int round = 0;; round++) {
-                LAUNCH(K_REFINE, k3_assign<<<ga, 256, 0, st>>>(cand[cur], cf[cur], cand[1 - cur], cf[1 - cur], C,
-                                                               faces, planes, repl, far, round == 0));
+                const auto grid = [&](int64_t items, int64_t per, int64_t most) {
+                    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(most, (items + per - 1) / per));
+                };
+                LAUNCH(K_REFINE, k3_assign<<<grid(cands, 256 * AS_ITEMS, ctx->cus * 4), 256, 0, st>>>(
+                    cand[cur], cf[cur], cand[1 - cur], cf[1 - cur], C, faces, planes, repl, far, round));
+                was_serial[round & 1] = serial;
                 if (serial) {
                     // one block inserts every face's farthest candidate in turn
                     LAUNCH(K_REFINE_SPLIT, k3_insert<<<1, INS_THREADS, 0, st>>>(x, y, z, C, faces, planes, far,
-                                                                                 vis, repl));
+                                                                                 vis, repl, round));
                 } else {
-                    LAUNCH(K_REFINE_SPLIT, k3_pick<<<gp, 256, 0, st>>>(C, far, pairs));
+                    LAUNCH(K_REFINE_SPLIT, k3_pick<<<grid(4 * nf, 256, ctx->cus * 4), 256, 0, st>>>(C, far, pairs,
+                                                                                                    round));
+                    const unsigned gv = grid(cands, 1, ctx->cus * 16);
                     for (int sub = 0; sub < INS_PASSES; sub++) {
                         const int stamp = round * INS_PASSES + sub + 1;
                         LAUNCH(K_REFINE_SPLIT, k3_visible<<<gv, 64, 0, st>>>(x, y, z, C, faces, planes, pairs, pvis,
-                                                                              phz, pn, claim, stamp));
+                                                                              phz, pn, claim, claim_out, stamp));
                         LAUNCH(K_REFINE_SPLIT, k3_apply<<<gv, 64, 0, st>>>(x, y, z, C, faces, planes, far, vis,
                                                                             repl, pairs, pvis, phz, pn, claim,
-                                                                            stamp));
+                                                                            claim_out, stamp));
                     }
-                    LAUNCH(K_MISC, k3_round_end<<<1, 64, 0, st>>>(C));
                 }
-                HIPCHECK(hipMemcpyAsync(&hc, C, sizeof(hc), hipMemcpyDeviceToHost, st));
-                HIPCHECK(hipStreamSynchronize(st));
                 cur = 1 - cur;
-                if (hc.overflow == 2) return HULL_EHIP;      // internal: the mesh lost its shape
-                if (hc.overflow) { overflow = true; break; }
-                if (hc.ncand == 0) break;
-                if ((round + 2) * INS_PASSES >= (1 << 20)) return HULL_EHIP;
+                HIPCHECK(hipMemcpyAsync(&B->seen[round & 1], C, sizeof(hc), hipMemcpyDeviceToHost, st));
+                HIPCHECK(hipEventRecord(B->ev[round & 1], st));
+                if (round == 0) continue;
+                HIPCHECK(hipEventSynchronize(B->ev[(round - 1) & 1]));
+                hc = B->seen[(round - 1) & 1];
+                if (hc.overflow == 2 || (round + 2) * INS_PASSES >= (1 << 20)) {
+                    HIPCHECK(hipStreamSynchronize(st));      // internal: the mesh lost its shape
+                    return HULL_EHIP;
+                }
+                cands = hc.nlist[round & 1];
+                nf = hc.nfaces;
+                if (hc.overflow || cands == 0) {
+                    overflow = hc.overflow;
+                    break;
+                }
                 // a round whose proposals all exceeded the per-proposal room
-                // is followed by one serial round
-                serial = all_serial || (!serial && hc.inserted == 0);
+                // is followed by a serial round
+                serial = all_serial || (!was_serial[(round - 1) & 1] && !was_serial[round & 1] && hc.inserted == 0);
             }
             if (overflow) {
                 if (fcap >= (int64_t(1) << 28)) return HULL_ENOMEM;

@@ -520,7 +520,7 @@ struct Hull3Ctl {
     int64_t hi_dot;               // and largest
     int state;                    // 0 solid, 1 flat, 2 collinear, 3 one point, 4 empty
     int nfaces, fcap, born_lo;
-    int ncand, nout, inserted, overflow;
+    int nlist[2], inserted, overflow; // round r reads nlist[r & 1] candidates and leaves the other
     int ncorner, lo_idx, hi_idx, npair;
     uint32_t p[4];                // start simplex
     int64_t nrm[3];               // flat sets: their plane's normal
@@ -617,7 +617,9 @@ __global__ void k3_start(const float *__restrict__ x, const float *__restrict__ 
     C->inserted = 0;
     C->overflow = 0;
     C->ncorner = 0;
-    C->ncand = (int)nc;
+    C->nlist[0] = (int)nc;
+    C->nlist[1] = 0;
+    C->npair = 0;
     if (nc <= 0) { C->state = 4; return; }
     C->p[0] = cand[0];
     if (!C->seed[0]) { C->state = 3; return; }
@@ -704,9 +706,11 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
                                                  float4 *__restrict__ cout, int *__restrict__ fout,
                                                  Hull3Ctl *__restrict__ C, const Face3 *__restrict__ faces,
                                                  const Plane3 *__restrict__ planes, const int2 *__restrict__ repl,
-                                                 unsigned long long *__restrict__ far, int first) {
+                                                 unsigned long long *__restrict__ far, int round) {
     __shared__ int bcnt, bbase;
-    const int64_t nc = C->ncand;
+    const int64_t nc = C->nlist[round & 1];
+    const bool first = round == 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) C->npair = 0;      // for k3_pick
     const int nfaces = C->nfaces;
     const int lane = lane_id();
     constexpr int STEP = 256 * AS_ITEMS;
@@ -767,7 +771,7 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
         wo = __shfl(wo, 0);
         __syncthreads();
         if (threadIdx.x == 0) {
-            bbase = bcnt ? atomicAdd(&C->nout, bcnt) : 0;
+            bbase = bcnt ? atomicAdd(&C->nlist[(round + 1) & 1], bcnt) : 0;
             bcnt = 0;
         }
         __syncthreads();
@@ -803,12 +807,20 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
 // ---------------------------------------------------------------------------
 // Parallel insertion.  Every face with candidates proposes its farthest one
 // q.  Each proposal finds the faces q sees (breadth-first from its face) and
-// the horizon, and claims those faces and the outside faces across the
-// horizon with its priority (round, coarse distance, ~index; maximum wins).
-// A proposal that holds every claim is inserted.  Two winners touch disjoint
-// faces, so no face one of them creates is seen by the other and the
-// insertions give the hull of inserting them one after another; the
-// proposal of highest priority always wins, so every round inserts.
+// the horizon, and claims with its priority (round, coarse distance, ~index;
+// maximum wins) the faces it sees, in one array, and the faces across its
+// horizon, in another.  It is inserted when it holds every face it sees, no
+// proposal above it has one of them across its horizon, and none above it
+// sees a face across its own.  So the faces two winners see are disjoint and
+// no two of them neighbours (they may share a face across their horizons:
+// each moves another of its edges).  Inserted after one of them, the other
+// sees the faces it saw before and no new one: what a point sees is
+// connected, and a new face borders only new faces and faces across its
+// winner's horizon.  So the insertions give the hull of inserting the winners
+// one after another; the proposal of highest priority always wins, so every
+// round inserts.  (With one array, where winners may not share a face across
+// their horizons either, a pass inserts half as many: a ball of 2^24 points
+// took 39 rounds, now 27.)
 struct Pair3 {
     uint32_t q;
     int f;
@@ -820,8 +832,11 @@ constexpr int INS_PASSES = 4;       // claim-and-insert passes per assignment
 
 // Round start: the proposals.  Clears far[] for the next assignment.
 __global__ __launch_bounds__(256) void k3_pick(Hull3Ctl *__restrict__ C, unsigned long long *__restrict__ far,
-                                               Pair3 *__restrict__ pairs) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) C->inserted = 0;
+                                               Pair3 *__restrict__ pairs, int round) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        C->inserted = 0;
+        C->nlist[round & 1] = 0;      // read by this round's assignment, filled by the next one's
+    }
     const int F = C->nfaces;
     const int64_t Fw = (F + WAVE - 1) / WAVE * WAVE;
     for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < Fw; t += int64_t(gridDim.x) * blockDim.x) {
@@ -861,7 +876,8 @@ __global__ __launch_bounds__(64) void k3_visible(const float *__restrict__ x, co
                                                  const Face3 *__restrict__ faces, const Plane3 *__restrict__ planes,
                                                  const Pair3 *__restrict__ pairs, int *__restrict__ pv,
                                                  int *__restrict__ ph, int2 *__restrict__ pn,
-                                                 unsigned long long *__restrict__ claim, int stamp) {
+                                                 unsigned long long *__restrict__ claim,
+                                                 unsigned long long *__restrict__ claim_out, int stamp) {
     __shared__ int vl[PV_CAP];
     __shared__ int hl[PV_CAP];
     __shared__ int tmp[WAVE];
@@ -920,7 +936,7 @@ __global__ __launch_bounds__(64) void k3_visible(const float *__restrict__ x, co
             }
             for (int h = lane; h < nh; h += WAVE) {
                 ph[(int64_t)p * PV_CAP + h] = hl[h];
-                atomicMax(&claim[faces[hl[h] >> 2].nb[hl[h] & 3]], prio);
+                atomicMax(&claim_out[faces[hl[h] >> 2].nb[hl[h] & 3]], prio);
             }
         }
         if (lane == 0) pn[p] = ok ? make_int2(nv, nh) : make_int2(-1, -1);
@@ -938,7 +954,8 @@ __global__ __launch_bounds__(64) void k3_apply(const float *__restrict__ x, cons
                                                int2 *__restrict__ repl, const Pair3 *__restrict__ pairs,
                                                const int *__restrict__ pv, const int *__restrict__ ph,
                                                const int2 *__restrict__ pn,
-                                               const unsigned long long *__restrict__ claim, int stamp) {
+                                               const unsigned long long *__restrict__ claim,
+                                               const unsigned long long *__restrict__ claim_out, int stamp) {
     __shared__ int ha[PV_CAP], hb[PV_CAP], ho[PV_CAP];
     __shared__ int base;
     const int lane = threadIdx.x;
@@ -953,11 +970,14 @@ __global__ __launch_bounds__(64) void k3_apply(const float *__restrict__ x, cons
         const int *Hz = ph + (int64_t)p * PV_CAP;
         const int NV = cnt.x, NH = cnt.y;
         bool won = true;
-        for (int i = lane; i < NV; i += WAVE) won = won && claim[V[i]] == prio;
+        for (int i = lane; i < NV; i += WAVE) {
+            const int v = V[i];
+            won = won && claim[v] == prio && claim_out[v] < prio;
+        }
         for (int h = lane; h < NH; h += WAVE) {
             const int fi = Hz[h] >> 2, e = Hz[h] & 3;
             const int O = faces[fi].nb[e];
-            won = won && claim[O] == prio;
+            won = won && claim[O] < prio;
             ha[h] = faces[fi].v[e];
             hb[h] = faces[fi].v[e == 2 ? 0 : e + 1];
             ho[h] = O;
@@ -1008,14 +1028,6 @@ __global__ __launch_bounds__(64) void k3_apply(const float *__restrict__ x, cons
     }
 }
 
-// Round end: the assignment's output is the next round's input.
-__global__ void k3_round_end(Hull3Ctl *__restrict__ C) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    C->ncand = C->nout;
-    C->nout = 0;
-    C->npair = 0;
-}
-
 constexpr int INS_THREADS = 1024;
 constexpr int INS_LIST = 2048;      // points inserted per round at most
 constexpr int HZ_CAP = 2048;        // horizon edges of one insertion
@@ -1030,7 +1042,8 @@ __global__ __launch_bounds__(INS_THREADS) void k3_insert(const float *__restrict
                                                          const float *__restrict__ z, Hull3Ctl *__restrict__ C,
                                                          Face3 *__restrict__ faces, Plane3 *__restrict__ planes,
                                                          unsigned long long *__restrict__ far,
-                                                         int *__restrict__ vis, int2 *__restrict__ repl) {
+                                                         int *__restrict__ vis, int2 *__restrict__ repl,
+                                                         int round) {
     __shared__ uint32_t list[INS_LIST];
     __shared__ int lface[INS_LIST];
     __shared__ int nl, nh, nv, nf0, bad, over;
@@ -1045,8 +1058,7 @@ __global__ __launch_bounds__(INS_THREADS) void k3_insert(const float *__restrict
         over = 0;
         nf0 = C->nfaces;
         C->inserted = 0;
-        C->ncand = C->nout;     // the assignment's output is the next input
-        C->nout = 0;
+        C->nlist[round & 1] = 0;
     }
     __syncthreads();
     const int F0 = nf0;
