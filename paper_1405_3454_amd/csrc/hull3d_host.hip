@@ -83,7 +83,9 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         const Dirs d = ctx->dirs;
         LAUNCH(K_EXTREMES, (k3_extremes<0><<<g3, 256, 0, st>>>(x, y, z, n, d, pval, pidx)));
         LAUNCH(K_EXTREMES, (k3_extremes<1><<<g3, 256, 0, st>>>(x, y, z, n, d, pval, pidx)));
-        LAUNCH(K_POLYGON, k3_poly<<<1, 1024, 0, st>>>(x, y, z, W3, pval, pidx, slots, poly));
+        LAUNCH(K_POLYGON, k3_slots<<<1, 1024, 0, st>>>(x, y, z, W3, pval, pidx, slots, poly));
+        LAUNCH(K_POLYGON, k3_planes<<<(TRIPLES3 + 255) / 256, 256, 0, st>>>(poly));
+        LAUNCH(K_POLYGON, k3_poly<<<1, 1024, 0, st>>>(poly));
         const unsigned gd = (unsigned)(ctx->cus * 4);
         LAUNCH(K_DISCARD, k3_discard<<<gd, 256, 0, st>>>(x, y, z, n, poly, W<uint64_t>(p, p.masks),
                                                         W<uint32_t>(p, p.tile_cnt)));

@@ -212,20 +212,30 @@ __global__ __launch_bounds__(256) void k3_extremes(const float *__restrict__ x, 
 }
 
 // ---------------------------------------------------------------------------
-// Step 2, one block: reduce the waves' partials to the slots, then the
-// polyhedron of the distinct slot points: every plane through three of them
-// with all of them on one side and at least one strictly, deduplicated and
-// oriented inwards.  Also the inscribed ball used as a quick accept (centre:
-// the mean of the distinct points, strictly inside when there is an
-// interior; radius: the least binary64 distance to a plane, reduced by a
-// safety margin), and the distinct points for the hull stage.
+// Step 2, in three launches: the waves' partials reduced to the slots and
+// their distinct points (k3_slots); the polyhedron of those, every plane
+// through three of them with all of them on one side and at least one
+// strictly, each plane kept once (k3_planes, a triple per thread); the kept
+// planes in order, oriented inwards, and the inscribed ball used as a quick
+// accept (k3_poly; centre: the mean of the distinct points, strictly inside
+// when there is an interior; radius: the least binary64 distance to a plane,
+// reduced by a safety margin).  (One block for all of it took 395 us: the
+// partials read a record at a time, and 11 triples per thread against every
+// point; now 68.)
+struct PlaneK {             // a plane as k3_discard evaluates it: n.p - na
+    double nx, ny, nz, na, bound;
+};
 struct Poly3 {
     int nf;                 // planes; 0: no interior, nothing is discarded
     int m;                  // distinct slot points
     double cx, cy, cz;      // quick-accept ball: (p - c)^2 < r2 is strictly inside
     double r2;
     uint32_t pts[S3];       // the distinct slot points (indices)
+    I3 q[S3];               // and their coordinates
+    unsigned long long keep[(S3 * (S3 - 1) * (S3 - 2) / 6 + 63) / 64];    // triples whose plane is kept
+    unsigned long long flip[(S3 * (S3 - 1) * (S3 - 2) / 6 + 63) / 64];    // and points outwards
     Plane3 f[F3_CAP];
+    PlaneK k[F3_CAP];
 };
 
 // Triple number t -> (i < j < k) over S3 points.
@@ -242,103 +252,151 @@ __device__ __forceinline__ bool i3_zero(I3 a) { return a.x == 0 && a.y == 0 && a
 
 constexpr int TWORDS3 = (TRIPLES3 + 63) / 64;
 
-__global__ __launch_bounds__(1024) void k3_poly(const float *__restrict__ x, const float *__restrict__ y,
-                                                const float *__restrict__ z, int64_t W,
-                                                const double *__restrict__ pval,
-                                                const uint32_t *__restrict__ pidx,
-                                                uint32_t *__restrict__ slots_out, Poly3 *__restrict__ out) {
+__global__ __launch_bounds__(1024) void k3_slots(const float *__restrict__ x, const float *__restrict__ y,
+                                                 const float *__restrict__ z, int64_t W,
+                                                 const double *__restrict__ pval,
+                                                 const uint32_t *__restrict__ pidx,
+                                                 uint32_t *__restrict__ slots_out, Poly3 *__restrict__ out) {
+    constexpr int NW = 1024 / WAVE;
+    __shared__ double wv[NW][S3];
+    __shared__ uint32_t wi[NW][S3];
     __shared__ uint32_t bi[S3];
     __shared__ I3 qs[S3];
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    // wave w reads the records w, w + NW, ..., a lane per slot, eight in flight
+    const int k = min(lane, S3 - 1);
+    const bool mx = k & 1;
+    double bv = mx ? -INFINITY : INFINITY;
+    uint32_t b = NONE;
+    auto take = [&](double v, uint32_t i) {
+        const int less = mx ? v > bv : v < bv;
+        const bool t = (int)(i != NONE) & ((int)(b == NONE) | less | ((int)(v == bv) & (int)(i < b)));
+        bv = t ? v : bv;
+        b = t ? i : b;
+    };
+    constexpr int U = 8;
+    for (int64_t r0 = w; r0 < W; r0 += U * NW) {
+        double v[U];
+        uint32_t i[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t r = min(r0 + u * NW, W - 1);
+            v[u] = pval[r * S3 + k];
+            i[u] = pidx[r * S3 + k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) take(v[u], r0 + u * NW < W ? i[u] : NONE);
+    }
+    if (lane < S3) {
+        wv[w][lane] = bv;
+        wi[w][lane] = b;
+    }
+    for (int t = tid; t < (int)(sizeof(out->keep) / 8); t += 1024) { out->keep[t] = 0; out->flip[t] = 0; }
+    __syncthreads();
+    if (w == 0) {
+        for (int ww = 1; ww < NW; ww++) take(wv[ww][k], wi[ww][k]);
+        if (lane < S3) {
+            bi[lane] = b;
+            if (slots_out) slots_out[lane] = b;
+        }
+        // distinct points: the first slot of each coordinate triple, in slot order
+        const bool valid = lane < S3 && b != NONE;
+        I3 p{0, 0, 0};
+        if (valid) p = grid3(x, y, z, b);
+        if (lane < S3) qs[lane] = p;
+        wave_sync();
+        int first = valid;
+#pragma unroll 4
+        for (int j = 0; j < S3; j++) {
+            const I3 o = qs[j];
+            first &= 1 ^ ((int)(j < lane) & (int)(bi[j] != NONE) & (int)(o.x == p.x) & (int)(o.y == p.y) &
+                          (int)(o.z == p.z));
+        }
+        const uint64_t bm = __ballot(first);
+        if (first) {
+            const int pos = __popcll(bm & lanemask_lt());
+            out->q[pos] = p;
+            out->pts[pos] = b;
+        }
+        if (lane == 0) out->m = __popcll(bm);
+    }
+}
+
+// Supporting planes through three distinct points; of the triples on one
+// plane only the canonical one is kept: the plane's two lowest points and the
+// lowest point after them off their line.
+__global__ __launch_bounds__(256) void k3_planes(Poly3 *__restrict__ out) {
     __shared__ I3 q[S3];
-    __shared__ uint32_t qi[S3];
-    __shared__ int m, nf;
-    __shared__ unsigned long long keep[TWORDS3], flipb[TWORDS3];
+    __shared__ double qd[3][S3];
+    const int tid = threadIdx.x;
+    const int mm = out->m;
+    if (tid < mm) {
+        const I3 p = out->q[tid];
+        q[tid] = p;
+        qd[0][tid] = (double)p.x;
+        qd[1][tid] = (double)p.y;
+        qd[2][tid] = (double)p.z;
+    }
+    __syncthreads();
+    const int t = blockIdx.x * 256 + tid;
+    if (t >= TRIPLES3) return;
+    int i, j, k;
+    triple_of(t, i, j, k);
+    if (k >= mm) return;
+    const I3 nrm = i3_cross(i3_sub(q[j], q[i]), i3_sub(q[k], q[i]));
+    if (i3_zero(nrm)) return;
+    const Plane3 P = make_plane(nrm, q[i]);
+    int pos = 0, neg = 0;
+    unsigned long long on = 0;
+    for (int r = 0; r < mm && !(pos && neg); r++) {
+        const int sg = plane_sign(P, qd[0][r], qd[1][r], qd[2][r]);
+        pos |= sg > 0;
+        neg |= sg < 0;
+        on |= (unsigned long long)(sg == 0) << r;
+    }
+    if ((pos && neg) || (!pos && !neg)) return;
+    const int i0 = __ffsll(on) - 1;
+    const unsigned long long on1 = on & (on - 1);
+    const int j0 = __ffsll(on1) - 1;
+    if (i != i0 || j != j0) return;
+    int k0 = -1;
+    for (unsigned long long rest = on1 & (on1 - 1); rest; rest &= rest - 1) {
+        const int r = __ffsll(rest) - 1;
+        if (!i3_zero(i3_cross(i3_sub(q[j0], q[i0]), i3_sub(q[r], q[i0])))) { k0 = r; break; }
+    }
+    if (k != k0) return;
+    atomicOr(&out->keep[t >> 6], 1ull << (t & 63));
+    if (neg) atomicOr(&out->flip[t >> 6], 1ull << (t & 63));   // inwards: towards the points off it
+}
+
+__global__ __launch_bounds__(1024) void k3_poly(Poly3 *__restrict__ out) {
+    __shared__ I3 q[S3];
+    __shared__ int nf;
+    __shared__ unsigned long long keep[TWORDS3];
     __shared__ int wpre[TWORDS3];
+    __shared__ int wsum[1024 / WAVE];
     __shared__ I3 fn[F3_CAP];
     __shared__ I3 fa[F3_CAP];
     __shared__ double rmin[1024 / WAVE];
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6, NW = blockDim.x >> 6;
-    // 1. slots: wave w reduces slots w, w + NW, ... over the partials
-    for (int k = w; k < S3; k += NW) {
-        const bool mx = k & 1;
-        double v = mx ? -INFINITY : INFINITY;
-        uint32_t i = NONE;
-        for (int64_t r = lane; r < W; r += WAVE) {
-            const uint32_t ii = pidx[r * S3 + k];
-            const double vv = pval[r * S3 + k];
-            if (ii == NONE) continue;
-            if (i == NONE || (mx ? vv > v : vv < v) || (vv == v && ii < i)) { v = vv; i = ii; }
-        }
+    const int mm = out->m;
+    if (tid < mm) q[tid] = out->q[tid];
+    // the words' kept triples and the number before each
+    static_assert(TWORDS3 <= 1024, "a word per thread");
+    const unsigned long long mine = tid < TWORDS3 ? out->keep[tid] : 0;
+    if (tid < TWORDS3) keep[tid] = mine;
+    int inc = __popcll(mine);
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const double ov = __shfl_xor(v, o);
-            const uint32_t oi = (uint32_t)__shfl_xor((int)i, o);
-            if (oi != NONE && (i == NONE || (mx ? ov > v : ov < v) || (ov == v && oi < i))) { v = ov; i = oi; }
-        }
-        if (lane == 0) bi[k] = i;
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int v = __shfl_up(inc, o);
+        if (lane >= o) inc += v;
     }
-    for (int i = tid; i < TWORDS3; i += blockDim.x) { keep[i] = 0; flipb[i] = 0; }
+    if (lane == WAVE - 1) wsum[w] = inc;
     __syncthreads();
-    if (tid < S3 && slots_out) slots_out[tid] = bi[tid];
-    // 2. distinct points: the first slot of each coordinate triple, in slot order
-    if (w == 0) {
-        const bool valid = lane < S3 && bi[lane] != NONE;
-        I3 p{0, 0, 0};
-        if (valid) p = grid3(x, y, z, bi[lane]);
-        if (lane < S3) qs[lane] = p;
-        wave_sync();
-        bool first = valid;
-        for (int j = 0; j < lane && first; j++)
-            if (bi[j] != NONE && qs[j].x == p.x && qs[j].y == p.y && qs[j].z == p.z) first = false;
-        const uint64_t bm = __ballot(first);
-        if (first) {
-            const int pos = __popcll(bm & lanemask_lt());
-            q[pos] = p;
-            qi[pos] = bi[lane];
-        }
-        if (lane == 0) m = __popcll(bm);
-    }
-    __syncthreads();
-    // 3. supporting planes through three distinct points; of the triples on
-    // one plane only the canonical one is kept: the plane's two lowest
-    // points and the lowest point after them off their line
-    const int mm = m;
-    for (int t = tid; t < TRIPLES3; t += blockDim.x) {
-        int i, j, k;
-        triple_of(t, i, j, k);
-        if (k >= mm) continue;
-        const I3 nrm = i3_cross(i3_sub(q[j], q[i]), i3_sub(q[k], q[i]));
-        if (i3_zero(nrm)) continue;
-        const Plane3 P = make_plane(nrm, q[i]);
-        int pos = 0, neg = 0;
-        unsigned long long on = 0;
-        for (int r = 0; r < mm; r++) {
-            const int sg = plane_sign(P, (double)q[r].x, (double)q[r].y, (double)q[r].z);
-            pos += sg > 0;
-            neg += sg < 0;
-            on |= (unsigned long long)(sg == 0) << r;
-        }
-        if ((pos && neg) || (!pos && !neg)) continue;
-        const int i0 = __ffsll(on) - 1;
-        const unsigned long long on1 = on & (on - 1);
-        const int j0 = __ffsll(on1) - 1;
-        if (i != i0 || j != j0) continue;
-        int k0 = -1;
-        for (unsigned long long rest = on1 & (on1 - 1); rest; rest &= rest - 1) {
-            const int r = __ffsll(rest) - 1;
-            if (!i3_zero(i3_cross(i3_sub(q[j0], q[i0]), i3_sub(q[r], q[i0])))) { k0 = r; break; }
-        }
-        if (k != k0) continue;
-        atomicOr(&keep[t >> 6], 1ull << (t & 63));
-        if (neg) atomicOr(&flipb[t >> 6], 1ull << (t & 63));   // inwards: towards the points off it
-    }
-    __syncthreads();
-    // 4. the kept planes in triple order
-    if (tid == 0) {
-        int sum = 0;
-        for (int wd = 0; wd < TWORDS3; wd++) { wpre[wd] = sum; sum += __popcll(keep[wd]); }
-        nf = min(sum, F3_CAP);      // at most 2 * 42 - 4 faces
-    }
+    int before = 0;
+    for (int ww = 0; ww < w; ww++) before += wsum[ww];
+    if (tid < TWORDS3) wpre[tid] = before + inc - __popcll(mine);
+    if (tid == 1023) nf = min(before + inc, F3_CAP);      // at most 2 * 42 - 4 faces
     __syncthreads();
     for (int t = tid; t < TRIPLES3; t += blockDim.x) {
         const unsigned long long kw = keep[t >> 6], bit = 1ull << (t & 63);
@@ -348,15 +406,20 @@ __global__ __launch_bounds__(1024) void k3_poly(const float *__restrict__ x, con
         int i, j, k;
         triple_of(t, i, j, k);
         I3 nrm = i3_cross(i3_sub(q[j], q[i]), i3_sub(q[k], q[i]));
-        if (flipb[t >> 6] & bit) nrm = I3{-nrm.x, -nrm.y, -nrm.z};
+        if (out->flip[t >> 6] & bit) nrm = I3{-nrm.x, -nrm.y, -nrm.z};
         fn[pos] = nrm;
         fa[pos] = q[i];
     }
     __syncthreads();
     // 5. output and the quick-accept ball
     const int nff = nf;
-    for (int g = tid; g < nff; g += blockDim.x) out->f[g] = make_plane(fn[g], fa[g]);
-    if (tid < mm) out->pts[tid] = qi[tid];
+    // up to a multiple of eight with planes that every point is inside of
+    if (tid >= nff && tid < (nff + 7) / 8 * 8) out->k[tid] = PlaneK{0.0, 0.0, 0.0, -1.0, 0.0};
+    for (int g = tid; g < nff; g += blockDim.x) {
+        const Plane3 Q = make_plane(fn[g], fa[g]);
+        out->f[g] = Q;
+        out->k[g] = PlaneK{Q.nx, Q.ny, Q.nz, fma(Q.nz, Q.az, fma(Q.ny, Q.ay, Q.nx * Q.ax)), Q.bound};
+    }
     double cx = 0, cy = 0, cz = 0;
     for (int r = 0; r < mm; r++) { cx += (double)q[r].x; cy += (double)q[r].y; cz += (double)q[r].z; }
     cx /= mm > 0 ? mm : 1; cy /= mm > 0 ? mm : 1; cz /= mm > 0 ? mm : 1;
@@ -375,7 +438,6 @@ __global__ __launch_bounds__(1024) void k3_poly(const float *__restrict__ x, con
     if (tid == 0) {
         for (int ww = 1; ww < NW; ww++) r = fmin(r, rmin[ww]);
         out->nf = nff;
-        out->m = mm;
         // relative and absolute margins far above the rounding of these sums
         const double rs = nff > 0 ? r * (1.0 - 0x1p-20) - 4.0 : -1.0;
         out->cx = cx; out->cy = cy; out->cz = cz;
@@ -386,48 +448,74 @@ __global__ __launch_bounds__(1024) void k3_poly(const float *__restrict__ x, con
 // ---------------------------------------------------------------------------
 // Step 3: strict-inside test, survivor masks and counts per tile in the
 // layout of the 2D passes (bit l of word 4 c + j: point c*256 + 4 l + j).
-// Each lane takes its four points of a chunk together through the planes.
-// A plane is evaluated as n.p - n.a with n.a rounded once per block: both
-// dot products stay below |n|_1 2^24, so the three roundings of each, and
-// the final subtraction, err by less than |n|_1 2^-26, inside the plane's
-// bound |n|_1 2^-24; within the bound the sign is taken exactly.
-struct PlaneK {
-    double nx, ny, nz, na, bound;
-};
+// The points outside the quick-accept ball go to a queue of the wave, which
+// takes them through the planes 64 at a time: half of a ball's points, but
+// some in every chunk, so testing the chunks where they lie walked all the
+// planes for every point (803 us for 2^24 points).  A batch takes eight
+// planes at a time, from the scalar cache and without branches, so that
+// their loads overlap (a plane at a time, from LDS or memory, each waiting
+// for its own loads, 738 and 984 us; now 218).
+// A plane is evaluated as n.p - n.a, three fused steps from -(n.a) rounded
+// once: every partial sum stays below |n|_1 2^25, so the roundings err by less
+// than |n|_1 2^-26, inside the plane's bound |n|_1 2^-24; within the bound the
+// sign is taken exactly.
+constexpr int Q3 = 320;              // queue entries per wave: under 64, then up to 256 more
 
 __global__ __launch_bounds__(256) void k3_discard(const float *__restrict__ x, const float *__restrict__ y,
                                                   const float *__restrict__ z, int64_t n,
                                                   const Poly3 *__restrict__ P, uint64_t *__restrict__ masks,
                                                   uint32_t *__restrict__ tile_cnt) {
-    __shared__ Plane3 fl[F3_CAP];
-    __shared__ PlaneK fk[F3_CAP];
-    __shared__ int nfs;
-    __shared__ double ball[4];
-    const int tid = threadIdx.x, lane = lane_id();
-    if (tid == 0) {
-        nfs = P->nf;
-        ball[0] = P->cx; ball[1] = P->cy; ball[2] = P->cz; ball[3] = P->r2;
-    }
-    __syncthreads();
-    const int nf = nfs;
-    for (int g = tid; g < nf; g += blockDim.x) {
-        const Plane3 Q = P->f[g];
-        fl[g] = Q;
-        PlaneK K;
-        K.nx = Q.nx; K.ny = Q.ny; K.nz = Q.nz;
-        K.na = fma(Q.nz, Q.az, fma(Q.ny, Q.ay, Q.nx * Q.ax));
-        K.bound = Q.bound;
-        fk[g] = K;
-    }
-    __syncthreads();
-    const double cx = ball[0], cy = ball[1], cz = ball[2], r2 = ball[3];
+    __shared__ float qx[4][Q3], qy[4][Q3], qz[4][Q3];
+    __shared__ uint16_t qpos[4][Q3];
+    __shared__ unsigned long long tmask[4][TILE_WORDS];
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const uint64_t lt = lanemask_lt();
+    const int nf = P->nf;
+    const double cx = P->cx, cy = P->cy, cz = P->cz, r2 = P->r2;
     const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + tid) >> 6;
     const int64_t W = (int64_t(gridDim.x) * blockDim.x) >> 6;
     const int64_t T = (n + TILE - 1) / TILE;
+    // the planes through the scalar cache: read-only here, at uniform addresses
+    typedef const __attribute__((address_space(4))) PlaneK *PlanesC;
+    const PlanesC pk = (PlanesC)(uintptr_t)P->k;
+    float *QX = qx[w], *QY = qy[w], *QZ = qz[w];
+    uint16_t *QP = qpos[w];
+    unsigned long long *M = tmask[w];
+    // queue entries [from, from + count): those not strictly inside set their
+    // bit of the tile's mask
+    auto drain = [&](int from, int count) {
+        const int i = from + min(lane, count - 1);
+        const double px = (double)truncf(QX[i] * GRIDF), py = (double)truncf(QY[i] * GRIDF),
+                     pz = (double)truncf(QZ[i] * GRIDF);
+        // wave masks without branches: lanes some plane does not show to be
+        // strictly inside, and lanes some plane shows to be outside; the rest
+        // of the former are decided exactly
+        const uint64_t used = count >= WAVE ? ~uint64_t(0) : (uint64_t(1) << count) - 1;
+        uint64_t maybe = 0, outside = 0;
+        for (int g0 = 0; g0 < nf && (used & ~outside); g0 += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const double e = fma(pk[g0 + u].nx, px, fma(pk[g0 + u].ny, py, fma(pk[g0 + u].nz, pz, -pk[g0 + u].na)));
+                maybe |= __ballot(!(e > pk[g0 + u].bound));
+                outside |= __ballot(e < -pk[g0 + u].bound);
+            }
+        }
+        bool out = (outside >> lane) & 1;
+        if ((maybe & ~outside) & used) {
+            if (((maybe & ~outside) >> lane) & 1)
+                for (int g = 0; g < nf && !out; g++) out = plane_sign(P->f[g], px, py, pz) <= 0;
+        }
+        out = out && lane < count;
+        if (out) {
+            const int p = QP[i];
+            atomicOr(&M[(p >> 8) * 4 + (p & 3)], 1ull << ((p >> 2) & 63));
+        }
+    };
     for (int64_t t = wave; t < T; t += W) {
         const int64_t tb = t * TILE;
         const bool full = tb + TILE <= n;
-        uint32_t cnt = 0;
+        if (lane < TILE_WORDS) M[lane] = 0;
+        int qn = 0;
 #pragma unroll 1
         for (int c = 0; c < TILE_CHUNKS; c++) {
             const int64_t p0 = tb + c * CHUNK + 4 * lane;
@@ -451,41 +539,40 @@ __global__ __launch_bounds__(256) void k3_discard(const float *__restrict__ x, c
                     zs[j] = valid[j] ? z[p0 + j] : 0.f;
                 }
             }
-            double px[4], py[4], pz[4];
-            bool live[4], out[4];
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                px[j] = (double)(int64_t)(xs[j] * GRIDF);
-                py[j] = (double)(int64_t)(ys[j] * GRIDF);
-                pz[j] = (double)(int64_t)(zs[j] * GRIDF);
-                const double dx = px[j] - cx, dy = py[j] - cy, dz = pz[j] - cz;
+                const double dx = (double)truncf(xs[j] * GRIDF) - cx, dy = (double)truncf(ys[j] * GRIDF) - cy,
+                             dz = (double)truncf(zs[j] * GRIDF) - cz;
                 const bool in_ball = dx * dx + dy * dy + dz * dz < r2;
-                live[j] = valid[j] && nf > 0 && !in_ball;     // still to be tested
-                out[j] = false;
-            }
-            for (int g = 0; g < nf; g++) {
-                if (!__ballot(live[0] || live[1] || live[2] || live[3])) break;
-                const PlaneK K = fk[g];
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    if (!live[j]) continue;
-                    const double e = fma(K.nz, pz[j], fma(K.ny, py[j], K.nx * px[j])) - K.na;
-                    if (e > K.bound) continue;
-                    if (e < -K.bound || plane_sign(fl[g], px[j], py[j], pz[j]) <= 0) {
-                        live[j] = false;
-                        out[j] = true;
-                    }
+                const bool push = valid[j] && nf > 0 && !in_ball;
+                const uint64_t b = __ballot(push);
+                if (push) {
+                    const int o = qn + __popcll(b & lt);
+                    QX[o] = xs[j];
+                    QY[o] = ys[j];
+                    QZ[o] = zs[j];
+                    QP[o] = (uint16_t)(c * CHUNK + 4 * lane + j);
+                }
+                qn += __popcll(b);
+                if (nf == 0) {                       // no interior: every point survives
+                    const uint64_t v = __ballot(valid[j]);
+                    if (lane == 0) M[c * 4 + j] = v;
                 }
             }
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const bool surv = valid[j] && (nf == 0 || out[j]);
-                const uint64_t bm = __ballot(surv);
-                cnt += (uint32_t)__popcll(bm);
-                if (lane == 0) masks[t * TILE_WORDS + c * 4 + j] = bm;
+            wave_sync();
+            while (qn >= WAVE) {
+                qn -= WAVE;
+                drain(qn, WAVE);
             }
+            wave_sync();
         }
+        if (qn > 0) drain(0, qn);
+        wave_sync();
+        const uint64_t mw = lane < TILE_WORDS ? M[lane] : 0;
+        if (lane < TILE_WORDS) masks[t * TILE_WORDS + lane] = mw;
+        const uint32_t cnt = (uint32_t)wave_sum_i64((int64_t)__popcll(mw));
         if (lane == 0) tile_cnt[t] = cnt;
+        wave_sync();
     }
 }
 
@@ -526,7 +613,7 @@ struct Hull3Ctl {
     int64_t nrm[3];               // flat sets: their plane's normal
 };
 
-__device__ __forceinline__ double pdx(const float *v, uint32_t i) { return (double)(int64_t)(v[i] * GRIDF); }
+__device__ __forceinline__ double pdx(const float *v, uint32_t i) { return (double)truncf(v[i] * GRIDF); }
 
 // far key: distance estimate (non-negative float bits) above, ~index below
 __device__ __forceinline__ unsigned long long key_of(double d, uint32_t i) {
@@ -728,8 +815,8 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
             c[it] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (t >= nc) continue;
             c[it] = cin[t];
-            const double px = (double)(int64_t)(c[it].x * GRIDF), py = (double)(int64_t)(c[it].y * GRIDF),
-                         pz = (double)(int64_t)(c[it].z * GRIDF);
+            const double px = (double)truncf(c[it].x * GRIDF), py = (double)truncf(c[it].y * GRIDF),
+                         pz = (double)truncf(c[it].z * GRIDF);
             auto best_of = [&](int lo, int hi, bool alive_only) {
                 int bf = -1;
                 double bd = 0;
