@@ -4,11 +4,11 @@
 // sets) are the 2D path's.
 
 // Device buffers of the 3D path, owned by the context and grown on demand:
-// A holds what the filter passes need, B the hull stage (sized once the
-// survivor count is known).
+// A holds what the filter passes need, S the candidates' reduction before the
+// rounds, B the hull stage (each sized once its count is known).
 struct Hull3Bufs {
-    char *a = nullptr, *b = nullptr;
-    size_t acap = 0, bcap = 0;
+    char *a = nullptr, *b = nullptr, *s = nullptr;
+    size_t acap = 0, bcap = 0, scap = 0;
     // the rounds' status as the host reads it, one round behind
     Hull3Ctl *seen = nullptr;            // two, pinned
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -18,6 +18,7 @@ static void hull3_free(Hull3Bufs *h) {
     if (!h) return;
     if (h->a) (void)hipFree(h->a);
     if (h->b) (void)hipFree(h->b);
+    if (h->s) (void)hipFree(h->s);
     if (h->seen) (void)hipHostFree(h->seen);
     for (hipEvent_t e : h->ev)
         if (e) (void)hipEventDestroy(e);
@@ -109,11 +110,37 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
     HIPCHECK(hipMemcpyAsync(&nc, scount, 8, hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st));
 
-    // Step 4, with face room grown and the hull restarted if it runs out
+    // Step 4.  Many candidates: those inside tetrahedra of far points go first
+    const uint32_t *cidx = sv;               // the candidates' indices
+    const float4 *cpts = nullptr;            // and coordinates, where they are at hand
+    if (!nofilter && nc >= STAR_MIN) {
+        const int side = star_side(nc), ncell = star_cells(side);
+        size_t os = 0;
+        auto ts = [&](size_t bytes) { size_t r = os; os += al(bytes); return r; };
+        const size_t s_pts = ts(nc * 16), s_out = ts(nc * 16), s_idx = ts(nc * 4), s_cell = ts((ncell + 1) * 8),
+                     s_tab = ts(ncell * 16);
+        if ((rc = grow(&B->s, &B->scap, os))) return rc;
+        float4 *pts = reinterpret_cast<float4 *>(B->s + s_pts), *kept = reinterpret_cast<float4 *>(B->s + s_out);
+        uint32_t *kidx = reinterpret_cast<uint32_t *>(B->s + s_idx);
+        auto *cells = reinterpret_cast<unsigned long long *>(B->s + s_cell);     // then the kept count
+        float4 *tab = reinterpret_cast<float4 *>(B->s + s_tab);
+        const unsigned gq = (unsigned)std::min<int64_t>(ctx->cus * 8, (nc + 255) / 256);
+        LAUNCH(K_MISC, k_fill_i64<<<64, 256, 0, st>>>(reinterpret_cast<int64_t *>(cells), ncell + 1, 0));
+        LAUNCH(K_REFINE, k3_star_far<<<gq, 256, 0, st>>>(x, y, z, sv, nc, poly, side, cells, pts));
+        LAUNCH(K_REFINE, k3_star_table<<<(ncell + 255) / 256, 256, 0, st>>>(cells, ncell, pts, tab));
+        LAUNCH(K_REFINE, k3_star_keep<<<gq, 256, 0, st>>>(pts, nc, poly, side, tab, kept, kidx, cells + ncell));
+        HIPCHECK(hipMemcpyAsync(&nc, cells + ncell, 8, hipMemcpyDeviceToHost, st));
+        HIPCHECK(hipStreamSynchronize(st));
+        cidx = kidx;
+        cpts = kept;
+    }
+    // The rounds, with face room grown and the hull restarted if it runs out
     for (int64_t fcap = std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);; fcap *= 2) {
         size_t ob = 0;
         auto tb = [&](size_t bytes) { size_t r = ob; ob += al(bytes); return r; };
-        const size_t b_idx = tb(nc * 4 + 16), b_ca = tb(nc * 16 + 16), b_cb = tb(nc * 16 + 16),
+        // a copy of the survivor list, which may lie in the workspace that the
+        // flat case and the sort lay out anew
+        const size_t b_idx = tb(cpts ? 16 : nc * 4 + 16), b_ca = tb(nc * 16 + 16), b_cb = tb(nc * 16 + 16),
                      b_fa = tb(nc * 4 + 16), b_fb = tb(nc * 4 + 16), b_faces = tb(fcap * sizeof(Face3)),
                      b_planes = tb(fcap * sizeof(Plane3)), b_far = tb(fcap * 8), b_vis = tb(fcap * 4),
                      b_repl = tb(fcap * sizeof(int2)), b_claim = tb(2 * fcap * 8),
@@ -122,7 +149,11 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
                      b_corner = tb(nc * 8 + 16), b_ncorner = tb(16);
         if ((rc = grow(&B->b, &B->bcap, ob))) return rc;
         char *hb = B->b;
-        uint32_t *cidx = reinterpret_cast<uint32_t *>(hb + b_idx);
+        if (!cpts) {
+            uint32_t *copy = reinterpret_cast<uint32_t *>(hb + b_idx);
+            if (nc > 0 && cidx != copy) HIPCHECK(hipMemcpyAsync(copy, sv, nc * 4, hipMemcpyDeviceToDevice, st));
+            cidx = copy;
+        }
         float4 *cand[2] = {reinterpret_cast<float4 *>(hb + b_ca), reinterpret_cast<float4 *>(hb + b_cb)};
         int *cf[2] = {reinterpret_cast<int *>(hb + b_fa), reinterpret_cast<int *>(hb + b_fb)};
         unsigned long long *claim = reinterpret_cast<unsigned long long *>(hb + b_claim);
@@ -138,8 +169,6 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         int2 *repl = reinterpret_cast<int2 *>(hb + b_repl);
         uint64_t *corner = reinterpret_cast<uint64_t *>(hb + b_corner);
         int *ncorner = reinterpret_cast<int *>(hb + b_ncorner);
-        if (nc > 0)
-            HIPCHECK(hipMemcpyAsync(cidx, sv, nc * 4, hipMemcpyDeviceToDevice, st));
         LAUNCH(K_MISC, k3_ctl_init<<<1, 64, 0, st>>>(C, (int)fcap));
         const unsigned gs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ctx->cus * 4, (nc + 255) / 256));
         for (int phase = 1; phase <= 3; phase++)
@@ -174,7 +203,8 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         } else {
             LAUNCH(K_MISC, k3_fill_i32<<<256, 256, 0, st>>>(vis, fcap, -1));
             LAUNCH(K_MISC, k_fill_i64<<<256, 256, 0, st>>>(reinterpret_cast<int64_t *>(claim), 2 * fcap, 0));
-            LAUNCH(K_MISC, k3_gather<<<gs, 256, 0, st>>>(x, y, z, cidx, nc, cand[0]));
+            if (cpts) HIPCHECK(hipMemcpyAsync(cand[0], cpts, nc * 16, hipMemcpyDeviceToDevice, st));
+            else LAUNCH(K_MISC, k3_gather<<<gs, 256, 0, st>>>(x, y, z, cidx, nc, cand[0]));
             const bool all_serial = flags & HULL3_SERIAL;
             bool overflow = false;
             bool was_serial[2] = {false, false};

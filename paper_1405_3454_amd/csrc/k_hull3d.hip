@@ -47,6 +47,7 @@ struct Plane3 {
     double nx, ny, nz;
     double ax, ay, az;
     double bound;
+    double inv;             // 1 / |n|, for distances; fills the cache line
 };
 
 __device__ __forceinline__ Plane3 make_plane(I3 n, I3 a) {
@@ -56,13 +57,16 @@ __device__ __forceinline__ Plane3 make_plane(I3 n, I3 a) {
     // three products of |n_i| < 2^51 by |d_i| < 2^25 and two sums: the
     // rounding error stays far below 2^-49 |n|_1 2^25
     P.bound = (fabs(P.nx) + fabs(P.ny) + fabs(P.nz)) * 0x1p-24;
+    P.inv = rsqrt(P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
     return P;
 }
 
-// Sign of the plane at grid point (px, py, pz): binary64 estimate, exact
-// 128-bit fallback when it is within the error bound.
-__device__ __forceinline__ int plane_sign(const Plane3 &P, double px, double py, double pz) {
-    const double e = fma(P.nz, pz - P.az, fma(P.ny, py - P.ay, P.nx * (px - P.ax)));
+// The plane at grid point (px, py, pz) in binary64, and its sign: from that
+// estimate, exact in 128 bits when it is within the error bound.
+__device__ __forceinline__ double plane_value(const Plane3 &P, double px, double py, double pz) {
+    return fma(P.nz, pz - P.az, fma(P.ny, py - P.ay, P.nx * (px - P.ax)));
+}
+__device__ __forceinline__ int plane_sign_of(const Plane3 &P, double e, double px, double py, double pz) {
     if (e > P.bound) return 1;
     if (e < -P.bound) return -1;
     const __int128 v = (__int128)(int64_t)P.nx * (int64_t)(px - P.ax) +
@@ -70,10 +74,8 @@ __device__ __forceinline__ int plane_sign(const Plane3 &P, double px, double py,
                        (__int128)(int64_t)P.nz * (int64_t)(pz - P.az);
     return v > 0 ? 1 : v < 0 ? -1 : 0;
 }
-// Distance estimate of a point beyond a plane (for choosing far points).
-__device__ __forceinline__ double plane_dist(const Plane3 &P, double px, double py, double pz) {
-    const double e = fma(P.nz, pz - P.az, fma(P.ny, py - P.ay, P.nx * (px - P.ax)));
-    return e * rsqrt(P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
+__device__ __forceinline__ int plane_sign(const Plane3 &P, double px, double py, double pz) {
+    return plane_sign_of(P, plane_value(P, px, py, pz), px, py, pz);
 }
 
 // ---------------------------------------------------------------------------
@@ -764,6 +766,168 @@ __global__ __launch_bounds__(256) void k3_gather(const float *__restrict__ x, co
     }
 }
 
+// Candidates in the millions, before the rounds: those strictly inside
+// tetrahedra of four known points of the hull are dropped, so that the rounds
+// start with the few near its surface.  (The first rounds have few faces and
+// every candidate: the 4e6 survivors of a ball of 2^24 points kept the rounds'
+// assignments at 2.3 ms, since they left by a fifth a round; the launches here
+// take 375 us and bring the assignments to 0.66 ms.)
+//
+// The directions from the polyhedron's centre c (on the grid, strictly inside:
+// its ball is wider than the rounding) are cut into the cells of a cube map,
+// G x G per face; each face's map goes on STAR_PAD cells past the face, so
+// that every cell's neighbours lie in its own map.  A cell's far point is the
+// farthest from c of the candidates in it.  In the map's coordinates straight
+// lines are planes through c; the far points of a cell's eight neighbours make
+// a ring around the cell (a side of the ring joins two points beyond the same
+// side of the cell), so a candidate's direction lies in one of the eight
+// triangles of the ring and the cell's own far point A.  Where the candidate
+// is also strictly below that triangle's plane it is a proper convex
+// combination of c and the three points: strictly inside the hull.  The four
+// determinants are sums of three products below 2^77 in binary64, which err
+// by less than 2^27, and every comparison keeps 2^30 away from zero: what is
+// not certain is kept.  Empty cells and the outermost candidates keep
+// everything they should.
+constexpr int STAR_PAD = 2;
+constexpr int64_t STAR_MIN = 1 << 16;       // fewer candidates go to the rounds directly
+__host__ __device__ __forceinline__ int star_side(int64_t nc) {       // 64 to 256 candidates a cell
+    int g = 16;
+    while (g < 128 && (int64_t)6 * g * g * 256 < nc) g *= 2;
+    return g;
+}
+__host__ __device__ __forceinline__ int star_cells(int g) { return 6 * (g + 2 * STAR_PAD) * (g + 2 * STAR_PAD); }
+
+// Cell of direction d in the map of axis a, or -1 outside of it.
+__device__ __forceinline__ int star_cell(const float *d, int a, int g) {
+    const float m = fabsf(d[a]);
+    if (!(m > 0)) return -1;
+    const int gd = g + 2 * STAR_PAD;
+    const float h = 0.5f * (float)g;
+    const float b = d[a == 2 ? 0 : a + 1], c = d[a == 0 ? 2 : a - 1];
+    const float r = 1.0f / m;
+    const int i = (int)floorf((b * r + 1.0f) * h) + STAR_PAD, j = (int)floorf((c * r + 1.0f) * h) + STAR_PAD;
+    if (i < 0 || j < 0 || i >= gd || j >= gd || fabsf(b * r) > 3.0f || fabsf(c * r) > 3.0f) return -1;
+    return ((2 * a + (d[a] < 0)) * gd + j) * gd + i;
+}
+
+__device__ __forceinline__ bool star_on(const Poly3 *P) { return P->nf > 0 && P->r2 > 0; }
+
+// The candidates with their coordinates, and the cells' farthest keys
+// (distance from c, ~position in the list).
+__global__ __launch_bounds__(256) void k3_star_far(const float *__restrict__ x, const float *__restrict__ y,
+                                                   const float *__restrict__ z, const uint32_t *__restrict__ idx,
+                                                   int64_t n, const Poly3 *__restrict__ P, int g,
+                                                   unsigned long long *__restrict__ cells,
+                                                   float4 *__restrict__ pts) {
+    const bool on = star_on(P);
+    const float cx = (float)rint(P->cx), cy = (float)rint(P->cy), cz = (float)rint(P->cz);
+    for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += int64_t(gridDim.x) * blockDim.x) {
+        const uint32_t i = idx[t];
+        const float4 p = make_float4(x[i], y[i], z[i], __uint_as_float(i));
+        pts[t] = p;
+        if (!on) continue;
+        const float d[3] = {p.x * GRIDF - cx, p.y * GRIDF - cy, p.z * GRIDF - cz};
+        const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+        const unsigned long long k = ((unsigned long long)__float_as_uint(r2) << 32) | (uint32_t)~(uint32_t)t;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const int c = star_cell(d, a, g);
+            if (c >= 0) far_update(&cells[c], k);
+        }
+    }
+}
+
+// The far points themselves (w = 0: an empty cell).
+__global__ __launch_bounds__(256) void k3_star_table(const unsigned long long *__restrict__ cells, int n,
+                                                     const float4 *__restrict__ pts, float4 *__restrict__ tab) {
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= n) return;
+    const unsigned long long k = cells[c];
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (k) {
+        p = pts[~(uint32_t)k];
+        p.w = 1.0f;
+    }
+    tab[c] = p;
+}
+
+__global__ __launch_bounds__(256) void k3_star_keep(const float4 *__restrict__ pts, int64_t n,
+                                                    const Poly3 *__restrict__ P, int g,
+                                                    const float4 *__restrict__ tab, float4 *__restrict__ out,
+                                                    uint32_t *__restrict__ idx_out,
+                                                    unsigned long long *__restrict__ count) {
+    __shared__ int bcnt;
+    __shared__ int64_t bbase;
+    const bool on = star_on(P);
+    const int gd = g + 2 * STAR_PAD, lane = lane_id();
+    const double cx = rint(P->cx), cy = rint(P->cy), cz = rint(P->cz);
+    const int64_t nt = int64_t(gridDim.x) * 256;
+    for (int64_t t0 = int64_t(blockIdx.x) * 256; t0 < n; t0 += nt) {
+        const int64_t t = t0 + threadIdx.x;
+        const bool has = t < n;
+        bool keep = has;
+        float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (has) p = pts[t];
+        if (has && on) {
+            const float df[3] = {p.x * GRIDF - (float)cx, p.y * GRIDF - (float)cy, p.z * GRIDF - (float)cz};
+            const float ax = fabsf(df[0]), ay = fabsf(df[1]), az = fabsf(df[2]);
+            const int a = ax >= ay && ax >= az ? 0 : ay >= az ? 1 : 2;
+            const int cell = star_cell(df, a, g);
+            const int i = cell < 0 ? 0 : cell % gd, j = cell < 0 ? 0 : cell / gd % gd;
+            if (cell >= 0 && i > 0 && j > 0 && i < gd - 1 && j < gd - 1) {
+                const float4 A = tab[cell];
+                const double dx = (double)truncf(p.x * GRIDF) - cx, dy = (double)truncf(p.y * GRIDF) - cy,
+                             dz = (double)truncf(p.z * GRIDF) - cz;
+                const double px = (double)truncf(A.x * GRIDF) - cx, py = (double)truncf(A.y * GRIDF) - cy,
+                             pz = (double)truncf(A.z * GRIDF) - cz;
+                const double qx = dy * pz - dz * py, qy = dz * px - dx * pz, qz = dx * py - dy * px;   // d x a
+                constexpr double EPS = 0x1p30;
+                const int ring[9] = {1, 1 + gd, gd, gd - 1, -1, -1 - gd, -gd, 1 - gd, 1};
+                double bx = 0, by = 0, bz = 0, sb = 0;
+                bool pb = false;
+#pragma unroll
+                for (int k = 0; k < 9; k++) {
+                    const float4 R = tab[cell + ring[k]];
+                    const double rx = (double)truncf(R.x * GRIDF) - cx, ry = (double)truncf(R.y * GRIDF) - cy,
+                                 rz = (double)truncf(R.z * GRIDF) - cz;
+                    const double sr = rx * qx + ry * qy + rz * qz;          // det(a, r, d)
+                    const bool pr = R.w != 0;
+                    // between the last ring point b and this one, r
+                    if (k && pb && pr && ((sb >= EPS && sr <= -EPS) || (sb <= -EPS && sr >= EPS))) {
+                        const double nx = by * rz - bz * ry, ny = bz * rx - bx * rz, nz = bx * ry - by * rx;
+                        const double V = px * nx + py * ny + pz * nz;       // det(a, b, r)
+                        const double D = dx * nx + dy * ny + dz * nz;       // det(d, b, r)
+                        const double sg = V > 0 ? 1.0 : -1.0;
+                        if (sg * sb >= EPS && sg * sr <= -EPS && sg * D >= EPS &&
+                            sg * V - sg * (D - sr + sb) >= 4 * EPS)
+                            keep = false;
+                    }
+                    bx = rx;
+                    by = ry;
+                    bz = rz;
+                    sb = sr;
+                    pb = pr;
+                }
+                if (A.w == 0) keep = true;
+            }
+        }
+        if (threadIdx.x == 0) bcnt = 0;
+        __syncthreads();
+        const uint64_t m = __ballot(keep);
+        int o = 0;
+        if (lane == 0 && m) o = atomicAdd(&bcnt, __popcll(m));
+        o = __shfl(o, 0) + __popcll(m & lanemask_lt());
+        __syncthreads();
+        if (threadIdx.x == 0 && bcnt) bbase = (int64_t)atomicAdd(count, (unsigned long long)bcnt);
+        __syncthreads();
+        if (keep) {
+            out[bbase + o] = p;
+            idx_out[bbase + o] = __float_as_uint(p.w);
+        }
+        __syncthreads();
+    }
+}
+
 // A round's assignment (see above).  first: every candidate tests the start
 // faces.  A candidate whose face was removed follows the removals: the
 // insertion that removed a face created faces repl[f] = (first, count); the
@@ -773,7 +937,7 @@ __global__ __launch_bounds__(256) void k3_gather(const float *__restrict__ x, co
 // with one counter update; each wave merges the farthest keys of lanes that
 // share a face before updating far[].
 constexpr int CHAIN_MAX = 256;      // chain steps before a full scan
-constexpr int AS_ITEMS = 4;
+constexpr int AS_ITEMS = 2;
 constexpr int AS_MERGE = 4;         // faces merged per wave and item; the rest update directly
 
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
@@ -817,14 +981,24 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
             c[it] = cin[t];
             const double px = (double)truncf(c[it].x * GRIDF), py = (double)truncf(c[it].y * GRIDF),
                          pz = (double)truncf(c[it].z * GRIDF);
+            // the face of [lo, hi) that the candidate is farthest beyond
+            double fd = 0;
             auto best_of = [&](int lo, int hi, bool alive_only) {
                 int bf = -1;
-                double bd = 0;
-                for (int g = lo; g < hi; g++) {
-                    if (alive_only && !faces[g].alive) continue;
-                    if (plane_sign(planes[g], px, py, pz) > 0) {
-                        const double dg = plane_dist(planes[g], px, py, pz);
-                        if (bf < 0 || dg > bd) { bf = g; bd = dg; }
+                constexpr int U = 2;          // planes in flight
+                for (int g0 = lo; g0 < hi; g0 += U) {
+                    Plane3 P[U];
+#pragma unroll
+                    for (int u = 0; u < U; u++) P[u] = planes[min(g0 + u, hi - 1)];
+#pragma unroll
+                    for (int u = 0; u < U; u++) {
+                        const int g = g0 + u;
+                        if (g >= hi || (alive_only && !faces[g].alive)) continue;
+                        const double e = plane_value(P[u], px, py, pz);
+                        if (plane_sign_of(P[u], e, px, py, pz) > 0) {
+                            const double dg = e * P[u].inv;
+                            if (bf < 0 || dg > fd) { bf = g; fd = dg; }
+                        }
                     }
                 }
                 return bf;
@@ -834,6 +1008,10 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
                 g = best_of(0, nfaces, true);
             } else {
                 g = fin[t];
+                if (faces[g].alive) {
+                    const Plane3 P = planes[g];
+                    fd = plane_value(P, px, py, pz) * P.inv;
+                }
                 int steps = 0;
                 while (g >= 0 && !faces[g].alive && steps < CHAIN_MAX) {
                     const int2 r = repl[g];
@@ -843,7 +1021,7 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
                 if (g >= 0 && !faces[g].alive) g = best_of(0, nfaces, true);   // chain too long
             }
             f[it] = g;
-            if (g >= 0) key[it] = key_of(plane_dist(planes[g], px, py, pz), __float_as_uint(c[it].w));
+            if (g >= 0) key[it] = key_of(fd, __float_as_uint(c[it].w));
         }
         // appends: wave counts, a block offset, the wave's place in it
         uint64_t bal[AS_ITEMS];
