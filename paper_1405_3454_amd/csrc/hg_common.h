@@ -22,9 +22,12 @@ constexpr double GRIDD = 16777216.0;
 // Filter polygon of one set, in grid units (coordinate * 2^24, integers).
 // Edge e is strictly satisfied by p iff
 //     E_e(p) = fma(ex, py, fma(-ey, px, c)) > 0,   c = ey*ax - ex*ay,
-// exact in binary64 on the grid (|E| < 2^51).  Unused edges hold (0, 0, 1);
-// a polygon with fewer than 3 vertices has edge 0 = (0, 0, -1), so nothing
-// is strictly inside it.
+// exact in binary64 on the grid (|E| < 2^51).  Unused edges hold (0, 0, 1).
+// A polygon of two vertices has its segment's two directions as edges, so
+// nothing is strictly inside both, and the refinement rounds work on either
+// side of it (a thin diagonal set's extremes can be two points; without
+// edges all its points went to the sort).  With fewer vertices edge 0 is (0,
+// 0, -1): nothing is strictly inside it.
 struct Poly {
     double ex[MAX_SLOTS];
     double ey[MAX_SLOTS];

@@ -593,7 +593,7 @@ __device__ __forceinline__ void build_polygon(PolyScratch &G, const uint32_t *sl
         wave_sync();
         // lane e: vertex e and the edge from it to vertex e + 1
         const int e = lane;
-        const bool ev = e < h && h >= 3;
+        const bool ev = e < h && h >= 2;          // two vertices: there and back, nothing inside
         int ya = 0;
         if (e < MAX_SLOTS) {
             const double vx = e < h ? G.vx[e] : 0.0, vy = e < h ? G.vy[e] : 0.0;
@@ -619,7 +619,7 @@ __device__ __forceinline__ void build_polygon(PolyScratch &G, const uint32_t *sl
         if (lane == 0) {
             P.m = h;
             if (h < 3) {
-                P.c[0] = -1.0;    // nothing strictly inside
+                if (h < 2) P.c[0] = -1.0;    // nothing strictly inside
                 P.yspan = -1;
                 P.ky_lo = 0;
                 P.shift = 0;
@@ -826,7 +826,7 @@ __global__ __launch_bounds__(POLY_THREADS) void k_polygon(
         for (int i = tid; i < (int)(sizeof(Poly) / 4); i += (int)blockDim.x) dst[i] = src[i];
     }
     if (rtab) {    // the refinement's round-0 edges (the polygon's) and cleared farthest keys
-        const int m = P.m >= 3 ? P.m : 0;
+        const int m = P.m >= 2 ? P.m : 0;
         for (int e = tid; e < RE_CAP; e += blockDim.x) {
             REdge r = redge_empty();
             if (e < m) {
@@ -1113,7 +1113,7 @@ __device__ __forceinline__ void drain(DiscardLds &L, int from, int count, int32_
             }
         }
         out = (e & Q_OUTSIDE) || !inside;
-        if (MODE == DISCARD_ASSIGN && o.pm < 3) e_out = RE_NONE;   // no refinement edges
+        if (MODE == DISCARD_ASSIGN && o.pm < 2) e_out = RE_NONE;   // no refinement edges
     }
     if constexpr (MODE == DISCARD_MASKS) {
         if (out) {

@@ -170,7 +170,7 @@ __device__ __forceinline__ void small_edges(const Poly &P, const uint64_t *key, 
     bool rows[N];
     uint16_t any[N], met[N];
     int nmet[N];
-    const int m = P.m < 3 ? 0 : P.m;
+    const int m = P.m < 2 ? 0 : P.m;
 #pragma unroll
     for (int j = 0; j < N; j++) {
         const int32_t ky = (int32_t)(key[j] & 0xFFFFFF);
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
         }
         const int64_t ts = n ? (e - tile_base(a, phase) + TILE - 1) / TILE : 0;
         build_polygon(L.u.poly.G, sl, x, y, ts, L.P);
-        const int m = L.P.m >= 3 ? L.P.m : 0;
+        const int m = L.P.m >= 2 ? L.P.m : 0;
         for (int k = tid; k < MAX_SLOTS; k += BS) {
             const int b = k + 1 < m ? k + 1 : 0;
             L.tab[0][k] = k < m ? REdge{L.P.vx[k], L.P.vy[k], L.P.vx[b], L.P.vy[b]} : redge_empty();
