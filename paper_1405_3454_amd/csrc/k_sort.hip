@@ -37,6 +37,11 @@ constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_CLEAR_BLOCKS = 32;  // k_sort_small's blocks after the first: clear the passes' state
 constexpr int Y_DIGITS = 3;             // the low digits, which the hull stage's sort skips
 
+// Several sets of more than 1024 candidates in all are sorted set by set: 256
+// sets of about 16 candidates in 9 us, where one block took 47 for all 4000.
+__device__ __forceinline__ int64_t sort_small(const int *seg_fallback) {
+    return seg_fallback ? SMALL_THREADS : SORT_SMALL;
+}
 __host__ __device__ __forceinline__ int64_t sort_tile(int64_t count) {
     return count <= SORT_FEW ? SORT_THREADS * SORT_KPT_FEW : SORT_TILE;
 }
@@ -63,13 +68,124 @@ struct SortState {
     uint32_t nlong[3], ticket;           // long runs: a wave's, a block's, everyone's
 };
 
-// At most SORT_SMALL keys: block 0 sorts them in LDS (a rank per thread up to
-// 1024 keys: 2 us where the network below takes 10; above, a bitonic network
-// over the next power of two, padded with the largest key) and writes them
-// where the radix passes would have left them; the passes then return at
-// once.  Above SORT_SMALL the other blocks clear the passes' state and the
-// look-back entries of the tiles.  The sort is by key only, so equal keys are
-// interchangeable.
+// P keys in LDS (a power of two, at least 256) sorted by the 1024 threads of a
+// block.  Every wave ranks its 64 keys; then, up to 1024 keys, each key is
+// searched for in all the other runs of 64, four at a time, and goes to its
+// place at once; above, runs are merged in pairs, each key searched for in the
+// other run of its pair and moved to its own index plus what is below it there
+// (ties: the first run's first).  A bitonic network's barriers, log2(P)
+// (log2(P) + 1) / 2 of them, bound it before: 4096 sets of 600 keys took 103 us,
+// now 65 (73 with merges from 16 keys on, whose searches wait for one another); one
+// list of 4000 keys 50, now 23.
+__host__ __device__ __forceinline__ int sort_width(int n) {
+    int P = 4 * WAVE;
+    while (P < n) P <<= 1;
+    return P;
+}
+// The place of mine (key tid & 63 of the run at w0) in its run of 64 keys.
+__device__ __forceinline__ int run_rank(const uint64_t *b, int w0, uint64_t mine, int me) {
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < WAVE; j++) {
+        const uint64_t o = b[w0 + j];
+        rank += (int)(o < mine) | ((int)(o == mine) & (int)(j < me));
+    }
+    return rank;
+}
+// Keys of a later run come after equal ones of an earlier one: they are
+// searched for as key + 1.  Not padding (no key has its set field, 65535),
+// which may then land on padding: the places it leaves, beyond every key,
+// hold padding.
+__device__ __forceinline__ uint64_t search_key(uint64_t k, bool later) {
+    return k + (uint64_t)(later && k != ~0ull);
+}
+__device__ __forceinline__ void sort_1024(uint64_t *b, int P) {
+    const int tid = threadIdx.x, w0 = tid & ~(WAVE - 1);
+    const bool on = tid < P;
+    const uint64_t mine = on ? b[tid] : 0;
+    int rank = 0;
+    if (on) {
+        rank = run_rank(b, w0, mine, tid - w0);
+        wave_sync();
+        b[w0 + rank] = mine;
+    }
+    __syncthreads();
+    if (on)
+        for (int r0 = 0; r0 < P; r0 += 4 * WAVE) {
+            int pos[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int step = WAVE / 2; step > 0; step >>= 1)
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int r = r0 + u * WAVE;
+                    pos[u] += b[r + pos[u] + step - 1] < search_key(mine, r < w0) ? step : 0;
+                }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int r = r0 + u * WAVE;
+                pos[u] += b[r + pos[u]] < search_key(mine, r < w0) ? 1 : 0;
+                rank += r == w0 ? 0 : pos[u];
+            }
+        }
+    __syncthreads();
+    if (on) b[rank] = mine;
+    __syncthreads();
+}
+template <int K>
+__device__ __forceinline__ void merge_1024(uint64_t *b) {     // P = K * 1024
+    const int tid = threadIdx.x;
+    uint64_t k[K], lim[K];
+    int pos[K];
+#pragma unroll
+    for (int i = 0; i < K; i++) {
+        const int w0 = (tid & ~(WAVE - 1)) + i * SMALL_THREADS, me = tid & (WAVE - 1);
+        k[i] = b[w0 + me];
+        pos[i] = run_rank(b, w0, k[i], me);
+        wave_sync();
+        b[w0 + pos[i]] = k[i];
+    }
+    for (int run = WAVE; run < K * SMALL_THREADS; run <<= 1) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const int at = tid + i * SMALL_THREADS;
+            k[i] = b[at];
+            lim[i] = search_key(k[i], (at & run) != 0);
+            pos[i] = 0;
+        }
+        for (int step = run >> 1; step > 0; step >>= 1)
+#pragma unroll
+            for (int i = 0; i < K; i++) {
+                const int sib = ((tid + i * SMALL_THREADS) & ~(run - 1)) ^ run;
+                pos[i] += b[sib + pos[i] + step - 1] < lim[i] ? step : 0;
+            }
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const int sib = ((tid + i * SMALL_THREADS) & ~(run - 1)) ^ run;
+            pos[i] += b[sib + pos[i]] < lim[i] ? 1 : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const int at = tid + i * SMALL_THREADS;
+            b[(at & ~(2 * run - 1)) + (at & (run - 1)) + pos[i]] = k[i];
+        }
+    }
+    __syncthreads();
+}
+template <int PMAX>
+__device__ __forceinline__ void block_sort(uint64_t *b, int P) {
+    if (P <= SMALL_THREADS) sort_1024(b, P);
+    else if (P == 2 * SMALL_THREADS) merge_1024<2>(b);
+    else if (P == 4 * SMALL_THREADS || PMAX == 4 * SMALL_THREADS) merge_1024<4>(b);
+    else if constexpr (PMAX > 4 * SMALL_THREADS) merge_1024<8>(b);
+}
+
+// At most SORT_SMALL keys: block 0 sorts them in LDS, padded with the largest
+// key, and writes them where the radix passes would have left them; the
+// passes then return at once.  Above SORT_SMALL the other blocks clear the
+// passes' state and the look-back entries of the tiles.  The sort is by key
+// only, so equal keys are interchangeable.
 __global__ __launch_bounds__(SMALL_THREADS) void k_sort_small(const uint64_t *__restrict__ keys,
                                                               const int64_t *__restrict__ cnt_ptr,
                                                               uint64_t *__restrict__ out,
@@ -80,7 +196,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_sort_small(const uint64_t *__
     const int64_t count = *cnt_ptr;
     const int tid = threadIdx.x;
     if (seg_fallback && blockIdx.x == 0 && tid == 0) *seg_fallback = 0;
-    if (count > SORT_SMALL) {
+    if (count > sort_small(seg_fallback)) {
         if (blockIdx.x == 0) return;
         const int64_t nst = sort_tiles(count) * RADIX;
         const int64_t nt = (int64_t)(gridDim.x - 1) * SMALL_THREADS;
@@ -92,37 +208,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_sort_small(const uint64_t *__
     }
     if (blockIdx.x != 0 || count <= 0) return;
     const int n = (int)count;
-    if (n <= SMALL_THREADS) {
-        const uint64_t mine = tid < n ? keys[tid] : ~0ull;
-        b[tid] = mine;
-        __syncthreads();
-        int rank = 0;
-#pragma unroll 16
-        for (int j = 0; j < n; j++) {
-            const uint64_t o = b[j];
-            rank += (int)(o < mine) | ((int)(o == mine) & (int)(j < tid));
-        }
-        if (tid < n) out[rank] = mine;
-        return;
-    }
-    int m = 2;
-    while (m < n) m <<= 1;
-    for (int i = tid; i < m; i += SMALL_THREADS) b[i] = i < n ? keys[i] : ~0ull;
+    const int P = sort_width(n);
+    for (int i = tid; i < P; i += SMALL_THREADS) b[i] = i < n ? keys[i] : ~0ull;
     __syncthreads();
-    for (int k = 2; k <= m; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = tid; t < (m >> 1); t += SMALL_THREADS) {
-                const int i = 2 * j * (t / j) + (t % j), l = i + j;    // pair (i, l), i < l
-                const bool up = (i & k) == 0;                         // ascending run
-                const uint64_t a = b[i], c = b[l];
-                if ((a > c) == up) {
-                    b[i] = c;
-                    b[l] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
+    block_sort<SORT_SMALL>(b, P);
     for (int i = tid; i < n; i += SMALL_THREADS) out[i] = b[i];
 }
 
@@ -153,11 +242,10 @@ constexpr int SEG_THREADS = 1024;
 constexpr int SEG_MAX = 8192;         // keys of one set a block sorts in LDS (64 KB)
 
 // Each set's range [start[s], start[s + 1]) sorted in LDS by one block
-// (bitonic network over the next power of two, padded with the largest key)
 // into out, where the radix passes would have left it; block b takes the
 // sets b, b + gridDim.x, ...  A set of more than SEG_MAX keys, or a key in a
 // range that is not its set's, raises *fallback.
-__global__ __launch_bounds__(SEG_THREADS) void k_sort_sets(const uint64_t *__restrict__ keys,
+__global__ __launch_bounds__(SEG_THREADS, 8) void k_sort_sets(const uint64_t *__restrict__ keys,
                                                            const int64_t *__restrict__ cnt_ptr, int64_t S,
                                                            const int64_t *__restrict__ start,
                                                            uint64_t *__restrict__ out,
@@ -165,7 +253,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_sort_sets(const uint64_t *__res
     __shared__ uint64_t b[SEG_MAX];
     __shared__ int bad;
     const int64_t n = *cnt_ptr;
-    if (n <= SORT_SMALL) return;
+    if (n <= sort_small(fallback)) return;
     const int tid = threadIdx.x;
     for (int64_t s = blockIdx.x; s < S; s += gridDim.x) {
         const int64_t a = start[s], e = start[s + 1];
@@ -175,8 +263,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_sort_sets(const uint64_t *__res
             continue;
         }
         const int m = (int)(e - a);
-        int P = 1;
-        while (P < m) P <<= 1;
+        const int P = sort_width(m);
         if (tid == 0) bad = 0;
         __syncthreads();
         for (int i = tid; i < P; i += SEG_THREADS) {
@@ -190,20 +277,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_sort_sets(const uint64_t *__res
             __syncthreads();
             continue;
         }
-        for (int k = 2; k <= P; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int t = tid; t < (P >> 1); t += SEG_THREADS) {
-                    const int i = 2 * j * (t / j) + (t % j), l = i + j;    // pair (i, l), i < l
-                    const bool up = (i & k) == 0;                         // ascending run
-                    const uint64_t x = b[i], y = b[l];
-                    if ((x > y) == up) {
-                        b[i] = y;
-                        b[l] = x;
-                    }
-                }
-                __syncthreads();
-            }
-        }
+        block_sort<SEG_MAX>(b, P);
         for (int i = tid; i < m; i += SEG_THREADS) out[a + i] = b[i];
         __syncthreads();      // b is refilled for the next set
     }
@@ -219,7 +293,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_prep(const uint64_t *__re
     __shared__ uint32_t h[SORT_MAX_PASSES][RADIX];
     const int tid = threadIdx.x;
     const int64_t count = *cnt_ptr;
-    if (count <= SORT_SMALL) return;
+    if (count <= sort_small(seg_fallback)) return;
     if (seg_fallback && *seg_fallback == 0) return;    // k_sort_sets has sorted every set
     constexpr int U = 8, STEP = SORT_THREADS * U;
     if ((int64_t)blockIdx.x * STEP >= count) return;
@@ -384,7 +458,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(const uint64_t *__re
     __shared__ SortLds L;
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const int64_t count = *cnt_ptr;
-    if (count <= SORT_SMALL) return;     // k_sort_small has sorted them
+    if (count <= sort_small(seg_fallback)) return;     // k_sort_small has sorted them
     if (seg_fallback && *seg_fallback == 0) return;    // k_sort_sets has sorted every set
     const int64_t tiles = sort_tiles(count), tile = sort_tile(count);
     if ((int64_t)blockIdx.x >= tiles) return;
@@ -438,7 +512,7 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
     constexpr int TW = TIE_TILE + TIE_SHORT + 2;
     __shared__ uint64_t k[TW];                   // k[j]: key base - 1 + j
     const int64_t n = *cnt_ptr;
-    if (n <= SORT_SMALL) return;
+    if (n <= sort_small(seg_fallback)) return;
     if (seg_fallback && *seg_fallback == 0) return;
     const int tid = threadIdx.x;
     for (int64_t base = (int64_t)blockIdx.x * TIE_TILE; base < n; base += (int64_t)gridDim.x * TIE_TILE) {
@@ -497,7 +571,7 @@ __global__ __launch_bounds__(TIE_THREADS) void k_sort_long(uint64_t *__restrict_
     __shared__ unsigned long long lo, hi;
     __shared__ bool last;
     const int64_t n = *cnt_ptr;
-    if (n <= SORT_SMALL) return;
+    if (n <= sort_small(seg_fallback)) return;
     if (seg_fallback && *seg_fallback == 0) return;
     const int tid = threadIdx.x, lane = lane_id();
     // lowest and highest of keys a + t, a + t + step, ... below e, over a wave
