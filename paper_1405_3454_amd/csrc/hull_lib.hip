@@ -680,7 +680,7 @@ static int run_sort(hull_ctx *ctx, const Plan &p, hipStream_t st, const uint64_t
         in = out;
         out = (out == A) ? B : A;
     }
-    if (first == Y_DIGITS) {                   // `out` is free: it lists the long runs (17 keys or more each)
+    if (first == Y_DIGITS) {                   // `out` is free: it lists the long runs (over TIE_SHORT keys each)
         auto *runs = reinterpret_cast<LongRun *>(out);
         uint64_t *keys_s = in == A ? A : B;
         LAUNCH(K_SORT_SCATTER, k_sort_ties<<<(unsigned)std::min<int64_t>((int64_t)ctx->cus * 8, ncap / TIE_TILE + 1),

@@ -486,10 +486,16 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(const uint64_t *__re
     }
 }
 
-// Runs of equal (set, x) in keys sorted by (set, x): a run of up to TIE_SHORT
-// keys is sorted where it lies by the thread at its head; a longer one is
-// listed for k_sort_long.
-constexpr int TIE_SHORT = 16;
+// Runs of equal (set, x) in keys sorted by (set, x).  The chains need of a run
+// its lowest and its highest key, so it becomes its lowest key, copies of it,
+// and its highest: a run of up to TIE_SHORT keys in LDS by the thread at its
+// head, a longer one by k_sort_long, which finds it in a list.  A list entry
+// is an atomic on one counter, about 9 ns each, so few runs may need one: with
+// 2^27 clamped normal points (about 30 keys a run) and runs of up to 16 sorted
+// by their threads and longer ones listed this took 38.1 ms, now 1.2; with
+// 2^27 points of a square (8 a run) 5.7 ms, now 0.9.
+constexpr int TIE_SHORT = 256;
+constexpr int TIE_STEP = 4;              // keys read together along a run
 constexpr int64_t TIE_WAVE = 1 << 12, TIE_BLOCK = 1 << 18;
 struct LongRun {
     int64_t a, e;                        // keys [a, e)
@@ -501,15 +507,17 @@ __device__ __forceinline__ LongRun *tie_list(LongRun *runs, int64_t n, int kind)
     return runs + (kind == 2 ? 0 : kind == 1 ? all : all + block);
 }
 
-// A block takes TIE_TILE keys through LDS (with the key before and the
-// TIE_SHORT after them); the runs that start in the tile are its own.
+// A block takes TIE_TILE keys through LDS (with the key before and those
+// after them); the runs that start in the tile are its own, and it writes
+// back what it changed.  Blocks compare only the (set, x) of keys that are not
+// theirs, which every order of a run keeps.
 constexpr int TIE_TILE = 2048;
 
 __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
                                                    const int64_t *__restrict__ cnt_ptr,
                                                    SortState *__restrict__ state, LongRun *__restrict__ runs,
                                                    const int *__restrict__ seg_fallback) {
-    constexpr int TW = TIE_TILE + TIE_SHORT + 2;
+    constexpr int TW = TIE_TILE + TIE_SHORT + TIE_STEP + 1;
     __shared__ uint64_t k[TW];                   // k[j]: key base - 1 + j
     const int64_t n = *cnt_ptr;
     if (n <= sort_small(seg_fallback)) return;
@@ -532,19 +540,28 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
             const int j = t + 1;
             const uint64_t g = k[j] >> (8 * Y_DIGITS);
             if ((k[j + 1] >> (8 * Y_DIGITS)) != g || (k[j - 1] >> (8 * Y_DIGITS)) == g) continue;
-            int len = 2;
-            while (len <= TIE_SHORT && (k[j + len] >> (8 * Y_DIGITS)) == g) len++;
+            constexpr uint32_t Y = (1u << (8 * Y_DIGITS)) - 1;
+            uint32_t ylo = (uint32_t)k[j] & Y, yhi = ylo;
+            int len = 1;
+            for (bool more = true; more;) {
+                uint64_t c[TIE_STEP];
+#pragma unroll
+                for (int u = 0; u < TIE_STEP; u++) c[u] = k[j + len + u];
+#pragma unroll
+                for (int u = 0; u < TIE_STEP; u++) {
+                    more = more & ((c[u] >> (8 * Y_DIGITS)) == g);
+                    const uint32_t y = (uint32_t)c[u] & Y;
+                    ylo = more ? min(ylo, y) : ylo;
+                    yhi = more ? max(yhi, y) : yhi;
+                    len += more;
+                }
+                more = more & (len <= TIE_SHORT);
+            }
             const int64_t i = base + t;
             if (len <= TIE_SHORT) {
-                // sorted in LDS and in the list (other threads compare only
-                // the keys' (set, x), which every order of the run keeps)
-                for (int q = 1; q < len; q++) {
-                    const uint64_t c = k[j + q];
-                    int p = q;
-                    for (; p > 0 && k[j + p - 1] > c; p--) k[j + p] = k[j + p - 1];
-                    k[j + p] = c;
-                }
-                for (int q = 0; q < len; q++) keys[i + q] = k[j + q];
+                const uint64_t low = g << (8 * Y_DIGITS) | ylo;
+                for (int q = 0; q < len - 1; q++) k[j + q] = low;
+                k[j + len - 1] = g << (8 * Y_DIGITS) | yhi;
             } else {
                 int64_t lo = i + len, hi = n;        // the first key past the run
                 while (lo < hi) {
@@ -554,6 +571,12 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
                 const int kind = lo - i > TIE_BLOCK ? 2 : lo - i > TIE_WAVE ? 1 : 0;
                 tie_list(runs, n, kind)[atomicAdd(&state->nlong[kind], 1u)] = LongRun{i, lo, ~0ull, 0ull};
             }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int t = tid + u * 256;
+            if (t < TW && k[t] != v[u]) keys[base - 1 + t] = k[t];
         }
     }
 }

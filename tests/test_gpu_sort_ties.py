@@ -1,5 +1,5 @@
 """The sort of the hull stage by (set, x) where runs of equal x change hands:
-runs of up to 16 keys (a thread), up to 4096 (a wave), up to 2^18 (a block),
+runs of up to 256 keys (a thread), up to 4096 (a wave), up to 2^18 (a block),
 longer (every block), mixed with distinct x, at counts below and above the
 tile sizes.  All points go to the sort (no filter), and the hull is compared
 with the oracle's.
@@ -29,6 +29,7 @@ def _columns(runs, seed):
 
 CASES = [
     [(1, 4097)], [(16, 300), (17, 300)], [(4096, 3), (4097, 3), (1, 5000)], [(40000, 2), (2, 40000), (1, 1000)],
+    [(255, 70), (256, 70), (257, 70), (258, 70)], [(30, 3000), (2, 9)],
     [(1 << 18, 1), ((1 << 18) + 1, 2), (300000, 1), (5, 5000)], [(700001, 1)], [(1, 20000), (3, 2500), (100, 20)],
 ]
 
