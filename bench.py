@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC = {"discard": 4.7449e9, "extremes": 4.3306e9}
 TRAFFIC_SOURCES = ("paper_1405_3454_amd/csrc/k_filter.hip", "paper_1405_3454_amd/csrc/hg_common.h",
                    "paper_1405_3454_amd/csrc/hg_device.h")
-TRAFFIC_SHA = "74a25708c58cdbde"
+TRAFFIC_SHA = "ce8f5f958a275c93"
 
 
 def _traffic(kernel, log2n):

@@ -93,14 +93,13 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         const int64_t *tile_off = W<int64_t>(p, p.tile_off);
         if ((rc = run_scan(ctx, p, st, W<uint32_t>(p, p.tile_cnt), tile_off + 1, W<int64_t>(p, p.tile_pos))))
             return rc;
-        LAUNCH(K_SCATTER, k_set_offsets<<<1, 256, 0, st>>>(tile_off, W<int64_t>(p, p.tile_pos), 1, so));
+        LAUNCH(K_SCATTER, k_set_offsets<<<1, 256, 0, st>>>(tile_off, W<int64_t>(p, p.tile_pos), 1, so, scount));
         uint64_t *nokeys = nullptr;
         const int64_t *nobase = nullptr;
         LAUNCH(K_SCATTER, k_scatter<<<gd, 256, 0, st>>>(x, y, n, phase_of(x), nullptr, 1, tile_off,
                                                         W<int32_t>(p, p.tile_set), W<uint64_t>(p, p.masks),
                                                         W<uint32_t>(p, p.tile_cnt), W<int64_t>(p, p.tile_pos),
                                                         sv, nokeys, nobase, INT64_MAX));
-        LAUNCH(K_MISC, k_copy_count<<<1, 64, 0, st>>>(so + 1, scount));
     } else {
         LAUNCH(K_MISC, k3_iota<<<1024, 256, 0, st>>>(sv, n));
         LAUNCH(K_MISC, k_fill_i64<<<1, 64, 0, st>>>(scount, 1, n));

@@ -458,12 +458,18 @@ static int run_validate(hull_ctx *ctx, const Plan &p, hipStream_t st, const floa
 }
 
 static int run_tilemap(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x,
-                       const int64_t *off, int64_t n1, int64_t S) {
+                       const int64_t *off, int64_t n1, int64_t S, int64_t *counts = nullptr,
+                       unsigned long long *clr = nullptr) {
     int64_t *tile_off = W<int64_t>(p, p.tile_off);
+    const unsigned nb = (unsigned)std::min<int64_t>(ctx->cus * 4, (p.tcap + 255) / 256);
+    if (S == 1) {
+        LAUNCH(K_TILEMAP, k_tile_one<<<nb, 256, 0, st>>>(off, n1, TILE, phase_of(x), tile_off, W<int32_t>(p, p.tile_set),
+                                                         W<uint32_t>(p, p.pticket), counts, HULL_NCOUNTS, clr, RE_CAP));
+        return HULL_OK;
+    }
     LAUNCH(K_TILEMAP, k_tile_offsets<<<1, 1024, 0, st>>>(off, n1, S, TILE, phase_of(x), tile_off,
                                                          W<uint32_t>(p, p.pticket)));
-    LAUNCH(K_TILEMAP, k_tile_sets<<<(unsigned)std::min<int64_t>(ctx->cus * 4, (p.tcap + 255) / 256), 256,
-                                     0, st>>>(tile_off, S, W<int32_t>(p, p.tile_set)));
+    LAUNCH(K_TILEMAP, k_tile_sets<<<nb, 256, 0, st>>>(tile_off, S, W<int32_t>(p, p.tile_set)));
     return HULL_OK;
 }
 
@@ -547,6 +553,7 @@ static int run_polygon(hull_ctx *ctx, const Plan &p, hipStream_t st, const float
     default: return HULL_EINVAL;
     }
 #undef K2
+    if (slots_out) return HULL_OK;      // the slots are the result: no discard pass reads the rows
     // row-group blocks per set: all 16 for a few sets, one for thousands
     const unsigned ny = (unsigned)std::max<int64_t>(1, std::min<int64_t>(SPAN_ROWS / ROWS_PER_BLOCK,
                                                                          (2 * ctx->cus + S - 1) / S));
@@ -561,7 +568,7 @@ static int run_polygon(hull_ctx *ctx, const Plan &p, hipStream_t st, const float
 static int run_discard(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x,
                        const float *y, int64_t n_total, const int64_t *off, int64_t n1,
                        int64_t S, int nedge, uint32_t *surv, int64_t *surv_off, uint64_t *keys,
-                       const int64_t *out_base = nullptr, int64_t cap = INT64_MAX) {
+                       const int64_t *out_base = nullptr, int64_t cap = INT64_MAX, int64_t *total = nullptr) {
     const int64_t *tile_off = W<int64_t>(p, p.tile_off);
     const int32_t *tile_set = W<int32_t>(p, p.tile_set);
     auto *polys = W<Poly>(p, p.polys);
@@ -588,7 +595,7 @@ static int run_discard(hull_ctx *ctx, const Plan &p, hipStream_t st, const float
     int rc = run_scan(ctx, p, st, tcnt, tile_off + S, tpos);
     if (rc) return rc;
     LAUNCH(K_SCATTER, k_set_offsets<<<(unsigned)((S + 256) / 256), 256, 0, st>>>(tile_off, tpos, S,
-                                                                                  surv_off));
+                                                                                  surv_off, total));
     LAUNCH(K_SCATTER, k_scatter<<<g, 256, 0, st>>>(x, y, n_total, phase_of(x), off, S, tile_off, tile_set, masks, tcnt,
                                                    tpos, surv, keys, out_base, cap));
     return HULL_OK;
@@ -932,14 +939,15 @@ static int run_compute(hull_ctx *ctx, hipStream_t st, const float *x, const floa
                          h_out);
     // one set: the farthest keys of refinement round 0's children start cleared
     const bool one_ref = S == 1 && refine;
-    LAUNCH(K_MISC, k_counts_init<<<1, 64, 0, st>>>(
-        ctx->counts, HULL_NCOUNTS, one_ref ? W<unsigned long long>(p, p.rfar1) : nullptr, RE_CAP));
+    unsigned long long *clr = one_ref ? W<unsigned long long>(p, p.rfar1) : nullptr;
+    if (S > 1 || flags & HULL_NOFILTER)     // else run_tilemap's one launch does it
+        LAUNCH(K_MISC, k_counts_init<<<1, 64, 0, st>>>(ctx->counts, HULL_NCOUNTS, clr, RE_CAP));
     if (flags & HULL_NOFILTER) {
         LAUNCH(K_KEYS, k_all_keys<<<2048, 256, 0, st>>>(x, y, off, n1, S, n_total, surv, keys,
                                                          surv_off));
         LAUNCH(K_MISC, k_copy_count<<<1, 64, 0, st>>>(surv_off + S, ctx->counts));
     } else {
-        if ((rc = run_tilemap(ctx, p, st, x, off, n1, S))) return rc;
+        if ((rc = run_tilemap(ctx, p, st, x, off, n1, S, ctx->counts, clr))) return rc;
         if (learned) {
             rc = run_learned_dirs(ctx, p, st, x, y, n_total, off, n1, S);
             if (rc) return rc;
@@ -1155,10 +1163,7 @@ int hull_discard(hull_ctx *ctx, const float *x, const float *y, int64_t n, const
     if ((rc = run_tilemap(ctx, p, st, x, nullptr, n, 1))) return rc;
     if ((rc = run_polygon(ctx, p, st, x, y, n, 1, false, slots, n_slots, nullptr, nullptr))) return rc;
     int64_t *so = W<int64_t>(p, p.surv_off);
-    if ((rc = run_discard(ctx, p, st, x, y, n, nullptr, n, 1, n_slots, surv, so, nullptr)))
-        return rc;
-    LAUNCH(K_MISC, k_copy_count<<<1, 64, 0, st>>>(so + 1, n_surv));
-    return HULL_OK;
+    return run_discard(ctx, p, st, x, y, n, nullptr, n, 1, n_slots, surv, so, nullptr, nullptr, INT64_MAX, n_surv);
 }
 
 int hull_of_subset(hull_ctx *ctx, const float *x, const float *y, int64_t n, const uint32_t *idx,
