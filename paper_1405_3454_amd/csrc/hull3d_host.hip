@@ -171,8 +171,8 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         LAUNCH(K_MISC, k3_ctl_init<<<1, 64, 0, st>>>(C, (int)fcap));
         const unsigned gs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ctx->cus * 4, (nc + 255) / 256));
         for (int phase = 1; phase <= 3; phase++)
-            LAUNCH(K_MISC, k3_seed<<<gs, 256, 0, st>>>(x, y, z, cidx, nc, phase, C));
-        LAUNCH(K_MISC, k3_start<<<1, 64, 0, st>>>(x, y, z, cidx, nc, C, faces, planes, far));
+            LAUNCH(K_MISC, k3_seed<<<gs, 256, 0, st>>>(x, y, z, sv, cidx, nc, phase, C));
+        LAUNCH(K_MISC, k3_start<<<1, 64, 0, st>>>(x, y, z, sv, nc, C, faces, planes, far));
         Hull3Ctl hc;
         HIPCHECK(hipMemcpyAsync(&hc, C, sizeof(hc), hipMemcpyDeviceToHost, st));
         HIPCHECK(hipStreamSynchronize(st));

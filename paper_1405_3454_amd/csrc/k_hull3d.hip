@@ -625,16 +625,18 @@ __device__ __forceinline__ unsigned long long key_of(double d, uint32_t i) {
 
 // Start, phase 1..3: candidate farthest from p0 / from line p0 p1 / from the
 // plane p0 p1 p2, by atomic maximum of (distance estimate, ~index); a
-// distance that is exactly zero gives key 0.
+// distance that is exactly zero gives key 0.  p0 is the first survivor, the
+// lowest index among the copies of its point, which the candidates' order
+// (any, after the star reduction) does not tell.
 __global__ __launch_bounds__(256) void k3_seed(const float *__restrict__ x, const float *__restrict__ y,
-                                               const float *__restrict__ z, const uint32_t *__restrict__ cand,
-                                               int64_t nc, int phase, Hull3Ctl *__restrict__ C) {
+                                               const float *__restrict__ z, const uint32_t *__restrict__ first,
+                                               const uint32_t *__restrict__ cand, int64_t nc, int phase,
+                                               Hull3Ctl *__restrict__ C) {
     if (nc <= 0) return;
     // a phase runs only when the one before found a point
     if (phase >= 2 && C->seed[0] == 0) return;
     if (phase >= 3 && C->seed[1] == 0) return;
-    const uint32_t i0 = cand[0];
-    const I3 a = grid3(x, y, z, i0);
+    const I3 a = grid3(x, y, z, first[0]);
     I3 b{0, 0, 0}, c{0, 0, 0};
     if (phase >= 2) b = grid3(x, y, z, (uint32_t)~(uint32_t)C->seed[0]);
     if (phase >= 3) c = grid3(x, y, z, (uint32_t)~(uint32_t)C->seed[1]);
@@ -697,7 +699,7 @@ __device__ __forceinline__ void face_plane(const float *x, const float *y, const
 
 // The start simplex (or the kind of degenerate set), one thread.
 __global__ void k3_start(const float *__restrict__ x, const float *__restrict__ y, const float *__restrict__ z,
-                         const uint32_t *__restrict__ cand, int64_t nc, Hull3Ctl *__restrict__ C,
+                         const uint32_t *__restrict__ first, int64_t nc, Hull3Ctl *__restrict__ C,
                          Face3 *__restrict__ faces, Plane3 *__restrict__ planes,
                          unsigned long long *__restrict__ far) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
@@ -710,7 +712,7 @@ __global__ void k3_start(const float *__restrict__ x, const float *__restrict__ 
     C->nlist[1] = 0;
     C->npair = 0;
     if (nc <= 0) { C->state = 4; return; }
-    C->p[0] = cand[0];
+    C->p[0] = first[0];
     if (!C->seed[0]) { C->state = 3; return; }
     C->p[1] = ~(uint32_t)C->seed[0];
     if (!C->seed[1]) {
