@@ -236,6 +236,12 @@ int hull_compute_host(hull_ctx *ctx, const float *x, const float *y, int64_t n,
 int hull3_compute(hull_ctx *ctx, const float *x, const float *y, const float *z, int64_t n,
                   uint32_t *slots, uint32_t *surv, int64_t *n_surv, uint32_t *hull, int64_t *h,
                   int flags, void *stream);
+/* Faces that hull3_compute's hull stage of this context first has room for
+ * (4 .. 2^28); 0, the default: eight per candidate and 1024 more, at most
+ * 2^24.  A stage that makes more starts again with twice the room, up to 2^29,
+ * beyond which the call gives HULL_ENOMEM.  No value changes any result.
+ * HULL_EINVAL outside the range. */
+int hull3_face_room(hull_ctx *ctx, int64_t faces);
 
 /* ---- batched forms (many sets, CSR offsets) ----------------------------
  * S: 1 .. 65535 sets.

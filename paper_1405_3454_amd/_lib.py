@@ -66,6 +66,7 @@ SIGNATURES = {
     "hull_compute": (I, [P, P, P, I64, P, P, I, P]),
     "hull_compute_host": (I, [P, P, P, I64, I64, I64, P, P, P, I64, P, P, I, P]),
     "hull3_compute": (I, [P, P, P, P, I64, P, P, P, P, P, I, P]),
+    "hull3_face_room": (I, [P, I64]),
     "hull_extremes_batched": (I, [P, P, P, P, I64, I64, P, I, P]),
     "hull_discard_batched": (I, [P, P, P, P, I64, I64, P, I, P, P, P]),
     "hull_compute_batched": (I, [P, P, P, P, I64, I64, P, P, I, P]),

@@ -39,6 +39,12 @@ static int grow(char **p, size_t *cap, size_t want) {
     return HULL_OK;
 }
 
+extern "C" int hull3_face_room(hull_ctx *ctx, int64_t faces) {
+    if (!ctx || faces < 0 || (faces > 0 && faces < 4) || faces > (int64_t(1) << 28)) return HULL_EINVAL;
+    ctx->face_room = faces;
+    return HULL_OK;
+}
+
 extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, const float *z, int64_t n,
                              uint32_t *slots, uint32_t *surv, int64_t *n_surv, uint32_t *hull,
                              int64_t *h, int flags, void *stream) {
@@ -134,7 +140,8 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         cpts = kept;
     }
     // The rounds, with face room grown and the hull restarted if it runs out
-    for (int64_t fcap = std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);; fcap *= 2) {
+    const int64_t room = ctx->face_room ? ctx->face_room : std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);
+    for (int64_t fcap = room;; fcap *= 2) {
         size_t ob = 0;
         auto tb = [&](size_t bytes) { size_t r = ob; ob += al(bytes); return r; };
         // a copy of the survivor list, which may lie in the workspace that the
@@ -210,7 +217,8 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
             // The host launches a round before it reads the status of the one
             // before it, so the GPU never waits for it (a synchronisation a
             // round left it idle for 30 us each); the last round launched
-            // finds no candidates.  Grids follow the last status read:
+            // finds no candidates, or that the one before ran out of faces,
+            // and does nothing.  Grids follow the last status read:
             // candidates only get fewer, and every kernel loops.
             int64_t cands = nc, nf = 4;
             int cur = 0;

@@ -104,6 +104,7 @@ struct hull_ctx {
     StreamBufs *sb = nullptr;
     // the 3D path's buffers
     Hull3Bufs *h3 = nullptr;
+    int64_t face_room = 0;      // of its hull stage; 0: from the candidates
 };
 
 // Slots of one set's extremes: the preset's fixed positions, then the

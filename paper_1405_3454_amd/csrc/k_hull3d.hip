@@ -615,6 +615,13 @@ struct Hull3Ctl {
     int64_t nrm[3];               // flat sets: their plane's normal
 };
 
+// An earlier launch ran out of face room (nfaces is then past fcap, and faces
+// below it may be unmade) or found the mesh open: the rounds that the host has
+// launched in the meantime leave everything as it is.
+__device__ __forceinline__ bool mesh_over(const Hull3Ctl *C) {
+    return __builtin_amdgcn_readfirstlane(C->overflow) != 0;
+}
+
 __device__ __forceinline__ double pdx(const float *v, uint32_t i) { return (double)truncf(v[i] * GRIDF); }
 
 // far key: distance estimate (non-negative float bits) above, ~index below
@@ -961,6 +968,7 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
                                                  const Plane3 *__restrict__ planes, const int2 *__restrict__ repl,
                                                  unsigned long long *__restrict__ far, int round) {
     __shared__ int bcnt, bbase;
+    if (mesh_over(C)) return;
     const int64_t nc = C->nlist[round & 1];
     const bool first = round == 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) C->npair = 0;      // for k3_pick
@@ -1100,6 +1108,7 @@ constexpr int INS_PASSES = 4;       // claim-and-insert passes per assignment
 // Round start: the proposals.  Clears far[] for the next assignment.
 __global__ __launch_bounds__(256) void k3_pick(Hull3Ctl *__restrict__ C, unsigned long long *__restrict__ far,
                                                Pair3 *__restrict__ pairs, int round) {
+    if (mesh_over(C)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         C->inserted = 0;
         C->nlist[round & 1] = 0;      // read by this round's assignment, filled by the next one's
@@ -1148,6 +1157,7 @@ __global__ __launch_bounds__(64) void k3_visible(const float *__restrict__ x, co
     __shared__ int vl[PV_CAP];
     __shared__ int hl[PV_CAP];
     __shared__ int tmp[WAVE];
+    if (mesh_over(C)) return;
     const int lane = threadIdx.x;
     const int np = min(C->npair, PAIR_CAP);
     for (int p = blockIdx.x; p < np; p += gridDim.x) {
@@ -1225,6 +1235,7 @@ __global__ __launch_bounds__(64) void k3_apply(const float *__restrict__ x, cons
                                                const unsigned long long *__restrict__ claim_out, int stamp) {
     __shared__ int ha[PV_CAP], hb[PV_CAP], ho[PV_CAP];
     __shared__ int base;
+    if (mesh_over(C)) return;
     const int lane = threadIdx.x;
     const int np = min(C->npair, PAIR_CAP);
     const int fcap = C->fcap;
@@ -1318,6 +1329,7 @@ __global__ __launch_bounds__(INS_THREADS) void k3_insert(const float *__restrict
     __shared__ int hz_f[HZ_CAP], hz_e[HZ_CAP];
     __shared__ int vlist[VIS_CAP];
     __shared__ int front[2][VIS_CAP];
+    if (mesh_over(C)) return;
     const int tid = threadIdx.x;
     if (tid == 0) {
         nl = 0;
