@@ -157,7 +157,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         char *hb = B->b;
         if (!cpts) {
             uint32_t *copy = reinterpret_cast<uint32_t *>(hb + b_idx);
-            if (nc > 0 && cidx != copy) HIPCHECK(hipMemcpyAsync(copy, sv, nc * 4, hipMemcpyDeviceToDevice, st));
+            if (nc > 0) HIPCHECK(hipMemcpyAsync(copy, sv, nc * 4, hipMemcpyDeviceToDevice, st));
             cidx = copy;
         }
         float4 *cand[2] = {reinterpret_cast<float4 *>(hb + b_ca), reinterpret_cast<float4 *>(hb + b_cb)};

@@ -44,3 +44,11 @@ def check(n, every, room, **kw):
 @pytest.mark.parametrize("room", [4, 500, 4000, 12000])
 def test_reduced(room, serial):
     check(120000, 40, room, serial=serial)
+
+
+# fewer survivors, and no filter: the rounds start from the survivor list,
+# which every turn copies anew
+@pytest.mark.parametrize("kw", [{}, {"nofilter": True}, {"nofilter": True, "serial": True}])
+@pytest.mark.parametrize("room", [4, 3000])
+def test_from_the_list(room, kw):
+    check(20000, 10, room, **kw)
