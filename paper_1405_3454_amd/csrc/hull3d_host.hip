@@ -4,11 +4,11 @@
 // sets) are the 2D path's.
 
 // Device buffers of the 3D path, owned by the context and grown on demand:
-// A holds what the filter passes need, S the candidates' reduction before the
-// rounds, B the hull stage (each sized once its count is known).
+// A holds what the filter passes need, B the hull stage (sized once the
+// candidates' count is known).
 struct Hull3Bufs {
-    char *a = nullptr, *b = nullptr, *s = nullptr;
-    size_t acap = 0, bcap = 0, scap = 0;
+    char *a = nullptr, *b = nullptr;
+    size_t acap = 0, bcap = 0;
     // the rounds' status as the host reads it, one round behind
     Hull3Ctl *seen = nullptr;            // two, pinned
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -18,7 +18,6 @@ static void hull3_free(Hull3Bufs *h) {
     if (!h) return;
     if (h->a) (void)hipFree(h->a);
     if (h->b) (void)hipFree(h->b);
-    if (h->s) (void)hipFree(h->s);
     if (h->seen) (void)hipHostFree(h->seen);
     for (hipEvent_t e : h->ev)
         if (e) (void)hipEventDestroy(e);
@@ -119,25 +118,26 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
     const uint32_t *cidx = sv;               // the candidates' indices
     const float4 *cpts = nullptr;            // and coordinates, where they are at hand
     if (!nofilter && nc >= STAR_MIN) {
+        // in the workspace, whose chain lists and candidate lists (16 bytes a
+        // point twice, 4, and 8 for the cells) are idle until the final sort
         const int side = star_side(nc), ncell = star_cells(side);
-        size_t os = 0;
-        auto ts = [&](size_t bytes) { size_t r = os; os += al(bytes); return r; };
-        const size_t s_pts = ts(nc * 16), s_out = ts(nc * 16), s_idx = ts(nc * 4), s_cell = ts((ncell + 1) * 8),
-                     s_tab = ts(ncell * 16);
-        if ((rc = grow(&B->s, &B->scap, os))) return rc;
-        float4 *pts = reinterpret_cast<float4 *>(B->s + s_pts), *kept = reinterpret_cast<float4 *>(B->s + s_out);
-        uint32_t *kidx = reinterpret_cast<uint32_t *>(B->s + s_idx);
-        auto *cells = reinterpret_cast<unsigned long long *>(B->s + s_cell);     // then the kept count
-        float4 *tab = reinterpret_cast<float4 *>(B->s + s_tab);
+        float4 *pts = W<float4>(p, p.lo0), *kept = W<float4>(p, p.lo1);
+        uint32_t *kidx = W<uint32_t>(p, p.cidx);
+        auto *cells = W<unsigned long long>(p, p.ckeys);     // then the kept count, then the far points
+        float4 *tab = reinterpret_cast<float4 *>(cells + (ncell + 2) / 2 * 2);
         const unsigned gq = (unsigned)std::min<int64_t>(ctx->cus * 8, (nc + 255) / 256);
         LAUNCH(K_MISC, k_fill_i64<<<64, 256, 0, st>>>(reinterpret_cast<int64_t *>(cells), ncell + 1, 0));
         LAUNCH(K_REFINE, k3_star_far<<<gq, 256, 0, st>>>(x, y, z, sv, nc, poly, side, cells, pts));
         LAUNCH(K_REFINE, k3_star_table<<<(ncell + 255) / 256, 256, 0, st>>>(cells, ncell, pts, tab));
         LAUNCH(K_REFINE, k3_star_keep<<<gq, 256, 0, st>>>(pts, nc, poly, side, tab, kept, kidx, cells + ncell));
-        HIPCHECK(hipMemcpyAsync(&nc, cells + ncell, 8, hipMemcpyDeviceToHost, st));
+        int64_t nk = 0;
+        HIPCHECK(hipMemcpyAsync(&nk, cells + ncell, 8, hipMemcpyDeviceToHost, st));
         HIPCHECK(hipStreamSynchronize(st));
-        cidx = kidx;
-        cpts = kept;
+        if (nk < nc) {                       // (a set without an interior keeps all of them)
+            nc = nk;
+            cidx = kidx;
+            cpts = kept;
+        }
     }
     // The rounds, with face room grown and the hull restarted if it runs out
     const int64_t room = ctx->face_room ? ctx->face_room : std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);
@@ -191,8 +191,10 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
             LAUNCH(K_MISC, k3_small_out<<<1, 64, 0, st>>>(C, hull, h));
             return HULL_OK;
         }
-        Plan ph;
-        if ((rc = prepare(ctx, std::max<int64_t>(nc, 1), 1, st, &ph))) return rc;
+        // the candidates' plan in the same workspace, which it cannot outgrow:
+        // what the survivor and candidate lists hold stays until it is used
+        Plan ph = make_plan(std::max<int64_t>(nc, 1), 1, p.nwave);
+        ph.base = p.base;
         int64_t *hcount = W<int64_t>(ph, ph.hoff) + 1;      // count slot for the sort
         const uint64_t *sorted = nullptr;
         if (hc.state == 1) {
