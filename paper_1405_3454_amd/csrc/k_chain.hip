@@ -9,10 +9,9 @@
 //     goes while it does not make a strict turn, so collinear points go).
 //  2. k_chain_merge: one wave per group of CHAIN_G neighbouring chains joins
 //     them: at the first level the chains side by side are pruned like a
-//     chunk (below); above it they are joined left to right, the tail of the
-//     chain built so far and the head of the next one walked to their common
-//     tangent (the bridge) at each junction.  Repeated until one chain per
-//     kind is left.
+//     chunk (below); above it the tail of one chain and the head of the next
+//     are walked to their common tangent (the bridge) at each junction.
+//     Repeated until one chain per kind is left.
 //  3. Per set: the lower chain followed by the upper chain's interior in
 //     reverse gives the counter-clockwise hull from the lexicographic
 //     minimum; each hull key is mapped back to the lowest point index with
@@ -60,7 +59,6 @@ __device__ __forceinline__ bool drop_mid(uint64_t a, uint64_t b, uint64_t c) {
 constexpr uint32_t YMIN_ID = 0x7fffffffu;   // identity of min over y < 2^24
 constexpr int32_t YMAX_ID = -1;
 constexpr int PRUNE_PASSES = 24;
-constexpr int JOIN_PASSES = 256;            // a join of long chains: a pass per point walked back
 
 struct Chain0Lds {
     uint64_t list[2][2][CHAIN_C];   // [lower, upper][ping-pong]
@@ -305,10 +303,13 @@ __device__ __forceinline__ int64_t last_seg_start(P src, int64_t lo, int64_t hi)
 // Walk the junction of the chain built so far (o[0..len), its last set
 // segment starting at tailseg) with the next chain c[0..m) to their common
 // tangent.  Returns the new length of o and sets *bstart to the first
-// element of c to append.
+// element of c to append.  Called by a whole wave, whose lanes test the next
+// 64 points of a walk together: a long arc that one later point cuts off is
+// walked back at 64 points a step.
 template <bool UPPER, typename PO, typename PC>
 __device__ __forceinline__ int64_t bridge(PO o, int64_t len, int64_t tailseg, PC c, int64_t m,
                                           int64_t *bstart) {
+    const int lane = lane_id();
     int64_t b = 0;
     if (len > 0) {
         uint64_t last = o[len - 1];
@@ -318,14 +319,18 @@ __device__ __forceinline__ int64_t bridge(PO o, int64_t len, int64_t tailseg, PC
             bool changed = true;
             while (changed) {
                 changed = false;
-                while (a > tailseg && drop_mid<UPPER>(o[a - 1], o[a], c[b])) {
-                    a--;
-                    changed = true;
+                for (int k = WAVE; k == WAVE; a -= k) {
+                    const int64_t i = a - lane;
+                    const uint64_t d = __ballot(i > tailseg && drop_mid<UPPER>(o[i - 1], o[i], c[b]));
+                    k = ~d ? __builtin_ctzll(~d) : WAVE;
+                    changed |= k > 0;
                 }
-                while (b + 1 < m && key_set(c[b + 1]) == key_set(c[b]) &&
-                       drop_mid<UPPER>(o[a], c[b], c[b + 1])) {
-                    b++;
-                    changed = true;
+                for (int k = WAVE; k == WAVE; b += k) {
+                    const int64_t i = b + lane;
+                    const uint64_t d = __ballot(i + 1 < m && key_set(c[i + 1]) == key_set(c[i]) &&
+                                                drop_mid<UPPER>(o[a], c[i], c[i + 1]));
+                    k = ~d ? __builtin_ctzll(~d) : WAVE;
+                    changed |= k > 0;
                 }
             }
             len = a + 1;
@@ -335,10 +340,64 @@ __device__ __forceinline__ int64_t bridge(PO o, int64_t len, int64_t tailseg, PC
     return len;
 }
 
+// Join of chains that lie one after another in LDS, by one wave, in place:
+// chain g (g < np <= 64) at buf + g * per, its length in lane g's mine.
+template <bool UPPER>
+__device__ int join_pieces(uint64_t *buf, int per, int np, int mine) {
+    int64_t len = 0, tailseg = 0;
+    for (int g = 0; g < np; g++) {
+        const int64_t m = __shfl(mine, g);
+        const uint64_t *c = buf + g * per;
+        if (m == 0) continue;
+        int64_t b;
+        len = bridge<UPPER>(buf, len, tailseg, c, m, &b);
+        if (b == m) continue;
+        const int64_t ls = last_seg_start(c, b, m);
+        if (ls > b) tailseg = len + (ls - b);
+        else if (len == 0 || key_set(buf[len - 1]) != key_set(c[b])) tailseg = len;
+        for (int64_t i0 = b; i0 < m; i0 += WAVE) {      // moved down: len <= g * per + b
+            const int64_t i = i0 + lane_id();
+            const uint64_t v = i < m ? c[i] : 0;
+            wave_sync();
+            if (i < m) buf[len + i - b] = v;
+            wave_sync();
+        }
+        len += m - b;
+    }
+    return (int)len;
+}
+
+// Chain of the sorted list buf[0..n) in LDS by one wave, in place.  A pruning
+// pass shortens a list of pieces that nearly fit quickly, but takes an arc
+// that one later point cuts off back by one point only, so after PASSES of
+// them the rest is cut into pieces, a lane each, whose serial chains are
+// joined at their bridges.  (Unfiltered points of a parabola and a corner
+// below its end: 300 sets of 2000 took 3.5 ms with up to 256 passes and one
+// serial chain, now 0.55; one set of 8192 2.4 ms, now 0.5.)
+constexpr int PIECE_MIN = 32;
+
+template <bool UPPER, int U, int PASSES>
+__device__ int list_chain(uint64_t *buf, int n) {
+    const int lane = lane_id();
+    const uint64_t lt = lanemask_lt();
+    for (int pass = 0; pass < PASSES; pass++) {
+        const int n2 = prune_pass<UPPER, U>(buf, buf, n, lt);
+        const bool moved = n2 != n;
+        n = n2;
+        wave_sync();
+        if (!moved) return n;
+    }
+    const int per = max(PIECE_MIN, (n + WAVE - 1) / WAVE), b0 = min(n, lane * per);
+    const int mine = serial_chain<UPPER>(buf + b0, min(n, b0 + per) - b0);
+    wave_sync();
+    return join_pieces<UPPER>(buf, per, (n + per - 1) / per, mine);
+}
+
 // Merge of CHAIN_G neighbouring chains by one wave.  Groups that fit are
 // staged in LDS: at level 0 (many short chains) pruned in parallel (serial
-// chain only when the passes run out), above it (few long chains) joined by
-// serial bridge walks; larger groups walk the bridges in global memory.
+// chain only when the passes run out), above it (few long chains) all their
+// junctions walked at once, a lane each, or where that is not possible taken
+// as one list again; larger groups are joined in global memory.
 constexpr int MERGE_CAP = 4096;           // keys staged per wave (32 KB)
 
 // The group's ng chains side by side in buf (chain g of length m_g from
@@ -387,7 +446,7 @@ __device__ __forceinline__ void stage_group(const uint64_t *__restrict__ in, int
 // whose both junctions were walked is left with fewer than two points and
 // none is consumed, the joined chain is these pieces in order, the same as
 // the left-to-right join's, and it is written to o; otherwise returns false
-// (nothing written) and the caller joins left to right.
+// (nothing written).
 template <bool UPPER>
 __device__ bool parallel_join(const uint64_t *__restrict__ buf, const int64_t *__restrict__ goff,
                               int ng, int64_t mine, uint64_t *__restrict__ o, int64_t *len_out,
@@ -481,31 +540,13 @@ __device__ void merge_group(const uint64_t *__restrict__ in, const uint32_t *__r
         }
         len = M;
     } else if (M <= MERGE_CAP && lev > 0) {
-        // a few long chains (the upper levels): joined left to right in LDS,
-        // walking each junction to its bridge
+        // a few long chains (the upper levels)
         stage_group(in, R, u0, (int)min((int64_t)CHAIN_G, U - u0), incl, M, goff, buf);
         if (!parallel_join<UPPER>(buf, goff, (int)min((int64_t)CHAIN_G, U - u0), mine, o, &len, ne, pref,
                                   psrc)) {
             // chains that end up with fewer than two points (more chains than
-            // the hull has vertices): the list is pruned like a chunk.  (Joined
-            // left to right, one bridge after another, the 2^23 points' group
-            // took 172 us instead of 40.)
-            const uint64_t lt = lanemask_lt();
-            int n = (int)M;
-            bool moved = true;
-            for (int pass = 0; moved && pass < JOIN_PASSES; pass++) {
-                const int m2 = prune_pass<UPPER>(buf, buf, n, lt);
-                moved = m2 != n;
-                n = m2;
-                wave_sync();
-            }
-            if (moved) {
-                int h = 0;
-                if (lane == 0) h = serial_chain<UPPER>(buf, n);
-                wave_sync();
-                n = __builtin_amdgcn_readlane(h, 0);
-            }
-            len = n;
+            // the hull has vertices)
+            len = list_chain<UPPER, 4, 32>(buf, (int)M);
             for (int64_t i = lane; i < len; i += WAVE) o[i] = buf[i];
         }
     } else if (M <= MERGE_CAP) {
@@ -576,7 +617,7 @@ __device__ __forceinline__ void block_copy(const uint64_t *__restrict__ src, uin
 }
 
 // A group too large for one wave's LDS stage (or a single long chain), by
-// the whole block: thread 0 walks each junction to its bridge in global
+// the whole block: the first wave walks each junction to its bridge in global
 // memory, then every thread copies the next chain's remainder.
 // sh: 3 + 2 * CHAIN_G int64 of LDS.
 template <bool UPPER>
@@ -603,7 +644,7 @@ __device__ void merge_group_block(const uint64_t *__restrict__ in, const uint32_
         const int64_t m = gm[g];
         if (m == 0) continue;
         const uint64_t *src = in + (u0 + g) * R;
-        if (threadIdx.x == 0) {
+        if (threadIdx.x < WAVE) {
             int64_t b;
             const int64_t nl = bridge<UPPER>(o, len, tailseg, src, m, &b);
             int64_t nt = tailseg;
@@ -612,9 +653,11 @@ __device__ void merge_group_block(const uint64_t *__restrict__ in, const uint32_
                 if (ls > b) nt = nl + (ls - b);
                 else nt = (nl > 0 && key_set(o[nl - 1]) == key_set(src[b])) ? tailseg : nl;
             }
-            sh[0] = nl;
-            sh[1] = b;
-            sh[2] = nt;
+            if (threadIdx.x == 0) {
+                sh[0] = nl;
+                sh[1] = b;
+                sh[2] = nt;
+            }
         }
         __syncthreads();
         const int64_t nl = sh[0], b = sh[1], nt = sh[2];
@@ -720,8 +763,8 @@ __global__ __launch_bounds__(256) void k_chain_merge(const uint64_t *__restrict_
 // other sets.  The set's chain goes to out[start, start + len) and the rest
 // of its range is filled with SET_GAP keys (set field beyond every set), so
 // that out[0, cnt) lists every set's chain in set order.  The pieces are staged
-// in LDS and pruned together when the range fits, else joined left to right at
-// their bridges.
+// in LDS when the range fits and taken as one list, else joined left to right
+// at their bridges.
 constexpr uint64_t SET_GAP = ~0ull;
 
 // First index i in sorted[0, n) with set(sorted[i]) >= s.
@@ -794,25 +837,7 @@ __device__ void set_chain(const uint64_t *__restrict__ sorted, int64_t n, uint32
             buf[i] = lists[gsrc[lo] + i];
         }
         wave_sync();
-        // the pieces side by side hold every vertex of the set's chain: pruned
-        // like a chunk (joined at their bridges one after another, 74 us for
-        // 4096 sets, now 67)
-        const uint64_t lt = lanemask_lt();
-        int k = (int)M;
-        bool moved = true;
-        for (int pass = 0; moved && pass < JOIN_PASSES; pass++) {
-            const int k2 = prune_pass<UPPER, 1>(buf, buf, k, lt);
-            moved = k2 != k;
-            k = k2;
-            wave_sync();
-        }
-        if (moved) {
-            int h = 0;
-            if (lane == 0) h = serial_chain<UPPER>(buf, k);
-            wave_sync();
-            k = __builtin_amdgcn_readlane(h, 0);
-        }
-        len = k;
+        len = list_chain<UPPER, 1, 16>(buf, (int)M);
         for (int64_t i = lane; i < len; i += WAVE) dst[i] = buf[i];
     } else {
         for (int64_t c = c0; c <= c1; c++) {

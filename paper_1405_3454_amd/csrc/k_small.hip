@@ -630,49 +630,38 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
             }
         for (int i = tid; i < M; i += BS) up[i] = lo[i];
         __syncthreads();
-        // chains: half the waves prune a part of the lower list each, the
-        // others of the upper one; then one wave per list prunes the joined
-        // parts (a pass drops the points on or beyond the segment of their
-        // neighbours; what no pass drops any more is the chain)
+        // chains: half the waves take a part of the lower list each, the
+        // others of the upper one; then one wave per list the joined parts
         const int nseg = M > 256 ? NW / 2 : 1;
         const int kind = w >= NW / 2, q = w % (NW / 2);
         const int per = ((M + nseg - 1) / nseg + WAVE - 1) / WAVE * WAVE;
         uint64_t *list = kind ? up : lo;
-        auto prune = [&](uint64_t *l, int c) {
-            bool moved = true;
-            for (int pass = 0; moved && pass < PRUNE_PASSES; pass++) {
-                const int c2 = kind ? prune_pass<true, 1>(l, l, c, lt) : prune_pass<false, 1>(l, l, c, lt);
-                moved = c2 != c;
-                c = c2;
-                wave_sync();
-            }
-            if (moved) {
-                int h = 0;
-                if (lane == 0) h = kind ? serial_chain<true>(l, c) : serial_chain<false>(l, c);
-                wave_sync();
-                c = __builtin_amdgcn_readlane(h, 0);
-            }
-            return c;
-        };
+        auto chain = [&](uint64_t *l, int c) { return kind ? list_chain<true, 1, 16>(l, c) : list_chain<false, 1, 16>(l, c); };
         if (q < nseg) {
             const int b0 = min(M, q * per), c = min(M, b0 + per) - b0;
-            const int r = prune(list + b0, c);
+            const int r = chain(list + b0, c);
             if (lane == 0) L.seg[kind][q] = r;
         }
         __syncthreads();
         if (q == 0) {
-            int c = L.seg[kind][0];
-            for (int t = 1; t < nseg; t++) {
-                const int b0 = min(M, t * per), ct = L.seg[kind][t];
-                for (int i0 = 0; i0 < ct; i0 += WAVE) {   // moved down: c + i <= b0 + i
-                    const uint64_t v = i0 + lane < ct ? list[b0 + i0 + lane] : 0;
-                    wave_sync();
-                    if (i0 + lane < ct) list[c + i0 + lane] = v;
-                    wave_sync();
+            const int mine = lane < nseg ? L.seg[kind][lane] : 0;
+            int c = (int)wave_sum_i64(mine);
+            if (c > 4 * WAVE) {       // long parts; short ones are taken as one list again (2 us less)
+                c = kind ? join_pieces<true>(list, per, nseg, mine) : join_pieces<false>(list, per, nseg, mine);
+            } else if (nseg > 1) {
+                int at = __shfl(mine, 0);
+                for (int t = 1; t < nseg; t++) {
+                    const int b0 = min(M, t * per), ct = __shfl(mine, t);
+                    for (int i0 = 0; i0 < ct; i0 += WAVE) {   // moved down: at + i <= b0 + i
+                        const uint64_t v = i0 + lane < ct ? list[b0 + i0 + lane] : 0;
+                        wave_sync();
+                        if (i0 + lane < ct) list[at + i0 + lane] = v;
+                        wave_sync();
+                    }
+                    at += ct;
                 }
-                c += ct;
+                c = chain(list, c);
             }
-            if (nseg > 1) c = prune(list, c);
             if (lane == 0) L.seg[kind][0] = c;
         }
         __syncthreads();
