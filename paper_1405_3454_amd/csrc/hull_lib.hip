@@ -870,19 +870,20 @@ static int prepare(hull_ctx *ctx, int64_t n, int64_t S, hipStream_t st, Plan *p)
     return rc;
 }
 
-// Inputs that one block per set takes from the points to the hull (k_small).
-// One set: up to 8192 points, which always fit the block's LDS (square, disk,
-// annulus, circle at 8192: 30, 37, 49 and 341 us against 98, 103, 106 and 381
-// with the launches of the general path; at 16384 points a circle, all of
-// them hull vertices, takes 809 us against 434).  Several sets: the host knows
-// the total only, so the bound keeps a set that holds most of it small (64
-// sets of 500 to 8000 points 55 us against 232, 500 of 500 points 50 against
-// 241; one of 30000 points and one of ten 98 us against 161, but one of 240000
-// and fifteen of 1000 would take 557 against 189).
-constexpr int64_t SMALL_ONE = SM_CAP, SMALL_PER_SET = 4096, SMALL_BATCH = 1 << 18;
-static bool small_input(int64_t n_total, int64_t S, bool learned) {
+// Inputs that one block per set takes from the points to the hull (k_small):
+// up to 8192 points in all, which always fit a block's LDS (square, disk,
+// annulus, circle at 8192: 30, 37, 49 and 285 us against 98, 103, 106 and 381
+// with the launches of the general path; 8000 on a circle and ten more as two
+// sets 300 against 490).  Without the filter every point goes to the sort,
+// which the general path spreads over the chip above 4096 keys: there one set
+// of 4096 points takes 93 us against 98, one of 5000 154 against 126.  The host
+// knows the total only, so with a larger bound one block could be handed a
+// large set: 240000 points and sixty sets of 30 took 411 (square) to 10200 us
+// (circle) against 204 and 677.
+constexpr int64_t SMALL_POINTS = SM_CAP, SMALL_UNFILTERED = SORT_SMALL;
+static bool small_input(int64_t n_total, int64_t S, bool learned, bool nofilter) {
     if (learned || S > SM_SETS) return false;
-    return n_total <= (S == 1 ? SMALL_ONE : std::min(SMALL_BATCH, SMALL_ONE + SMALL_PER_SET * S));
+    return n_total <= (S == 1 && nofilter ? SMALL_UNFILTERED : SMALL_POINTS);
 }
 
 static int run_small(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x, const float *y,
@@ -935,7 +936,7 @@ static int run_compute(hull_ctx *ctx, hipStream_t st, const float *x, const floa
     const bool refine = !(flags & (HULL_NOREFINE | HULL_NOFILTER));
     const int64_t *cnt = ctx->counts;
     int64_t *segcnt = W<int64_t>(p, p.segcnt);
-    if (small_input(n_total, S, learned) && (off ? hoff_out != nullptr : h_out != nullptr))
+    if (small_input(n_total, S, learned, flags & HULL_NOFILTER) && (off ? hoff_out != nullptr : h_out != nullptr))
         return run_small(ctx, p, st, x, y, n_total, off, n1, S, flags & HULL_NOFILTER, refine, hull, hoff_out,
                          h_out);
     // one set: the farthest keys of refinement round 0's children start cleared
