@@ -507,13 +507,14 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(const uint64_t *__re
 
 // Runs of equal (set, x) in keys sorted by (set, x).  The chains need of a run
 // its lowest and its highest key, so it becomes its lowest key, copies of it,
-// and its highest: a run of up to TIE_SHORT keys in LDS by the thread at its
-// head, a longer one by k_sort_long, which finds it in a list.  A list entry
+// and its highest: in LDS a run of up to TIE_THREAD keys by the thread at its
+// head and one of up to TIE_SHORT by a wave (a thread walks 250 keys in 60
+// us), a longer one by k_sort_long, which finds it in a list.  A list entry
 // is an atomic on one counter, about 9 ns each, so few runs may need one: with
 // 2^27 clamped normal points (about 30 keys a run) and runs of up to 16 sorted
 // by their threads and longer ones listed this took 38.1 ms, now 1.2; with
 // 2^27 points of a square (8 a run) 5.7 ms, now 0.9.
-constexpr int TIE_SHORT = 256;
+constexpr int TIE_THREAD = 32, TIE_SHORT = 256;
 constexpr int TIE_STEP = 4;              // keys read together along a run
 constexpr int64_t TIE_WAVE = 1 << 12, TIE_BLOCK = 1 << 18;
 constexpr int64_t TIE_PART = 1 << 15;    // keys of a run above TIE_BLOCK that a block takes at once
@@ -539,11 +540,14 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
                                                    SortState *__restrict__ state, LongRun *__restrict__ runs,
                                                    const int *__restrict__ seg_fallback) {
     constexpr int TW = TIE_TILE + TIE_SHORT + TIE_STEP + 1;
+    constexpr uint32_t Y = (1u << (8 * Y_DIGITS)) - 1;
     __shared__ uint64_t k[TW];                   // k[j]: key base - 1 + j
+    __shared__ uint16_t heads[TIE_TILE / TIE_THREAD];   // where runs of more than TIE_THREAD keys start
+    __shared__ int nheads;
     const int64_t n = *cnt_ptr;
     if (n <= sort_small(seg_fallback)) return;
     if (seg_fallback && *seg_fallback == 0) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = lane_id();
     for (int64_t base = (int64_t)blockIdx.x * TIE_TILE; base < n; base += (int64_t)gridDim.x * TIE_TILE) {
         __syncthreads();
         constexpr int U = (TW + 255) / 256;
@@ -556,12 +560,12 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
 #pragma unroll
         for (int u = 0; u < U; u++)
             if (tid + u * 256 < TW) k[tid + u * 256] = v[u];
+        if (tid == 0) nheads = 0;
         __syncthreads();
         for (int t = tid; t < TIE_TILE && base + t < n; t += 256) {
             const int j = t + 1;
             const uint64_t g = k[j] >> (8 * Y_DIGITS);
             if ((k[j + 1] >> (8 * Y_DIGITS)) != g || (k[j - 1] >> (8 * Y_DIGITS)) == g) continue;
-            constexpr uint32_t Y = (1u << (8 * Y_DIGITS)) - 1;
             uint32_t ylo = (uint32_t)k[j] & Y, yhi = ylo;
             int len = 1;
             for (bool more = true; more;) {
@@ -576,15 +580,44 @@ __global__ __launch_bounds__(256) void k_sort_ties(uint64_t *__restrict__ keys,
                     yhi = more ? max(yhi, y) : yhi;
                     len += more;
                 }
-                more = more & (len <= TIE_SHORT);
+                more = more & (len <= TIE_THREAD);
             }
-            const int64_t i = base + t;
+            if (len > TIE_THREAD) {
+                heads[atomicAdd(&nheads, 1)] = (uint16_t)t;
+                continue;
+            }
+            const uint64_t low = g << (8 * Y_DIGITS) | ylo;
+            for (int q = 0; q < len - 1; q++) k[j + q] = low;
+            k[j + len - 1] = g << (8 * Y_DIGITS) | yhi;
+        }
+        __syncthreads();
+        for (int h = tid >> 6; h < nheads; h += 256 / WAVE) {
+            const int t = heads[h], j = t + 1;
+            const uint64_t g = k[j] >> (8 * Y_DIGITS);
+            uint32_t ylo = Y, yhi = 0;
+            int len = 0;
+            for (bool more = true; more && len <= TIE_SHORT;) {
+                const int i = j + len + lane;
+                const uint64_t c = i < TW ? k[i] : ~0ull;
+                const uint64_t in = __ballot((c >> (8 * Y_DIGITS)) == g);
+                const int m = ~in ? __builtin_ctzll(~in) : WAVE;
+                if (lane < m) {
+                    ylo = min(ylo, (uint32_t)c & Y);
+                    yhi = max(yhi, (uint32_t)c & Y);
+                }
+                len += m;
+                more = m == WAVE;
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                ylo = min(ylo, (uint32_t)__shfl_xor((int)ylo, o));
+                yhi = max(yhi, (uint32_t)__shfl_xor((int)yhi, o));
+            }
             if (len <= TIE_SHORT) {
-                const uint64_t low = g << (8 * Y_DIGITS) | ylo;
-                for (int q = 0; q < len - 1; q++) k[j + q] = low;
-                k[j + len - 1] = g << (8 * Y_DIGITS) | yhi;
-            } else {
-                int64_t lo = i + len, hi = n;        // the first key past the run
+                for (int q = lane; q < len; q += WAVE) k[j + q] = g << (8 * Y_DIGITS) | (q == len - 1 ? yhi : ylo);
+            } else if (lane == 0) {
+                const int64_t i = base + t;
+                int64_t lo = i + TIE_SHORT, hi = n;  // the first key past the run
                 while (lo < hi) {
                     const int64_t mid = (lo + hi) >> 1;
                     if ((keys[mid] >> (8 * Y_DIGITS)) == g) lo = mid + 1; else hi = mid;
