@@ -183,7 +183,7 @@ static Plan make_plan(int64_t n, int64_t S, int64_t W) {
         return r;
     };
     p.tcap = n / TILE + 2 * S + 2;
-    p.u0cap = n / CHAIN_C + n / SM_CAP + 2;
+    p.u0cap = n / CHAIN_C + 2;
     p.nwave = W;
     // list entries: the discard pass's regions (q = ceil(T / W) tiles of
     // points per wave) end by T * TILE
@@ -890,19 +890,8 @@ static int run_small(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *
                      int64_t n_total, const int64_t *off, int64_t n1, int64_t S, bool nofilter, bool refine,
                      uint32_t *hull, int64_t *hoff_out, int64_t *h_out) {
     SmallWs ws;
-    ws.idx = W<uint32_t>(p, p.surv);
-    ws.key = W<uint64_t>(p, p.keys0);
-    ws.edge = W<uint16_t>(p, p.hkeys);
     ws.cidx = W<uint32_t>(p, p.cidx);
     ws.ckey = W<uint64_t>(p, p.ckeys);
-    ws.sortA = W<uint64_t>(p, p.keysA);
-    ws.sortB = W<uint64_t>(p, p.keysB);
-    ws.lo[0] = W<uint64_t>(p, p.lo0);
-    ws.lo[1] = W<uint64_t>(p, p.lo1);
-    ws.up[0] = W<uint64_t>(p, p.up0);
-    ws.up[1] = W<uint64_t>(p, p.up1);
-    ws.ccnt = W<uint32_t>(p, p.ccnt);
-    ws.u0cap = p.u0cap;
     ws.hull = W<uint32_t>(p, p.hpos);
     ws.hcnt = W<uint32_t>(p, p.hcnt);
     ws.scnt = W<int32_t>(p, p.bounds);

@@ -12,15 +12,13 @@
 // of every stage, are the general path's: the same predicates on the same
 // slots, edges and farthest keys.
 //
-// A set's survivors live in LDS up to SM_CAP of them, and so do the
-// candidates of the sort and the chains; above that they live in the set's
-// own range of the workspace lists, and the sort and the chains run there,
-// still by the one block.
+// A set has at most SM_CAP points here, so its survivors and the candidates of
+// the sort and the chains fit the block's LDS.
 #include "hg_device.h"
 
 namespace hg {
 
-constexpr int SM_CAP = 8192;          // survivors, and candidates, held in LDS
+constexpr int SM_CAP = 8192;          // points of a set
 constexpr int SM_LIGHT = 2048;        // up to here both fit side by side
 constexpr int SM_THREADS = 512;       // per block: 256 took 84 us on 8000 annulus points, 512 53 us; 1000 points 20 us both
 constexpr int SM_COUNTS = 1 + REF_ROUNDS;
@@ -38,30 +36,15 @@ struct SmallLds {
     Poly P;
     int nsurv, ncand, alive[SM_COUNTS];
     int seg[2][8];
-    union {
-        struct {
-            PolyScratch G;
-            uint32_t sl[MAX_SLOTS];
-            SlotBest wbest[16][MAX_SLOTS];
-        } poly;
-        struct {
-            uint32_t run[RADIX];
-        } sort;
-        struct {
-            int64_t goff[4][CHAIN_G + 1], pref[4][CHAIN_G], src[4][CHAIN_G], sh[3 + 2 * CHAIN_G];
-            int ne[4][CHAIN_G];
-        } merge;
-    } u;
+    PolyScratch G;
+    uint32_t sl[MAX_SLOTS];
+    SlotBest wbest[16][MAX_SLOTS];
 };
 
 // Workspace of a call: list entries of a set at its own points' positions.
 struct SmallWs {
-    uint32_t *idx, *cidx;             // survivors; candidates
-    uint64_t *key, *ckey;
-    uint16_t *edge;
-    uint64_t *sortA, *sortB, *lo[2], *up[2];
-    uint32_t *ccnt;
-    int64_t u0cap;
+    uint32_t *cidx;                   // candidates
+    uint64_t *ckey;
     uint32_t *hull;                   // several sets: each set's hull
     uint32_t *hcnt;
     int32_t *scnt;                    // [S][SM_COUNTS]
@@ -222,95 +205,6 @@ __device__ __forceinline__ uint16_t small_step(const REdge *tab, uint16_t st, ui
     return out;
 }
 
-// Stable LSD radix sort of n keys by the block (8-bit digits, BS / 64 waves
-// of 512 consecutive keys per tile), from `in` through A and B; the result is
-// in B (an even number of passes).
-template <int BS>
-__device__ void small_radix(const uint64_t *in, uint64_t *A, uint64_t *B, int n, SmallLds &L) {
-    constexpr int NW = BS / WAVE, PER = 8;
-    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const uint64_t lt = lanemask_lt();
-    uint32_t *run = L.u.sort.run;
-    auto *wcnt = reinterpret_cast<uint32_t (*)[RADIX]>(L.raw);   // free here: digit counters, a row per wave
-    for (int pass = 0; pass < 6; pass++) {
-        const uint64_t *src = pass == 0 ? in : (pass & 1) ? A : B;
-        uint64_t *dst = (pass & 1) ? B : A;
-        const int shift = 8 * pass;
-        for (int d = tid; d < RADIX; d += BS) run[d] = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += BS) atomicAdd(&run[(uint32_t)(src[i] >> shift) & (RADIX - 1)], 1u);
-        __syncthreads();
-        if (w == 0) {                 // exclusive scan of the 256 counts
-            uint32_t c[4], t = 0;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                c[q] = run[lane * 4 + q];
-                t += c[q];
-            }
-            uint32_t inc = t;
-#pragma unroll
-            for (int o = 1; o < WAVE; o <<= 1) {
-                const uint32_t v = __shfl_up(inc, o);
-                if (lane >= o) inc += v;
-            }
-            uint32_t at = inc - t;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                run[lane * 4 + q] = at;
-                at += c[q];
-            }
-        }
-        __syncthreads();
-        for (int base = 0; base < n; base += BS * PER) {
-            for (int d = tid; d < NW * RADIX; d += BS) wcnt[d / RADIX][d % RADIX] = 0;
-            __syncthreads();
-            uint64_t k[PER];
-            uint32_t rank[PER], dg[PER];
-#pragma unroll
-            for (int r = 0; r < PER; r++) {
-                const int i = base + (w * PER + r) * WAVE + lane;
-                k[r] = i < n ? src[i] : 0;
-            }
-#pragma unroll
-            for (int r = 0; r < PER; r++) {
-                const int i = base + (w * PER + r) * WAVE + lane;
-                const bool has = i < n;
-                dg[r] = (uint32_t)(k[r] >> shift) & (RADIX - 1);
-                uint64_t peers = __ballot(has);
-#pragma unroll
-                for (int b = 0; b < 8; b++) {
-                    const bool bit = (dg[r] >> b) & 1;
-                    const uint64_t m = __ballot(bit);
-                    peers &= bit ? m : ~m;
-                }
-                const int lead = has ? __ffsll((unsigned long long)peers) - 1 : 0;
-                uint32_t old = 0;
-                if (has && lead == lane) {
-                    old = wcnt[w][dg[r]];
-                    wcnt[w][dg[r]] = old + (uint32_t)__popcll(peers);
-                }
-                wave_sync();
-                rank[r] = __shfl(old, lead) + (uint32_t)__popcll(peers & lt);
-            }
-            __syncthreads();
-            for (int d = tid; d < RADIX; d += BS) {
-                uint32_t at = run[d];
-                for (int ww = 0; ww < NW; ww++) {
-                    const uint32_t c = wcnt[ww][d];
-                    wcnt[ww][d] = at;
-                    at += c;
-                }
-                run[d] = at;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < PER; r++)
-                if (base + (w * PER + r) * WAVE + lane < n) dst[wcnt[w][dg[r]] + rank[r]] = k[r];
-            __syncthreads();
-        }
-    }
-}
-
 // Position of key k in the hull whose lower chain is lo[0, nl) and upper
 // chain up[0, nu), or -1.
 __device__ __forceinline__ int small_find(const uint64_t *lo, int nl, const uint64_t *up, int nu, uint64_t k) {
@@ -351,8 +245,8 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
 
     // Steps 1 and 2
     if (!nofilter) {
-        uint32_t *sl = L.u.poly.sl;
-        SlotBest (*wbest)[MAX_SLOTS] = L.u.poly.wbest;
+        uint32_t *sl = L.sl;
+        SlotBest (*wbest)[MAX_SLOTS] = L.wbest;
         switch (preset) {
         case 0: small_extremes<0, BS>(x, y, a, e, dirs, wbest, sl, L.raw); break;
         case 1: small_extremes<1, BS>(x, y, a, e, dirs, wbest, sl, L.raw); break;
@@ -364,7 +258,7 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
         default: small_extremes<7, BS>(x, y, a, e, dirs, wbest, sl, L.raw); break;
         }
         const int64_t ts = n ? (e - tile_base(a, phase) + TILE - 1) / TILE : 0;
-        build_polygon(L.u.poly.G, sl, x, y, ts, L.P);
+        build_polygon(L.G, sl, x, y, ts, L.P);
         const int m = L.P.m >= 2 ? L.P.m : 0;
         for (int k = tid; k < MAX_SLOTS; k += BS) {
             const int b = k + 1 < m ? k + 1 : 0;
@@ -416,44 +310,31 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
                 const uint64_t key = ((uint64_t)((uint32_t)(int32_t)px[u] & 0xFFFFFFu) << 24) |
                                      ((uint32_t)(int32_t)py[u] & 0xFFFFFFu);
                 const uint32_t id = (uint32_t)(a + i0 + u * BS);
-                if (o < SM_CAP) {
-                    lkey[o] = key;
-                    lidx[o] = id;
-                } else {
-                    ws.key[a + o] = key;
-                    ws.idx[a + o] = id;
-                }
+                lkey[o] = key;
+                lidx[o] = id;
             }
             at += __popcll(b[u]);
         }
     }
     __syncthreads();
     const int K = L.nsurv;
-    const bool in_lds = K <= SM_CAP;
-    if (!in_lds) {                    // all of them in the workspace
-        for (int i = tid; i < SM_CAP; i += BS) {
-            ws.key[a + i] = lkey[i];
-            ws.idx[a + i] = lidx[i];
-        }
-        __syncthreads();
-    }
 
     // refinement rounds: the survivors' edges, then per round the children of
     // each edge at its farthest point (k_ref_pass on one block)
-    auto rounds = [&](const uint64_t *key, const uint32_t *idx, uint16_t *edge) {
+    auto rounds = [&]() {
         if (!refine) {
-            for (int i = tid; i < K; i += BS) edge[i] = RE_NONE;
+            for (int i = tid; i < K; i += BS) ledge[i] = RE_NONE;
             __syncthreads();
             return;
         }
         for (int i = tid; i < K; i += BS) {
-            const uint64_t k = key[i];
+            const uint64_t k = lkey[i];
             double dist;
             uint16_t eo;
             small_edges<1>(L.P, &k, &eo, &dist);
-            edge[i] = eo;
+            ledge[i] = eo;
             if (eo != RE_NONE) {
-                const unsigned long long fk = far_key(dist, idx[i]);
+                const unsigned long long fk = far_key(dist, lidx[i]);
                 if (L.far[0][eo] < fk) atomicMax(&L.far[0][eo], fk);
             }
         }
@@ -472,14 +353,14 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
             __syncthreads();
             int alive = 0;
             for (int i = tid; i < K; i += BS) {
-                const uint16_t st = edge[i];
+                const uint16_t st = ledge[i];
                 if (st == RE_DROP) continue;
                 uint16_t out = st;
                 if (st < RE_DROP) {
                     double dist;
-                    out = small_step(L.tab[q], st, key[i], &dist);
-                    edge[i] = out;
-                    if (out < RE_DROP) atomicMax(&L.far[q][out], (unsigned long long)far_key(dist, idx[i]));
+                    out = small_step(L.tab[q], st, lkey[i], &dist);
+                    ledge[i] = out;
+                    if (out < RE_DROP) atomicMax(&L.far[q][out], (unsigned long long)far_key(dist, lidx[i]));
                 }
                 alive += out != RE_DROP;
             }
@@ -561,173 +442,128 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
     };
     if (refine && K <= BS) rounds_reg(std::integral_constant<int, 1>());
     else if (refine && K <= 4 * BS) rounds_reg(std::integral_constant<int, 4>());
-    else if (in_lds) rounds(lkey, lidx, ledge);
-    else rounds(ws.key + a, ws.idx + a, ws.edge + a);
+    else rounds();
 
     // candidates: in LDS side by side with a light survivor list, else in the
-    // workspace (index and key), the keys back to LDS when they fit
+    // workspace (index and key), the keys back to LDS from there
     const bool light = K <= SM_LIGHT;
     uint64_t *lo = reinterpret_cast<uint64_t *>(light ? L.raw + SM_LIGHT * 8 : L.raw);
     uint64_t *up = reinterpret_cast<uint64_t *>(light ? L.raw + SM_LIGHT * 16 : L.raw + SM_UP);
-    auto collect = [&](const uint64_t *key, const uint32_t *idx, const uint16_t *edge) {
-        for (int i0 = 0; i0 < K; i0 += BS) {
-            const int i = i0 + tid;
-            const bool keep = i < K && edge[i] != RE_DROP;
-            const uint64_t b = __ballot(keep);
-            if (!b) continue;
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&L.ncand, __popcll(b));
-            at = __builtin_amdgcn_readfirstlane(at) + __popcll(b & lt);
-            if (!keep) continue;
-            if (light) {
-                lo[at] = key[i];
-            } else {
-                ws.ckey[a + at] = key[i];
-                ws.cidx[a + at] = idx[i];
-            }
-        }
-        __syncthreads();
-    };
-    if (in_lds) collect(lkey, lidx, ledge);
-    else collect(ws.key + a, ws.idx + a, ws.edge + a);
-    const int M = L.ncand;
-
-    int nl = 0, nu = 0;
-    const uint64_t *clo = lo, *cup = up;
-    uint32_t *hull_out = off ? ws.hull + a : hull1;
-    if (M <= SM_CAP) {
-        int pw = 1;
-        while (pw < M) pw <<= 1;
-        if (light && M <= BS) {       // a rank per thread
-            const uint64_t mine = tid < M ? lo[tid] : 0;
-            int rank = 0;
-#pragma unroll 16
-            for (int j = 0; j < M; j++) {
-                const uint64_t o = lo[j];
-                    rank += (int)(o < mine) | ((int)(o == mine) & (int)(j < tid));
-            }
-            __syncthreads();
-            if (tid < M) lo[rank] = mine;
-            pw = 0;
-        } else if (light) {
-            for (int i = M + tid; i < pw; i += BS) lo[i] = ~0ull;
-        } else {
-            for (int i = tid; i < pw; i += BS) lo[i] = i < M ? ws.ckey[a + i] : ~0ull;
-        }
-        __syncthreads();
-        for (int k = 2; k <= pw; k <<= 1)
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int t = tid; t < (pw >> 1); t += BS) {
-                    const int i = 2 * j * (t / j) + (t % j), l = i + j;
-                    const bool asc = (i & k) == 0;
-                    const uint64_t u = lo[i], v = lo[l];
-                    if ((u > v) == asc) {
-                        lo[i] = v;
-                        lo[l] = u;
-                    }
-                }
-                __syncthreads();
-            }
-        for (int i = tid; i < M; i += BS) up[i] = lo[i];
-        __syncthreads();
-        // chains: half the waves take a part of the lower list each, the
-        // others of the upper one; then one wave per list the joined parts
-        const int nseg = M > 256 ? NW / 2 : 1;
-        const int kind = w >= NW / 2, q = w % (NW / 2);
-        const int per = ((M + nseg - 1) / nseg + WAVE - 1) / WAVE * WAVE;
-        uint64_t *list = kind ? up : lo;
-        auto chain = [&](uint64_t *l, int c) { return kind ? list_chain<true, 1, 16>(l, c) : list_chain<false, 1, 16>(l, c); };
-        if (q < nseg) {
-            const int b0 = min(M, q * per), c = min(M, b0 + per) - b0;
-            const int r = chain(list + b0, c);
-            if (lane == 0) L.seg[kind][q] = r;
-        }
-        __syncthreads();
-        if (q == 0) {
-            const int mine = lane < nseg ? L.seg[kind][lane] : 0;
-            int c = (int)wave_sum_i64(mine);
-            if (c > 4 * WAVE) {       // long parts; short ones are taken as one list again (2 us less)
-                c = kind ? join_pieces<true>(list, per, nseg, mine) : join_pieces<false>(list, per, nseg, mine);
-            } else if (nseg > 1) {
-                int at = __shfl(mine, 0);
-                for (int t = 1; t < nseg; t++) {
-                    const int b0 = min(M, t * per), ct = __shfl(mine, t);
-                    for (int i0 = 0; i0 < ct; i0 += WAVE) {   // moved down: at + i <= b0 + i
-                        const uint64_t v = i0 + lane < ct ? list[b0 + i0 + lane] : 0;
-                        wave_sync();
-                        if (i0 + lane < ct) list[at + i0 + lane] = v;
-                        wave_sync();
-                    }
-                    at += ct;
-                }
-                c = chain(list, c);
-            }
-            if (lane == 0) L.seg[kind][0] = c;
-        }
-        __syncthreads();
-        nl = L.seg[0][0];
-        nu = L.seg[1][0];
-        const int h = (int)hull_size(nl, nu);
-        if (!light) {                 // the upper chain behind the lower one makes room for the hull
-            for (int i = tid; i < nu; i += BS) lo[nl + i] = up[i];
-            cup = lo + nl;
-            __syncthreads();
-        }
-        uint32_t *hull = reinterpret_cast<uint32_t *>(light ? L.raw + SM_LIGHT * 24 : L.raw + SM_UP);
-        for (int i = tid; i < h; i += BS) hull[i] = NONE;
-        __syncthreads();
+    for (int i0 = 0; i0 < K; i0 += BS) {
+        const int i = i0 + tid;
+        const bool keep = i < K && ledge[i] != RE_DROP;
+        const uint64_t b = __ballot(keep);
+        if (!b) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&L.ncand, __popcll(b));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(b & lt);
+        if (!keep) continue;
         if (light) {
-            for (int i = tid; i < K; i += BS) {
-                if (ledge[i] == RE_DROP) continue;
-                const int p = small_find(clo, nl, cup, nu, lkey[i]);
-                if (p >= 0 && p < h) atomicMin(&hull[p], lidx[i]);
-            }
+            lo[at] = lkey[i];
         } else {
-            for (int i = tid; i < M; i += BS) {
-                const int p = small_find(clo, nl, cup, nu, ws.ckey[a + i]);
-                if (p >= 0 && p < h) atomicMin(&hull[p], ws.cidx[a + i]);
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < h; i += BS) hull_out[i] = hull[i];
-    } else {
-        // more candidates than LDS holds: the general sort and chain steps on
-        // the workspace, by this block
-        small_radix<BS>(ws.ckey + a, ws.sortA + a, ws.sortB + a, M, L);
-        const int64_t cc = a / CHAIN_C + a / SM_CAP;      // chunk counts: no two such sets overlap
-        uint32_t *cnt[2][2] = {{ws.ccnt + cc, ws.ccnt + ws.u0cap + cc},
-                               {ws.ccnt + 2 * ws.u0cap + cc, ws.ccnt + 3 * ws.u0cap + cc}};
-        if (w < 4)
-            chain_chunks(ws.sortB + a, M, ws.lo[0] + a, ws.up[0] + a, cnt[0][0], cnt[1][0],
-                         reinterpret_cast<Chain0Lds *>(L.raw)[w], w, min(NW, 4));
-        __syncthreads();
-        int cur = 0, lev = 0;
-        for (int64_t R = CHAIN_C; R < M; R *= CHAIN_G, lev++, cur = 1 - cur) {
-            const int64_t U = (M + R - 1) / R;
-            auto &X = L.u.merge;
-            uint64_t *stage = reinterpret_cast<uint64_t *>(L.raw) + (w & 3) * MERGE_CAP;
-            for (int kind = 0; kind < 2; kind++) {
-                const uint64_t *in = (kind ? ws.up : ws.lo)[cur] + a;
-                uint64_t *out = (kind ? ws.up : ws.lo)[1 - cur] + a;
-                chain_merge(kind, in, cnt[kind][cur], U, R, lev, out, cnt[kind][1 - cur], w < 4 ? w : U, min(NW, 4),
-                            0, 1, stage, X.goff[w & 3], X.ne[w & 3], X.pref[w & 3], X.src[w & 3], X.sh);
-                __syncthreads();
-            }
-        }
-        clo = ws.lo[cur] + a;
-        cup = ws.up[cur] + a;
-        nl = (int)cnt[0][cur][0];
-        nu = (int)cnt[1][cur][0];
-        const int h = (int)hull_size(nl, nu);
-        for (int i = tid; i < h; i += BS) hull_out[i] = NONE;
-        __syncthreads();
-        for (int i = tid; i < M; i += BS) {
-            const int p = small_find(clo, nl, cup, nu, ws.ckey[a + i]);
-            if (p >= 0 && p < h) atomicMin(&hull_out[p], ws.cidx[a + i]);
+            ws.ckey[a + at] = lkey[i];
+            ws.cidx[a + at] = lidx[i];
         }
     }
+    __syncthreads();
+    const int M = L.ncand;
+
+    const uint64_t *clo = lo, *cup = up;
+    uint32_t *hull_out = off ? ws.hull + a : hull1;
+    int pw = 1;
+    while (pw < M) pw <<= 1;
+    if (light && M <= BS) {       // a rank per thread
+        const uint64_t mine = tid < M ? lo[tid] : 0;
+        int rank = 0;
+#pragma unroll 16
+        for (int j = 0; j < M; j++) {
+            const uint64_t o = lo[j];
+            rank += (int)(o < mine) | ((int)(o == mine) & (int)(j < tid));
+        }
+        __syncthreads();
+        if (tid < M) lo[rank] = mine;
+        pw = 0;
+    } else if (light) {
+        for (int i = M + tid; i < pw; i += BS) lo[i] = ~0ull;
+    } else {
+        for (int i = tid; i < pw; i += BS) lo[i] = i < M ? ws.ckey[a + i] : ~0ull;
+    }
+    __syncthreads();
+    for (int k = 2; k <= pw; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = tid; t < (pw >> 1); t += BS) {
+                const int i = 2 * j * (t / j) + (t % j), l = i + j;
+                const bool asc = (i & k) == 0;
+                const uint64_t u = lo[i], v = lo[l];
+                if ((u > v) == asc) {
+                    lo[i] = v;
+                    lo[l] = u;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < M; i += BS) up[i] = lo[i];
+    __syncthreads();
+    // chains: half the waves take a part of the lower list each, the
+    // others of the upper one; then one wave per list the joined parts
+    const int nseg = M > 256 ? NW / 2 : 1;
+    const int kind = w >= NW / 2, q = w % (NW / 2);
+    const int per = ((M + nseg - 1) / nseg + WAVE - 1) / WAVE * WAVE;
+    uint64_t *list = kind ? up : lo;
+    auto chain = [&](uint64_t *l, int c) { return kind ? list_chain<true, 1, 16>(l, c) : list_chain<false, 1, 16>(l, c); };
+    if (q < nseg) {
+        const int b0 = min(M, q * per), c = min(M, b0 + per) - b0;
+        const int r = chain(list + b0, c);
+        if (lane == 0) L.seg[kind][q] = r;
+    }
+    __syncthreads();
+    if (q == 0) {
+        const int mine = lane < nseg ? L.seg[kind][lane] : 0;
+        int c = (int)wave_sum_i64(mine);
+        if (c > 4 * WAVE) {       // long parts; short ones are taken as one list again (2 us less)
+            c = kind ? join_pieces<true>(list, per, nseg, mine) : join_pieces<false>(list, per, nseg, mine);
+        } else if (nseg > 1) {
+            int at = __shfl(mine, 0);
+            for (int t = 1; t < nseg; t++) {
+                const int b0 = min(M, t * per), ct = __shfl(mine, t);
+                for (int i0 = 0; i0 < ct; i0 += WAVE) {   // moved down: at + i <= b0 + i
+                    const uint64_t v = i0 + lane < ct ? list[b0 + i0 + lane] : 0;
+                    wave_sync();
+                    if (i0 + lane < ct) list[at + i0 + lane] = v;
+                    wave_sync();
+                }
+                at += ct;
+            }
+            c = chain(list, c);
+        }
+        if (lane == 0) L.seg[kind][0] = c;
+    }
+    __syncthreads();
+    const int nl = L.seg[0][0], nu = L.seg[1][0];
+    const int h = (int)hull_size(nl, nu);
+    if (!light) {                 // the upper chain behind the lower one makes room for the hull
+        for (int i = tid; i < nu; i += BS) lo[nl + i] = up[i];
+        cup = lo + nl;
+        __syncthreads();
+    }
+    uint32_t *hull = reinterpret_cast<uint32_t *>(light ? L.raw + SM_LIGHT * 24 : L.raw + SM_UP);
+    for (int i = tid; i < h; i += BS) hull[i] = NONE;
+    __syncthreads();
+    if (light) {
+        for (int i = tid; i < K; i += BS) {
+            if (ledge[i] == RE_DROP) continue;
+            const int p = small_find(clo, nl, cup, nu, lkey[i]);
+            if (p >= 0 && p < h) atomicMin(&hull[p], lidx[i]);
+        }
+    } else {
+        for (int i = tid; i < M; i += BS) {
+            const int p = small_find(clo, nl, cup, nu, ws.ckey[a + i]);
+            if (p >= 0 && p < h) atomicMin(&hull[p], ws.cidx[a + i]);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < h; i += BS) hull_out[i] = hull[i];
     if (tid == 0) {
-        const int64_t h = hull_size(nl, nu);
         if (off) ws.hcnt[s] = (uint32_t)h;
         else *h1 = h;
     }
