@@ -17,6 +17,7 @@
 #include "k_refine.hip"
 #include "k_hull3d.hip"
 #include "k_small.hip"
+#include "k_big.hip"
 
 using namespace hg;
 
@@ -167,7 +168,7 @@ struct Plan {
     size_t tile_off, tile_set, pval, pidx, slots, vals, polys, spans, redges, masks, tile_cnt, tile_pos,
         scan_bs, surv_off, surv, keys0, keysA, keysB, lo0, up0, lo1, up1, ccnt, bounds, hcnt,
         hoff, hkeys, hpos, sstat, sgst, consts, err, setdirs, learn, cand, rtab0, rtab1, rfar0,
-        rfar1, rfar2, segcnt, segmeta, cidx, ckeys, bpart, pticket, total;
+        rfar1, rfar2, segcnt, segmeta, cidx, ckeys, bpart, pticket, big, total;
     int64_t tcap, u0cap;
     int64_t nwave;      // discard waves = regions of the full method's survivor lists
 };
@@ -219,6 +220,7 @@ static Plan make_plan(int64_t n, int64_t S, int64_t W) {
     p.sstat = take(sort_tiles_max(n) * RADIX * 8);              // look-back entries of the tiles
     p.sgst = take(sizeof(SortState));
     p.consts = take(8 * 8);
+    p.big = take(S > 1 ? sizeof(BigState) : 8);
     p.err = take(8);
     p.setdirs = take(S * MAX_DIRS * 2 * 8);
     p.learn = take(learned_ws_bytes(S));
@@ -876,14 +878,19 @@ static int prepare(hull_ctx *ctx, int64_t n, int64_t S, hipStream_t st, Plan *p)
 // with the launches of the general path; 8000 on a circle and ten more as two
 // sets 300 against 490).  Without the filter every point goes to the sort,
 // which the general path spreads over the chip above 4096 keys: there one set
-// of 4096 points takes 93 us against 98, one of 5000 154 against 126.  The host
-// knows the total only, so with a larger bound one block could be handed a
-// large set: 240000 points and sixty sets of 30 took 411 (square) to 10200 us
-// (circle) against 204 and 677.
-constexpr int64_t SMALL_POINTS = SM_CAP, SMALL_UNFILTERED = SORT_SMALL;
-static bool small_input(int64_t n_total, int64_t S, bool learned, bool nofilter) {
+// of 4096 points takes 93 us against 98, one of 5000 154 against 126.
+// Several sets of up to 4096 points on average (64 of 500 to 8000: 48 us
+// against 171; 500 of 500 56 against 241): the host knows the total only, so
+// sets too large for a block are left to k_big, whose phases need the filter
+// and the rounds (without them such batches stay on the general path).  No
+// split of such a total was slower than there, from one set with all of it to
+// 31 of 8193 points, of squares, disks, annuli, circles, lines and columns.
+constexpr int64_t SMALL_POINTS = SM_CAP, SMALL_UNFILTERED = SORT_SMALL, SMALL_PER_SET = 4096;
+static bool small_input(int64_t n_total, int64_t S, bool learned, int flags) {
     if (learned || S > SM_SETS) return false;
-    return n_total <= (S == 1 && nofilter ? SMALL_UNFILTERED : SMALL_POINTS);
+    if (n_total <= (S == 1 && flags & HULL_NOFILTER ? SMALL_UNFILTERED : SMALL_POINTS)) return true;
+    return S > 1 && !(flags & (HULL_NOFILTER | HULL_NOREFINE)) &&
+           n_total <= std::min(BIG_POINTS, SMALL_POINTS + SMALL_PER_SET * S);
 }
 
 static int run_small(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x, const float *y,
@@ -895,12 +902,43 @@ static int run_small(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *
     ws.hull = W<uint32_t>(p, p.hpos);
     ws.hcnt = W<uint32_t>(p, p.hcnt);
     ws.scnt = W<int32_t>(p, p.bounds);
+    ws.defer = nullptr;
+    auto *state = W<BigState>(p, p.big);
+    const bool may_defer = n_total > SMALL_POINTS;      // several sets, some perhaps large
+    if (may_defer) {
+        ws.defer = ws.scnt + S * SM_COUNTS;
+        ws.far = W<unsigned long long>(p, p.rfar0);
+        ws.claims = state->claim;
+        ws.nclaim = 2 * B_NPHASES;
+    }
     LAUNCH(K_FINAL, k_small<SM_THREADS><<<(unsigned)S, SM_THREADS, 0, st>>>(x, y, n_total, phase_of(x), off, n1, ctx->preset,
                                                              ctx->dirs, nofilter, refine, ws, hull, h_out,
                                                              ctx->counts));
-    if (off)
+    if (!off) return HULL_OK;
+    if (!may_defer) {
         LAUNCH(K_FINAL, k_small_out<<<(unsigned)std::min<int64_t>(64, (S + 3) / 4), 256, 0, st>>>(
             off, S, ws.hcnt, ws.scnt, ws.hull, hoff_out, hull, ctx->counts));
+        return HULL_OK;
+    }
+    BigWs bw;
+    bw.st = state;
+    bw.defer = ws.defer;
+    bw.polys = W<Poly>(p, p.polys);
+    bw.far = ws.far;
+    bw.idx = W<uint32_t>(p, p.surv);
+    bw.key = W<uint64_t>(p, p.keys0);
+    bw.edge = W<uint16_t>(p, p.hkeys);
+    bw.cidx = ws.cidx;
+    bw.ckey = ws.ckey;
+    bw.lo[0] = W<uint64_t>(p, p.lo0);
+    bw.lo[1] = W<uint64_t>(p, p.lo1);
+    bw.up[0] = W<uint64_t>(p, p.up0);
+    bw.up[1] = W<uint64_t>(p, p.up1);
+    bw.hull = ws.hull;
+    bw.hcnt = ws.hcnt;
+    bw.scnt = ws.scnt;
+    LAUNCH(K_FINAL, k_big<<<BIG_BLOCKS, BIG_THREADS, 0, st>>>(x, y, n_total, phase_of(x), off, S, ctx->preset, ctx->dirs,
+                                                              bw, hoff_out, hull, ctx->counts));
     return HULL_OK;
 }
 
@@ -925,7 +963,7 @@ static int run_compute(hull_ctx *ctx, hipStream_t st, const float *x, const floa
     const bool refine = !(flags & (HULL_NOREFINE | HULL_NOFILTER));
     const int64_t *cnt = ctx->counts;
     int64_t *segcnt = W<int64_t>(p, p.segcnt);
-    if (small_input(n_total, S, learned, flags & HULL_NOFILTER) && (off ? hoff_out != nullptr : h_out != nullptr))
+    if (small_input(n_total, S, learned, flags) && (off ? hoff_out != nullptr : h_out != nullptr))
         return run_small(ctx, p, st, x, y, n_total, off, n1, S, flags & HULL_NOFILTER, refine, hull, hoff_out,
                          h_out);
     // one set: the farthest keys of refinement round 0's children start cleared

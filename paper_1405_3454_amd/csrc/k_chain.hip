@@ -355,6 +355,10 @@ __device__ int join_pieces(uint64_t *buf, int per, int np, int mine) {
         const int64_t ls = last_seg_start(c, b, m);
         if (ls > b) tailseg = len + (ls - b);
         else if (len == 0 || key_set(buf[len - 1]) != key_set(c[b])) tailseg = len;
+        if (buf + len == c + b) {                       // in its place
+            len += m - b;
+            continue;
+        }
         for (int64_t i0 = b; i0 < m; i0 += WAVE) {      // moved down: len <= g * per + b
             const int64_t i = i0 + lane_id();
             const uint64_t v = i < m ? c[i] : 0;

@@ -12,13 +12,15 @@
 // of every stage, are the general path's: the same predicates on the same
 // slots, edges and farthest keys.
 //
-// A set has at most SM_CAP points here, so its survivors and the candidates of
-// the sort and the chains fit the block's LDS.
+// A set has at most SM_CAP survivors here, and so candidates, which fit the
+// block's LDS; in batches that may hold larger sets, those with more survivors
+// (or more than SM_TRY points) are left to k_big.
 #include "hg_device.h"
 
 namespace hg {
 
-constexpr int SM_CAP = 8192;          // points of a set
+constexpr int SM_CAP = 8192;          // survivors of a set
+constexpr int SM_TRY = 2 * SM_CAP;    // points of a set that may have no more (16000 of an annulus: 92 us)
 constexpr int SM_LIGHT = 2048;        // up to here both fit side by side
 constexpr int SM_THREADS = 512;       // per block: 256 took 84 us on 8000 annulus points, 512 53 us; 1000 points 20 us both
 constexpr int SM_COUNTS = 1 + REF_ROUNDS;
@@ -48,6 +50,12 @@ struct SmallWs {
     uint32_t *hull;                   // several sets: each set's hull
     uint32_t *hcnt;
     int32_t *scnt;                    // [S][SM_COUNTS]
+    // batches with room for sets of more points (else null): sets left to
+    // k_big; its claims and the sets' farthest keys, cleared for it
+    int32_t *defer;
+    unsigned long long *far;          // [S][RE_CAP]
+    uint32_t *claims;
+    int nclaim;
 };
 
 // Step 1 of points [a, e): the slots into sl.
@@ -242,6 +250,19 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
     uint16_t *ledge = reinterpret_cast<uint16_t *>(L.raw + SM_CAP * 12);
     if (tid == 0) { L.nsurv = 0; L.ncand = 0; }
     if (tid < SM_COUNTS) L.alive[tid] = 0;
+    auto leave = [&]() {
+        if (tid == 0) {
+            ws.defer[s] = 1;
+            ws.hcnt[s] = 0;
+        }
+        if (tid < SM_COUNTS) ws.scnt[s * SM_COUNTS + tid] = 0;
+        for (int k = tid; k < RE_CAP; k += BS) ws.far[s * RE_CAP + k] = 0;
+    };
+    if (ws.defer) {
+        if (s == 0 && tid < ws.nclaim) ws.claims[tid] = 0;
+        if (n > SM_TRY) return leave();
+        if (tid == 0) ws.defer[s] = 0;
+    }
 
     // Steps 1 and 2
     if (!nofilter) {
@@ -310,14 +331,17 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
                 const uint64_t key = ((uint64_t)((uint32_t)(int32_t)px[u] & 0xFFFFFFu) << 24) |
                                      ((uint32_t)(int32_t)py[u] & 0xFFFFFFu);
                 const uint32_t id = (uint32_t)(a + i0 + u * BS);
-                lkey[o] = key;
-                lidx[o] = id;
+                if (o < SM_CAP) {
+                    lkey[o] = key;
+                    lidx[o] = id;
+                }
             }
             at += __popcll(b[u]);
         }
     }
     __syncthreads();
     const int K = L.nsurv;
+    if (K > SM_CAP) return leave();
 
     // refinement rounds: the survivors' edges, then per round the children of
     // each edge at its farthest point (k_ref_pass on one block)
@@ -575,9 +599,55 @@ __global__ __launch_bounds__(BS) void k_small(const float *__restrict__ x, const
 }
 
 // Several sets after k_small: the hull offsets (S + 1), the sets' hulls moved
-// to their places, and the summed counts.  Every block scans the sizes for
-// the sets it moves (S is at most SM_SETS).
+// to their places, and the summed counts.  Every block (BS threads) scans the
+// sizes for the sets it moves (S is at most SM_SETS).  pre: SM_SETS + 1
+// entries of LDS, sh: BS / 64.
 constexpr int SM_SETS = 2048;
+
+template <int BS>
+__device__ __forceinline__ void small_out(const int64_t *__restrict__ off, int64_t S,
+                                          const uint32_t *__restrict__ hcnt, const int32_t *__restrict__ scnt,
+                                          const uint32_t *__restrict__ tmp, int64_t *__restrict__ hoff,
+                                          uint32_t *__restrict__ hull, int64_t *__restrict__ counts, int64_t *pre,
+                                          int64_t *sh) {
+    constexpr int NW = BS / WAVE;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    int64_t carry = 0;
+    for (int64_t b = 0; b < S; b += BS) {
+        const int64_t s = b + tid;
+        const int64_t c = s < S ? hcnt[s] : 0, inc = wave_incl_scan_i64(c);
+        if (lane == WAVE - 1) sh[w] = inc;
+        __syncthreads();
+        int64_t before = carry;
+#pragma unroll
+        for (int ww = 0; ww < NW; ww++) {
+            before += ww < w ? sh[ww] : 0;
+            carry += sh[ww];
+        }
+        if (s < S) pre[s] = before + inc - c;
+        __syncthreads();
+    }
+    if (tid == 0) pre[S] = carry;
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        for (int64_t s = tid; s <= S; s += BS) hoff[s] = pre[s];
+        for (int r = w; r < SM_COUNTS; r += NW) {
+            int64_t c = 0, none = 0;
+            for (int64_t s = lane; s < S; s += WAVE) {
+                const int32_t v = scnt[s * SM_COUNTS + r];
+                c += v;
+                none |= v < 0;
+            }
+            c = wave_sum_i64(c);
+            if (lane == 0) counts[r] = c;
+            if (__ballot(none) && lane == 0) counts[r] = -1;
+        }
+    }
+    for (int64_t s = (int64_t)blockIdx.x * NW + (tid >> 6); s < S; s += (int64_t)gridDim.x * NW) {
+        const int64_t a = off[s], o = pre[s], h = pre[s + 1] - o;
+        for (int64_t i = lane; i < h; i += WAVE) hull[o + i] = tmp[a + i];
+    }
+}
 
 __global__ __launch_bounds__(256) void k_small_out(const int64_t *__restrict__ off, int64_t S,
                                                    const uint32_t *__restrict__ hcnt,
@@ -587,37 +657,7 @@ __global__ __launch_bounds__(256) void k_small_out(const int64_t *__restrict__ o
                                                    int64_t *__restrict__ counts) {
     __shared__ int64_t sh[5];
     __shared__ int64_t pre[SM_SETS + 1];
-    const int tid = threadIdx.x;
-    int64_t carry = 0;
-    for (int64_t b = 0; b < S; b += 256) {
-        const int64_t s = b + tid;
-        int64_t tot;
-        const int64_t ex = block_excl_scan_i64(s < S ? hcnt[s] : 0, sh, &tot);
-        if (s < S) pre[s] = carry + ex;
-        carry += tot;
-    }
-    if (tid == 0) pre[S] = carry;
-    __syncthreads();
-    if (blockIdx.x == 0) {
-        for (int64_t s = tid; s <= S; s += 256) hoff[s] = pre[s];
-        for (int r = 0; r < SM_COUNTS; r++) {
-            int64_t c = 0, none = 0;
-            for (int64_t s = tid; s < S; s += 256) {
-                const int32_t v = scnt[s * SM_COUNTS + r];
-                c += v;
-                none |= v < 0;
-            }
-            int64_t tot, totn;
-            block_excl_scan_i64(c, sh, &tot);
-            block_excl_scan_i64(none, sh, &totn);
-            if (tid == 0) counts[r] = totn ? -1 : tot;
-        }
-    }
-    const int lane = lane_id();
-    for (int64_t s = (int64_t)blockIdx.x * 4 + (tid >> 6); s < S; s += (int64_t)gridDim.x * 4) {
-        const int64_t a = off[s], o = pre[s], h = pre[s + 1] - o;
-        for (int64_t i = lane; i < h; i += WAVE) hull[o + i] = tmp[a + i];
-    }
+    small_out<256>(off, S, hcnt, scnt, tmp, hoff, hull, counts, pre, sh);
 }
 
 }  // namespace hg
