@@ -1745,8 +1745,8 @@ static int run_learned_dirs(hull_ctx *ctx, const Plan &p, hipStream_t st, const 
 // 16 KiB per set (two tiles of list entries), 16 partials of 64 directions.
 static_assert(LAB_SPLIT * NCAND * sizeof(CandPart) <= 2 * TILE * 8, "the partials fit the chain's buffer");
 static int run_cand_extremes(hull_ctx *ctx, const Plan &p, hipStream_t st, const float *x, const float *y,
-                             int64_t S) {
-    const unsigned split = lab_split(S, ctx->cus);
+                             int64_t S, int64_t n_total) {
+    const unsigned split = lab_split(S, n_total, ctx->cus);
     auto *part = W<CandPart>(p, p.lo0);
     LAUNCH(K_LABELS, k_cand_extremes<<<dim3((unsigned)S, split), LAB_THREADS, 0, st>>>(
         x, y, W<Poly>(p, p.polys), W<uint32_t>(p, p.surv), W<int64_t>(p, p.surv_off), part));
@@ -1914,9 +1914,9 @@ int hull_labels_batched(hull_ctx *ctx, const float *x, const float *y, const int
     uint32_t *surv = W<uint32_t>(p, p.surv);
     int64_t *so = W<int64_t>(p, p.surv_off);
     RC(run_discard(ctx, p, st, x, y, n_total, offsets, 0, S, slot_count(ctx, false), surv, so, nullptr));
-    RC(run_cand_extremes(ctx, p, st, x, y, S));
+    RC(run_cand_extremes(ctx, p, st, x, y, S, n_total));
     uint32_t *cand = W<uint32_t>(p, p.cand), *cnt = W<uint32_t>(p, p.up0);
-    LAUNCH(K_LABELS, k_labels<<<dim3((unsigned)S, lab_split(S, ctx->cus)), LAB_THREADS, 0, st>>>(
+    LAUNCH(K_LABELS, k_labels<<<dim3((unsigned)S, lab_split(S, n_total, ctx->cus)), LAB_THREADS, 0, st>>>(
         x, y, W<Poly>(p, p.polys), cand, surv, so, cnt));
     LAUNCH(K_LABELS, k_label_gain<<<(unsigned)((S * NCAND + 255) / 256), 256, 0, st>>>(offsets, 0, S, cnt,
                                                                                        gain));
@@ -1940,7 +1940,7 @@ int hull_label_targets_batched(hull_ctx *ctx, const float *x, const float *y,
     uint32_t *surv = W<uint32_t>(p, p.surv);
     int64_t *so = W<int64_t>(p, p.surv_off);
     RC(run_discard(ctx, p, st, x, y, n_total, offsets, 0, S, slot_count(ctx, false), surv, so, nullptr));
-    RC(run_cand_extremes(ctx, p, st, x, y, S));
+    RC(run_cand_extremes(ctx, p, st, x, y, S, n_total));
     LAUNCH(K_LABELS, k_label_targets<<<(unsigned)S, 256, 0, st>>>(
         x, y, offsets, 0, S, W<Poly>(p, p.polys), W<uint32_t>(p, p.cand), surv, so, rounds, target, order));
     return HULL_OK;

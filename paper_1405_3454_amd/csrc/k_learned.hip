@@ -458,10 +458,15 @@ constexpr int LAB_BINS = LAB_THREADS / FIXED_SLOTS;   // height bins along a bas
 // factor of ten and with fewer most CUs wait for a few (256 sets, both passes:
 // 274, 250, 208 and 253 us with three, four, eight and sixteen per CU); more
 // sets than that have one each.
+// More blocks than CUs have at least LAB_POINTS points of a set of mean size
+// each, since each sets up the directions (300 sets of 1000 points: labels 171
+// us with seven blocks each, 134 with one).
 constexpr int LAB_BLOCKS_PER_CU = 8;
-static unsigned lab_split(int64_t S, int cus) {
-    const int64_t k = (LAB_BLOCKS_PER_CU * (int64_t)cus + S - 1) / S;
-    return (unsigned)(k < 1 ? 1 : k > LAB_SPLIT ? LAB_SPLIT : k);
+constexpr int64_t LAB_POINTS = 2048;
+static unsigned lab_split(int64_t S, int64_t n_total, int cus) {
+    const int64_t k = (LAB_BLOCKS_PER_CU * (int64_t)cus + S - 1) / S,
+                  most = std::max<int64_t>(n_total / (S * LAB_POINTS), cus / S);
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(std::min(k, most), LAB_SPLIT));
 }
 
 // Partial extreme of one direction over a block's share of a set.
@@ -622,9 +627,10 @@ __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
 //     The block shares one best value per direction, raised by an LDS maximum
 //     and started at the best base vertex; a survivor that reaches the best
 //     when it is seen is noted in a list, from which the lowest index of each
-//     final best is taken.  Should the list run over (thousands of copies of
-//     an extreme point), the survivors are walked once more for it.  A best
-//     per wave, found with cross-lane reductions, took as long.
+//     final best is taken (a vertex has the lowest of its copies; of a wave's
+//     ties only the lowest index is noted).  Should the list run over, the
+//     survivors are walked once more for it.  A best per wave, found with
+//     cross-lane reductions, took as long.
 //     A thin set's long edges end at vertices that are extreme along most of
 //     the directions, so their class (most of the survivors) visits them all.
 //     There a height per bin of the edge leaves out the survivors that stay
@@ -632,6 +638,13 @@ __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
 //     arithmetic errs by less than 2^-50): of the class, few remain.  The
 //     heights are taken at the start, after the first 512 survivors of a
 //     block and whenever the chunks done are four times as many.
+//     Of points on the segment of a two-vertex polygon only the ends can be
+//     extreme, but for the directions that the segment is nearly perpendicular
+//     to: with the ends' values 2^-25 apart, two grid points of the segment (at
+//     most 2^24 steps) are 2^-49 apart, more than the roundings.  Points that
+//     are all one point need no walk.  (Visited as others, 256 sets of 65536
+//     such points took 2.0 ms on a line and 8.5 ms in one place; 1.6 and 1.7
+//     with the former walk of every point; now 0.5 and 0.35.)
 __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     const float *__restrict__ x, const float *__restrict__ y, const Poly *__restrict__ polys,
     const uint32_t *__restrict__ surv, const int64_t *__restrict__ surv_off, CandPart *__restrict__ part) {
@@ -639,6 +652,9 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     __shared__ uint64_t dirs[LAB_CLASSES];
     __shared__ double bv[NCAND];                      // best value, and its lowest index
     __shared__ uint32_t bi[NCAND];
+    __shared__ double vv[NCAND];                      // the best vertex's value and index
+    __shared__ uint32_t vi[NCAND];
+    __shared__ uint64_t flat;                         // two vertices: directions across the segment
     __shared__ double cc[NCAND], ss[NCAND];
     __shared__ double nv[LAB_NOTES];                  // noted survivors: value, index, direction
     __shared__ uint32_t ni[LAB_NOTES];
@@ -649,22 +665,40 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     const int64_t s = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
     const Poly &P = polys[s];
+    CandPart *mine = part + (s * gridDim.y + blockIdx.y) * NCAND;
+    if (P.m < 2) {
+        if (tid < NCAND) mine[tid] = CandPart{0.0, P.m == 1 && blockIdx.y == 0 ? P.verts[0] : NONE, 0};
+        return;
+    }
     const int m = E.load(P);
     if (w == 0) {
         const int d = lane;
+        double first = -INFINITY;
         cc[d] = dCandCos[d];
         ss[d] = dCandSin[d];
-        double best = -INFINITY;
-        for (int k = 0; k < m; k++)
-            best = fmax(best, proj_dir(cc[d], ss[d], P.vx[k] * (1.0 / GRIDD), P.vy[k] * (1.0 / GRIDD)));
+        uint32_t id = NONE;
+        double v0 = 0, v1 = 0;
+        for (int k = 0; k < m; k++) {
+            const double v = proj_dir(cc[d], ss[d], P.vx[k] * (1.0 / GRIDD), P.vy[k] * (1.0 / GRIDD));
+            const uint32_t q = P.verts[k];
+            if (k == 0) v0 = v;
+            if (k == 1) v1 = v;
+            const bool t = (int)(v > first) | ((int)(v == first) & (int)(q < id));
+            first = t ? v : first;
+            id = t ? q : id;
+        }
         uint32_t edges = 0;
         for (int k = 0; k < m; k++) {
             const double v = proj_dir(cc[d], ss[d], P.vx[k] * (1.0 / GRIDD), P.vy[k] * (1.0 / GRIDD));
-            if (v >= best - 0x1p-40) edges |= (1u << k) | (1u << (k ? k - 1 : m - 1));
+            if (v >= first - 0x1p-40) edges |= (1u << k) | (1u << (k ? k - 1 : m - 1));
         }
-        bv[d] = best;
-        bi[d] = NONE;
-        if (d == 0) notes = 0;
+        bv[d] = vv[d] = first;
+        bi[d] = vi[d] = id;
+        const uint64_t f = __ballot(fabs(v0 - v1) <= 0x1p-25);
+        if (d == 0) {
+            flat = f;
+            notes = 0;
+        }
         for (int c = 0; c < LAB_CLASSES; c++) {
             const uint64_t b = __ballot((edges >> c) & 1);
             if (lane == 0) dirs[c] = b;
@@ -699,15 +733,16 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     };
     // walk(f): f(direction, value, index, lane in use) for the survivors of
     // the block's share that can matter and the directions of their class
+    const bool tall = bb - ba > LAB_THREADS;          // few survivors are walked sooner than heights are made
     auto walk = [&](bool refresh, auto &&f) {
         int64_t done = 0, next = 0;
         for (int64_t c0 = ba, c1; c0 < bb; c0 = c1, done++) {
             c1 = min(bb, c0 + (c0 == ba ? LAB_THREADS : LAB_CHUNK));
-            if (refresh && done == next) {
+            if (refresh && tall && done == next) {
                 heights();
                 next = next ? next * 4 : 1;
             }
-            lab_chunk(L, x, y, surv, c0, c1, E, m, &H);
+            lab_chunk(L, x, y, surv, c0, c1, E, m, tall ? &H : nullptr);
             int cls, at, len;
             for (int b = w; lab_batch(L, b, &cls, &at, &len); b += LAB_WAVES) {
                 const bool has = lane < len;
@@ -715,8 +750,8 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
                 const double xd = L.x[i], yd = L.y[i];
                 const uint32_t id = L.id[i];
                 uint64_t dm;
-                if (m == 0) dm = ~uint64_t(0);
-                else if (cls < FIXED_SLOTS) dm = uniform_u64(dirs[cls]);
+                if (cls < FIXED_SLOTS) dm = uniform_u64(dirs[cls]);
+                else if (m == 2) dm = uniform_u64(flat);
                 else {
                     dm = 0;
                     for (uint32_t o = L.out[i]; o; o &= o - 1) dm |= dirs[__ffs((int)o) - 1];
@@ -733,6 +768,15 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
     walk(true, [&](int d, double v, uint32_t id, bool has) {
         bool hit = has && v >= bv[d];
         if (!__ballot(hit)) return;
+        hit = hit && !(v == vv[d] && id >= vi[d]);    // the vertex, its copies, and ties behind it
+        const uint64_t any = __ballot(hit);
+        if (!any) return;
+        if (any & (any - 1)) {                        // of several the best, of ties the lowest
+            const double most = wave_extreme<false>(hit ? v : -INFINITY);
+            hit = hit && v == most;
+            const uint32_t low = wave_min_u32(hit ? id : NONE);
+            hit = hit && id == low;
+        }
         if (hit) atomicMax(&bv[d], v);
         wave_sync();
         hit = hit && v >= bv[d];
@@ -747,18 +791,19 @@ __global__ __launch_bounds__(LAB_THREADS) void k_cand_extremes(
         }
     });
     __syncthreads();
+    if (tid < NCAND && bv[tid] > vv[tid]) bi[tid] = NONE;        // a survivor beyond every vertex
+    __syncthreads();
     if (notes <= LAB_NOTES) {
         for (uint32_t i = tid; i < notes; i += LAB_THREADS)
             if (nv[i] == bv[nd[i]]) atomicMin(&bi[nd[i]], ni[i]);
     } else {
-        heights();
+        if (tall) heights();
         walk(false, [&](int d, double v, uint32_t id, bool has) {
             if (has && v == bv[d]) atomicMin(&bi[d], id);
         });
     }
     __syncthreads();
-    // a block whose share does not reach the best base vertex reports none
-    if (tid < NCAND) part[(s * gridDim.y + blockIdx.y) * NCAND + tid] = CandPart{bv[tid], bi[tid], 0};
+    if (tid < NCAND) mine[tid] = CandPart{bv[tid], bi[tid], 0};
 }
 
 // The extreme of each direction from a set's partials (NONE for an empty
@@ -833,7 +878,7 @@ __global__ __launch_bounds__(LAB_THREADS) void k_labels(
             if (lane == 0) dirs[c] = b;
         }
     }
-    const int64_t sa = surv_off[s], sb = surv_off[s + 1];
+    const int64_t sa = surv_off[s], sb = m ? surv_off[s + 1] : sa;
     uint32_t mine = 0;                                // lane d: the wave's count for direction d
     for (int64_t c0 = sa + (int64_t)blockIdx.y * LAB_CHUNK; c0 < sb; c0 += (int64_t)gridDim.y * LAB_CHUNK) {
         lab_chunk(L, x, y, surv, c0, min(sb, c0 + LAB_CHUNK), E, m, nullptr);
@@ -842,7 +887,7 @@ __global__ __launch_bounds__(LAB_THREADS) void k_labels(
             const bool has = lane < len;
             const int i = at + min(lane, len - 1);
             const double px = (double)L.x[i] * GRIDD, py = (double)L.y[i] * GRIDD;
-            uint64_t lm = m ? ~uint64_t(0) : 0;       // the lane's directions
+            uint64_t lm = ~uint64_t(0);               // the lane's directions
             if (cls < FIXED_SLOTS) lm = dirs[cls];
             else
                 for (uint32_t o = L.out[i]; o; o &= o - 1) lm &= dirs[__ffs((int)o) - 1];
