@@ -1599,9 +1599,16 @@ int hull_timing_reset(hull_ctx *ctx) {
 // labels.  Weight matrices in bf16, activations in bf16, accumulation and
 // the master copy of the parameters in float32.
 
+// Rows of the products for a batch of B: whole 64-row tiles, 128-row ones for
+// batches large enough to be cut into those.
+static int64_t padded_rows(int64_t B) {
+    const int64_t unit = B >= 4096 ? 128 : 64;
+    return std::max<int64_t>(64, (B + unit - 1) / unit * unit);
+}
+
 static int learned_ensure(hull_ctx *ctx, int64_t B, hipStream_t st) {
     LearnedState &L = ctx->learned;
-    const int64_t Bp = std::max<int64_t>(64, (B + 63) / 64 * 64);
+    const int64_t Bp = padded_rows(B);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (!L.params || Bp > L.bcap) {
         HIPCHECK(hipStreamIsCapturing(st, &cs));
@@ -1648,7 +1655,13 @@ static int gemm(hull_ctx *ctx, hipStream_t st, const GemmJob &a, const GemmJob *
         if (J.j[i].K % GKS) return HULL_EINVAL;
         tiles += J.j[i].tm * J.j[i].tn;
     }
-    LAUNCH(K_MLP, k_gemm<<<tiles, 256, 0, st>>>(J));
+    // the largest tiles that still give every CU a block (forward passes of
+    // 2048 sets 47 us with 64 x 64 tiles and 64 with 32 x 32, of 1000, where
+    // they are too few, 46 and 43)
+    if (!b && tiles / 16 >= ctx->cus && a.tm % 4 == 0 && a.tn % 4 == 0)
+        LAUNCH(K_MLP, k_gemm<4><<<tiles / 16, 256, 0, st>>>(J));
+    else if (!b && tiles / 4 >= ctx->cus) LAUNCH(K_MLP, k_gemm<2><<<tiles / 4, 256, 0, st>>>(J));
+    else LAUNCH(K_MLP, k_gemm<1><<<tiles, 256, 0, st>>>(J));
     return HULL_OK;
 }
 
@@ -1657,8 +1670,6 @@ static int gemm(hull_ctx *ctx, hipStream_t st, const GemmJob &a, const GemmJob *
         int rc_ = (expr);        \
         if (rc_) return rc_;     \
     } while (0)
-
-static int padded_rows(int64_t B) { return (int)std::max<int64_t>(64, (B + 63) / 64 * 64); }
 
 // The network's input as the products read it: hist itself, or a copy where
 // it is not 16-byte aligned.
@@ -1672,17 +1683,18 @@ static int mlp_input(hull_ctx *ctx, hipStream_t st, const bf16_t *hist, int64_t 
     return HULL_OK;
 }
 
-// scores (float32 [B][64]) of the histogram rows X[B][1024]
-static int mlp_forward(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B, float *scores) {
+// scores (float32 [B][64]) of the histogram rows X[B][1024]; transposes: with
+// those of the activations, which the backward pass reads
+static int mlp_forward(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B, float *scores, bool transposes) {
     LearnedState &L = ctx->learned;
-    const int Bp = padded_rows(B), tb = Bp / GT;
+    const int Bp = (int)padded_rows(B), tb = Bp / GT;
     GemmJob g{};
     g.A = X; g.lda = HBINS; g.B = L.wb + Q_W1; g.ldb = HBINS; g.K = HBINS;
     g.tm = tb; g.tn = L1 / GT; g.mode = G_RELU_BF16; g.arows = (int)B;
-    g.bias = L.params + P_B1; g.Cb = L.H1; g.CT = L.H1T;
+    g.bias = L.params + P_B1; g.Cb = L.H1; g.CT = transposes ? L.H1T : nullptr;
     RC(gemm(ctx, st, g));
     g.A = L.H1; g.lda = L1; g.B = L.wb + Q_W2; g.ldb = L1; g.K = L1; g.tn = L2 / GT; g.arows = Bp;
-    g.bias = L.params + P_B2; g.Cb = L.H2; g.CT = L.H2T;
+    g.bias = L.params + P_B2; g.Cb = L.H2; g.CT = transposes ? L.H2T : nullptr;
     RC(gemm(ctx, st, g));
     g.A = L.H2; g.lda = L2; g.B = L.wb + Q_W3; g.ldb = L2; g.K = L2; g.tn = NOUT / GT; g.mode = G_BIAS_F32;
     g.bias = L.params + P_B3; g.Cb = g.CT = nullptr; g.Cf = scores; g.crows = (int)B;
@@ -1694,7 +1706,7 @@ static int mlp_forward(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B
 // forward pass; products that do not need each other share a launch
 static int mlp_backward(hull_ctx *ctx, hipStream_t st, int64_t B, float *grads) {
     LearnedState &L = ctx->learned;
-    const int Bp = padded_rows(B), tb = Bp / GT;
+    const int Bp = (int)padded_rows(B), tb = Bp / GT;
     GemmJob w{}, z{};
     w.mode = G_F32;
     z.mode = G_MASK_BF16;
@@ -1718,7 +1730,7 @@ static int mlp_backward(hull_ctx *ctx, hipStream_t st, int64_t B, float *grads) 
 // the transposes the backward pass reads (dscores: also dS from it)
 static int mlp_backward_prep(hull_ctx *ctx, hipStream_t st, const bf16_t *X, int64_t B, const float *dscores) {
     LearnedState &L = ctx->learned;
-    const int Bp = padded_rows(B);
+    const int Bp = (int)padded_rows(B);
     LAUNCH(K_MLP, k_backward_prep<<<dim3(HBINS / 64 + (dscores ? 1 : 0), Bp / 64), 256, 0, st>>>(
         X, B, Bp, L.XT, dscores, L.dS, L.dST));
     return HULL_OK;
@@ -1733,7 +1745,7 @@ static int run_learned_dirs(hull_ctx *ctx, const Plan &p, hipStream_t st, const 
     LAUNCH(K_HIST32, k_hist32<<<(unsigned)S, HIST_THREADS, 0, st>>>(x, y, off, n1, S, hist, nullptr));
     const bf16_t *X = nullptr;
     RC(mlp_input(ctx, st, hist, S, &X));
-    RC(mlp_forward(ctx, st, X, S, ctx->learned.scores));
+    RC(mlp_forward(ctx, st, X, S, ctx->learned.scores, false));
     LAUNCH(K_MLP, k_top8<<<(unsigned)((S + 3) / 4), 256, 0, st>>>(ctx->learned.scores, S, ctx->dir_gap, nullptr,
                                                                  W<double>(p, p.setdirs)));
     return HULL_OK;
@@ -1842,7 +1854,7 @@ int hull_mlp_forward(hull_ctx *ctx, const uint16_t *hist, int64_t B, float *scor
     HIPCHECK(hipSetDevice(ctx->device));
     const bf16_t *X = nullptr;
     RC(mlp_input(ctx, st, hist, B, &X));
-    return mlp_forward(ctx, st, X, B, scores);
+    return mlp_forward(ctx, st, X, B, scores, false);
 }
 
 int hull_mlp_backward(hull_ctx *ctx, const uint16_t *hist, const float *dscores, int64_t B,
@@ -1853,7 +1865,7 @@ int hull_mlp_backward(hull_ctx *ctx, const uint16_t *hist, const float *dscores,
     HIPCHECK(hipSetDevice(ctx->device));
     const bf16_t *X = nullptr;
     RC(mlp_input(ctx, st, hist, B, &X));
-    RC(mlp_forward(ctx, st, X, B, ctx->learned.scores));
+    RC(mlp_forward(ctx, st, X, B, ctx->learned.scores, true));
     RC(mlp_backward_prep(ctx, st, X, B, dscores));
     return mlp_backward(ctx, st, B, grads);
 }
@@ -1867,8 +1879,8 @@ int hull_mlp_train_step(hull_ctx *ctx, const uint16_t *hist, const float *gain, 
     const bf16_t *X = nullptr;
     RC(mlp_input(ctx, st, hist, B, &X));
     LearnedState &L = ctx->learned;
-    RC(mlp_forward(ctx, st, X, B, L.scores));
-    const int Bp = padded_rows(B);
+    RC(mlp_forward(ctx, st, X, B, L.scores, true));
+    const int Bp = (int)padded_rows(B);
     LAUNCH(K_MLP, k_loss<<<(unsigned)Bp, 64, 0, st>>>(L.scores, gain, B, Bp, L.dS, L.dST, L.part));
     LAUNCH(K_MLP, k_loss_sum<<<1, 64, 0, st>>>(L.part, B, loss));
     RC(mlp_backward_prep(ctx, st, X, B, nullptr));

@@ -165,9 +165,9 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist32(const float *__restrict
 // ---------------------------------------------------------------------------
 // The network's products: C[M x N] = A[M x K] * B[N x K]^T in bf16 on MFMA
 // (16x16x32), fp32 accumulation; A and B with K along their rows (row strides
-// lda, ldb), M and N multiples of 32, K of 32.  A block makes a 32 x 32 tile,
-// each of its four waves a 16 x 16 one over the whole of K, step by step into
-// one accumulator (the results are rounded to bf16 for the next layer, so the
+// lda, ldb), M and N multiples of 64, K of 32.  A block makes a 32 R x 32 R
+// tile, each of its four waves a 16 R x 16 R one over the whole of K, step by
+// step into one accumulator each (the results are rounded to bf16 for the next layer, so the
 // order of the sums is kept), with the operands loaded straight into the
 // lanes that feed them to MFMA, eight steps ahead.  The products here are
 // small (512 x 512 x 1024 at a batch of 512), so what bounds them is the
@@ -176,7 +176,10 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist32(const float *__restrict
 // latency, and independent products share a launch.  (64 x 64 tiles with K
 // staged through LDS 32 at a time, one product a launch, took 17 us for the
 // first layer; forward, then forward and backward, with their helpers at a
-// batch of 512: 320 us, now 88 us.)
+// batch of 512: 320 us, now 88 us.)  With R = 2 or 4 each operand is read half
+// or a quarter as often, which is what bounds products of many tiles: the
+// forward pass of 20000 sets took 453 us with R = 1 (234 with those tiles),
+// 255 with R = 2, now 186.
 enum GemmMode { G_RELU_BF16 = 0, G_BIAS_F32 = 1, G_MASK_BF16 = 2, G_F32 = 3 };
 constexpr int GT = 32;                       // tile side
 constexpr int GKS = 32;                      // K per MFMA step
@@ -200,90 +203,119 @@ struct GemmJobs {
     int n;
 };
 
+template <int R>
 __global__ __launch_bounds__(256) void k_gemm(GemmJobs jobs) {
-    constexpr int TP = GT + 4;
-    __shared__ __attribute__((aligned(8))) uint16_t tile16[GT * TP];
+    constexpr int TS = GT * R, TP = TS + 4, AHEAD = GAHEAD / R;
+    __shared__ __attribute__((aligned(8))) uint16_t tile16[TS * TP];
     int tile = blockIdx.x;
-    const int first = jobs.j[0].tm * jobs.j[0].tn;
+    const int first = jobs.j[0].tm / R * (jobs.j[0].tn / R);
     const bool second = tile >= first;
     if (second) tile -= first;
     const GemmJob &J = jobs.j[second ? 1 : 0];
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m0 = tile / J.tn * GT, n0 = tile % J.tn * GT;
-    const int wm = (w >> 1) * 16, wn = (w & 1) * 16;
+    const int m0 = tile / (J.tn / R) * TS, n0 = tile % (J.tn / R) * TS;
+    const int wm = (w >> 1) * 16 * R, wn = (w & 1) * 16 * R;
     const int steps = J.K / GKS;
     const int r = lane & 15, k8 = (lane >> 4) * 8;
     const bool sums = J.asum && n0 + wn == 0;
-    float as = 0.f;
-    const bool live = m0 + wm + r < J.arows;
-    const bf16_t *pa = J.A + (int64_t)(live ? m0 + wm + r : 0) * J.lda + k8;
-    const bf16_t *pb = J.B + (int64_t)(n0 + wn + r) * J.ldb + k8;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 a[2][GAHEAD], b[2][GAHEAD];
-    auto load = [&](int s0, bf16x8 *va, bf16x8 *vb) {
+    float as[R];
+    bool live[R];
+    const bf16_t *pa[R], *pb[R];
+    f32x4 acc[R][R];
 #pragma unroll
-        for (int d = 0; d < GAHEAD; d++) {
+    for (int i = 0; i < R; i++) {
+        const int row = m0 + wm + 16 * i + r;
+        as[i] = 0.f;
+        live[i] = row < J.arows;
+        pa[i] = J.A + (int64_t)(live[i] ? row : 0) * J.lda + k8;
+        pb[i] = J.B + (int64_t)(n0 + wn + 16 * i + r) * J.ldb + k8;
+#pragma unroll
+        for (int j = 0; j < R; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 a[2][AHEAD][R], b[2][AHEAD][R];
+    auto load = [&](int s0, bf16x8 (*va)[R], bf16x8 (*vb)[R]) {
+#pragma unroll
+        for (int d = 0; d < AHEAD; d++) {
             const int k = min(s0 + d, steps - 1) * GKS;      // past the end: the last step again
-            va[d] = *reinterpret_cast<const bf16x8 *>(pa + k);
-            vb[d] = *reinterpret_cast<const bf16x8 *>(pb + k);
+#pragma unroll
+            for (int i = 0; i < R; i++) {
+                va[d][i] = *reinterpret_cast<const bf16x8 *>(pa[i] + k);
+                vb[d][i] = *reinterpret_cast<const bf16x8 *>(pb[i] + k);
+            }
         }
     };
-    auto multiply = [&](int s0, const bf16x8 *va, const bf16x8 *vb) {
+    auto multiply = [&](int s0, bf16x8 (*va)[R], bf16x8 (*vb)[R]) {
 #pragma unroll
-        for (int d = 0; d < GAHEAD; d++) {
+        for (int d = 0; d < AHEAD; d++) {
             if (s0 + d >= steps) break;
-            const bf16x8 av = live ? va[d] : bf16x8{};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, vb[d], acc, 0, 0, 0);
-            if (sums)
 #pragma unroll
-                for (int t = 0; t < 8; t++) as += (float)av[t];
+            for (int i = 0; i < R; i++) {
+                const bf16x8 av = live[i] ? va[d][i] : bf16x8{};
+#pragma unroll
+                for (int j = 0; j < R; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, vb[d][j], acc[i][j], 0, 0, 0);
+                if (sums)
+#pragma unroll
+                    for (int t = 0; t < 8; t++) as[i] += (float)av[t];
+            }
         }
     };
     load(0, a[0], b[0]);
-    for (int s0 = 0; s0 < steps; s0 += 2 * GAHEAD) {
-        if (s0 + GAHEAD < steps) load(s0 + GAHEAD, a[1], b[1]);
+    for (int s0 = 0; s0 < steps; s0 += 2 * AHEAD) {
+        if (s0 + AHEAD < steps) load(s0 + AHEAD, a[1], b[1]);
         multiply(s0, a[0], b[0]);
-        if (s0 + GAHEAD >= steps) break;
-        if (s0 + 2 * GAHEAD < steps) load(s0 + 2 * GAHEAD, a[0], b[0]);
-        multiply(s0 + GAHEAD, a[1], b[1]);
+        if (s0 + AHEAD >= steps) break;
+        if (s0 + 2 * AHEAD < steps) load(s0 + 2 * AHEAD, a[0], b[0]);
+        multiply(s0 + AHEAD, a[1], b[1]);
     }
-    if (sums) {
-        as += __shfl_xor(as, 16);
-        as += __shfl_xor(as, 32);
-        if (lane < 16) J.asum[m0 + wm + lane] = as;
-    }
-    // lane: column n0 + n, rows m0 + m .. m0 + m + 3
-    const int n = wn + r, m = wm + (lane >> 4) * 4;
+    if (sums)
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            as[i] += __shfl_xor(as[i], 16);
+            as[i] += __shfl_xor(as[i], 32);
+            if (lane < 16) J.asum[m0 + wm + 16 * i + lane] = as[i];
+        }
     const int ldc = J.tn * GT;
-    const int64_t o = (int64_t)(m0 + m) * ldc + n0 + n;
-    float v[4] = {acc[0], acc[1], acc[2], acc[3]};
-    if (J.mode == G_RELU_BF16 || J.mode == G_BIAS_F32) {
-        const float bias = J.bias[n0 + n];
 #pragma unroll
-        for (int q = 0; q < 4; q++) v[q] += bias;
-    }
-    if (J.mode == G_BIAS_F32 || J.mode == G_F32) {
+    for (int i = 0; i < R; i++)
 #pragma unroll
-        for (int q = 0; q < 4; q++)
-            if (m0 + m + q < J.crows) J.Cf[o + (int64_t)q * ldc] = v[q];
-        return;
-    }
-    uint16_t c[4];
+        for (int j = 0; j < R; j++) {
+            // lane: column n0 + n, rows m0 + m .. m0 + m + 3
+            const int n = wn + 16 * j + r, m = wm + 16 * i + (lane >> 4) * 4;
+            const int64_t o = (int64_t)(m0 + m) * ldc + n0 + n;
+            float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+            if (J.mode == G_RELU_BF16 || J.mode == G_BIAS_F32) {
+                const float bias = J.bias[n0 + n];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        if (J.mode == G_RELU_BF16) c[q] = f2bf(fmaxf(v[q], 0.0f));
-        else c[q] = bf2f(J.mask[o + (int64_t)q * ldc]) > 0.0f ? f2bf(v[q]) : (uint16_t)0;
-    }
-    if (J.CT)
-        *reinterpret_cast<ushort4 *>(J.CT + (int64_t)(n0 + n) * (J.tm * GT) + m0 + m) =
-            make_ushort4(c[0], c[1], c[2], c[3]);
-    if (!J.Cb) return;
+                for (int q = 0; q < 4; q++) v[q] += bias;
+            }
+            if (J.mode == G_BIAS_F32 || J.mode == G_F32) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) tile16[(m + q) * TP + n] = c[q];
+                for (int q = 0; q < 4; q++)
+                    if (m0 + m + q < J.crows) J.Cf[o + (int64_t)q * ldc] = v[q];
+                continue;
+            }
+            uint16_t c[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                if (J.mode == G_RELU_BF16) c[q] = f2bf(fmaxf(v[q], 0.0f));
+                else c[q] = bf2f(J.mask[o + (int64_t)q * ldc]) > 0.0f ? f2bf(v[q]) : (uint16_t)0;
+            }
+            if (J.CT)
+                *reinterpret_cast<ushort4 *>(J.CT + (int64_t)(n0 + n) * (J.tm * GT) + m0 + m) =
+                    make_ushort4(c[0], c[1], c[2], c[3]);
+            if (J.Cb)
+#pragma unroll
+                for (int q = 0; q < 4; q++) tile16[(m + q) * TP + n] = c[q];
+        }
+    if (J.mode == G_BIAS_F32 || J.mode == G_F32 || !J.Cb) return;
     __syncthreads();
-    const int tr = tid >> 3, tc = (tid & 7) * 4;         // four neighbours of one row per thread
-    *reinterpret_cast<ushort4 *>(J.Cb + (int64_t)(m0 + tr) * ldc + n0 + tc) =
-        *reinterpret_cast<const ushort4 *>(&tile16[tr * TP + tc]);
+#pragma unroll
+    for (int e = tid * 4; e < TS * TS; e += 256 * 4) {       // four neighbours of one row per thread
+        const int tr = e / TS, tc = e % TS;
+        *reinterpret_cast<ushort4 *>(J.Cb + (int64_t)(m0 + tr) * ldc + n0 + tc) =
+            *reinterpret_cast<const ushort4 *>(&tile16[tr * TP + tc]);
+    }
 }
 
 // float32 -> bf16 copy (weights after an update, or inputs); with cols > 0

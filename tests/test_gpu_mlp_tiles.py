@@ -1,6 +1,7 @@
 """The network's products tile by tile: every 16 x 16 tile of the scores and of
 the weight gradients, and every 16 entries of the bias gradients, so that one
-tile left out, repeated or misplaced shows.
+tile left out, repeated or misplaced shows; at batches whose products take
+tiles of 32, 64 and 128 rows a block.
 
 The reference rounds where the kernels do (bf16 weights, activations, hidden
 and output gradients), in binary64 otherwise.  What is left between them is
@@ -40,7 +41,7 @@ def _check(got, want, what):
     assert not bad.any(), (what, bad.nonzero()[:8].tolist(), int(bad.sum()))
 
 
-@pytest.mark.parametrize("B", [1, 31, 64, 65, 200, 512])
+@pytest.mark.parametrize("B", [1, 31, 64, 65, 200, 512, 2049, 4097, 8200])
 def test_every_tile(B):
     import torch
     from paper_1405_3454_amd import train
