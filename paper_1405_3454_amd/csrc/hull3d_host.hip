@@ -74,7 +74,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o += al(bytes); return r; };
     const size_t a_pval = take(W3 * S3 * 8), a_pidx = take(W3 * S3 * 4), a_poly = take(sizeof(Poly3)),
-                 a_ctl = take(sizeof(Hull3Ctl)), a_cnt = take(8);
+                 a_ctl = take(sizeof(Hull3Ctl)), a_cnt = take(16);
     if ((rc = grow(&B->a, &B->acap, o))) return rc;
     double *pval = reinterpret_cast<double *>(B->a + a_pval);
     uint32_t *pidx = reinterpret_cast<uint32_t *>(B->a + a_pidx);
@@ -91,7 +91,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         LAUNCH(K_EXTREMES, (k3_extremes<1><<<g3, 256, 0, st>>>(x, y, z, n, d, pval, pidx)));
         LAUNCH(K_POLYGON, k3_slots<<<1, 1024, 0, st>>>(x, y, z, W3, pval, pidx, slots, poly));
         LAUNCH(K_POLYGON, k3_planes<<<(TRIPLES3 + 255) / 256, 256, 0, st>>>(poly));
-        LAUNCH(K_POLYGON, k3_poly<<<1, 1024, 0, st>>>(poly));
+        LAUNCH(K_POLYGON, k3_poly<<<1, 1024, 0, st>>>(poly, scount + 1));
         const unsigned gd = (unsigned)(ctx->cus * 4);
         LAUNCH(K_DISCARD, k3_discard<<<gd, 256, 0, st>>>(x, y, z, n, poly, W<uint64_t>(p, p.masks),
                                                         W<uint32_t>(p, p.tile_cnt)));
@@ -110,14 +110,16 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         LAUNCH(K_MISC, k_fill_i64<<<1, 64, 0, st>>>(scount, 1, n));
     }
     if (n_surv) LAUNCH(K_MISC, k_copy_count<<<1, 64, 0, st>>>(scount, n_surv));
-    int64_t nc = 0;
-    HIPCHECK(hipMemcpyAsync(&nc, scount, 8, hipMemcpyDeviceToHost, st));
+    int64_t seen[2] = {0, 0};
+    HIPCHECK(hipMemcpyAsync(seen, scount, nofilter ? 8 : 16, hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st));
+    int64_t nc = seen[0];
+    const bool star = seen[1];               // the polyhedron's ball is wide enough for the reduction
 
     // Step 4.  Many candidates: those inside tetrahedra of far points go first
     const uint32_t *cidx = sv;               // the candidates' indices
     const float4 *cpts = nullptr;            // and coordinates, where they are at hand
-    if (!nofilter && nc >= STAR_MIN) {
+    if (star && nc >= STAR_MIN) {
         // in the workspace, whose chain lists and candidate lists (16 bytes a
         // point twice, 4, and 8 for the cells) are idle until the final sort
         const int side = star_side(nc), ncell = star_cells(side);
@@ -133,11 +135,9 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         int64_t nk = 0;
         HIPCHECK(hipMemcpyAsync(&nk, cells + ncell, 8, hipMemcpyDeviceToHost, st));
         HIPCHECK(hipStreamSynchronize(st));
-        if (nk < nc) {                       // (a set without an interior keeps all of them)
-            nc = nk;
-            cidx = kidx;
-            cpts = kept;
-        }
+        nc = nk;
+        cidx = kidx;
+        cpts = kept;
     }
     // The rounds, with face room grown and the hull restarted if it runs out
     const int64_t room = ctx->face_room ? ctx->face_room : std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);

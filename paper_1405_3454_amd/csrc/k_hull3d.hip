@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256) void k3_planes(Poly3 *__restrict__ out) {
     if (neg) atomicOr(&out->flip[t >> 6], 1ull << (t & 63));   // inwards: towards the points off it
 }
 
-__global__ __launch_bounds__(1024) void k3_poly(Poly3 *__restrict__ out) {
+__global__ __launch_bounds__(1024) void k3_poly(Poly3 *__restrict__ out, int64_t *__restrict__ star) {
     __shared__ I3 q[S3];
     __shared__ int nf;
     __shared__ unsigned long long keep[TWORDS3];
@@ -444,6 +444,7 @@ __global__ __launch_bounds__(1024) void k3_poly(Poly3 *__restrict__ out) {
         const double rs = nff > 0 ? r * (1.0 - 0x1p-20) - 4.0 : -1.0;
         out->cx = cx; out->cy = cy; out->cz = cz;
         out->r2 = rs > 0 ? rs * rs * (1.0 - 0x1p-20) : -1.0;
+        *star = nff > 0 && rs > 0;
     }
 }
 
@@ -782,8 +783,9 @@ __global__ __launch_bounds__(256) void k3_gather(const float *__restrict__ x, co
 // assignments at 2.3 ms, since they left by a fifth a round; the launches here
 // take 375 us and bring the assignments to 0.66 ms.)
 //
-// The directions from the polyhedron's centre c (on the grid, strictly inside:
-// its ball is wider than the rounding) are cut into the cells of a cube map,
+// The directions from the polyhedron's centre c (on the grid, strictly inside
+// where its ball is wider than the rounding; other sets, flat ones among them,
+// go to the rounds directly) are cut into the cells of a cube map,
 // G x G per face; each face's map goes on STAR_PAD cells past the face, so
 // that every cell's neighbours lie in its own map.  A cell's far point is the
 // farthest from c of the candidates in it.  In the map's coordinates straight
@@ -819,8 +821,6 @@ __device__ __forceinline__ int star_cell(const float *d, int a, int g) {
     return ((2 * a + (d[a] < 0)) * gd + j) * gd + i;
 }
 
-__device__ __forceinline__ bool star_on(const Poly3 *P) { return P->nf > 0 && P->r2 > 0; }
-
 // The candidates with their coordinates, and the cells' farthest keys
 // (distance from c, ~position in the list).
 __global__ __launch_bounds__(256) void k3_star_far(const float *__restrict__ x, const float *__restrict__ y,
@@ -828,13 +828,11 @@ __global__ __launch_bounds__(256) void k3_star_far(const float *__restrict__ x, 
                                                    int64_t n, const Poly3 *__restrict__ P, int g,
                                                    unsigned long long *__restrict__ cells,
                                                    float4 *__restrict__ pts) {
-    const bool on = star_on(P);
     const float cx = (float)rint(P->cx), cy = (float)rint(P->cy), cz = (float)rint(P->cz);
     for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += int64_t(gridDim.x) * blockDim.x) {
         const uint32_t i = idx[t];
         const float4 p = make_float4(x[i], y[i], z[i], __uint_as_float(i));
         pts[t] = p;
-        if (!on) continue;
         const float d[3] = {p.x * GRIDF - cx, p.y * GRIDF - cy, p.z * GRIDF - cz};
         const float r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
         const unsigned long long k = ((unsigned long long)__float_as_uint(r2) << 32) | (uint32_t)~(uint32_t)t;
@@ -867,7 +865,6 @@ __global__ __launch_bounds__(256) void k3_star_keep(const float4 *__restrict__ p
                                                     unsigned long long *__restrict__ count) {
     __shared__ int bcnt;
     __shared__ int64_t bbase;
-    const bool on = star_on(P);
     const int gd = g + 2 * STAR_PAD, lane = lane_id();
     const double cx = rint(P->cx), cy = rint(P->cy), cz = rint(P->cz);
     const int64_t nt = int64_t(gridDim.x) * 256;
@@ -877,7 +874,7 @@ __global__ __launch_bounds__(256) void k3_star_keep(const float4 *__restrict__ p
         bool keep = has;
         float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
         if (has) p = pts[t];
-        if (has && on) {
+        if (has) {
             const float df[3] = {p.x * GRIDF - (float)cx, p.y * GRIDF - (float)cy, p.z * GRIDF - (float)cz};
             const float ax = fabsf(df[0]), ay = fabsf(df[1]), az = fabsf(df[2]);
             const int a = ax >= ay && ax >= az ? 0 : ay >= az ? 1 : 2;
