@@ -338,7 +338,7 @@ int oracle_compute(const float *x, const float *y, int64_t n,
  * ---------------------------------------------------------------------- */
 
 /* 32 x 32 occupancy histogram of a point set, the network's input.
- * Sample: every stride-th point, stride = ceil(n / 16384), starting at 0.
+ * Sample: every point, or 256 runs of 64 of a larger set (oracle_hist_index).
  * Grid coordinates kx = x * 2^24 (integers on the input grid).  The bins
  * span a square window around the sample's bounding box, so the set keeps its
  * aspect ratio: with box widths wx = max kx - min kx + 1, wy likewise, and

@@ -79,12 +79,13 @@ __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float((uint32
 
 // ---------------------------------------------------------------------------
 // 32 x 32 occupancy histogram of each set (one block per set).  Sample: every
-// stride-th point of the set, stride = ceil(n / 16384).  Bins cover a square
-// window of side w = max(width, height) of the sample's bounding box (grid
-// units), centred on the box, so that the set's aspect ratio and the angles
-// of its features are kept: origin (x0 - (w - wx) / 2, y0 - (w - wy) / 2),
-// bin = (k - origin) * 32 / w in integer arithmetic; value = count * 1024 / ns
-// (binary64 product and quotient, then float, then bf16).
+// point of a set of up to 16384, else 256 runs of 64 consecutive points spread
+// evenly over the set.  Bins cover a square window of side w = max(width,
+// height) of the sample's bounding box (grid units), centred on the box, so
+// that the set's aspect ratio and the angles of its features are kept: origin
+// (x0 - (w - wx) / 2, y0 - (w - wy) / 2), bin = (k - origin) * 32 / w in
+// integer arithmetic; value = count * 1024 / ns (binary64 product and
+// quotient, then float, then bf16).
 constexpr int HIST_THREADS = 1024;
 constexpr int HPER = HSAMPLE / HIST_THREADS;    // samples per thread, held in registers
 static_assert(HSAMPLE % HIST_THREADS == 0, "the samples split evenly over the threads");
