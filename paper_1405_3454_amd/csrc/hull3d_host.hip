@@ -119,6 +119,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
     // Step 4.  Many candidates: those inside tetrahedra of far points go first
     const uint32_t *cidx = sv;               // the candidates' indices
     const float4 *cpts = nullptr;            // and coordinates, where they are at hand
+    const uint32_t *first = sv;              // the start simplex's first corner
     if (star && nc >= STAR_MIN) {
         // in the workspace, whose chain lists and candidate lists (16 bytes a
         // point twice, 4, and 8 for the cells) are idle until the final sort
@@ -138,6 +139,7 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         nc = nk;
         cidx = kidx;
         cpts = kept;
+        first = poly->pts;                   // slot 0
     }
     // The rounds, with face room grown and the hull restarted if it runs out
     const int64_t room = ctx->face_room ? ctx->face_room : std::min<int64_t>(8 * nc + 1024, int64_t(1) << 24);
@@ -178,8 +180,8 @@ extern "C" int hull3_compute(hull_ctx *ctx, const float *x, const float *y, cons
         LAUNCH(K_MISC, k3_ctl_init<<<1, 64, 0, st>>>(C, (int)fcap));
         const unsigned gs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ctx->cus * 4, (nc + 255) / 256));
         for (int phase = 1; phase <= 3; phase++)
-            LAUNCH(K_MISC, k3_seed<<<gs, 256, 0, st>>>(x, y, z, sv, cidx, nc, phase, C));
-        LAUNCH(K_MISC, k3_start<<<1, 64, 0, st>>>(x, y, z, sv, nc, C, faces, planes, far));
+            LAUNCH(K_MISC, k3_seed<<<gs, 256, 0, st>>>(x, y, z, first, cidx, nc, phase, C));
+        LAUNCH(K_MISC, k3_start<<<1, 64, 0, st>>>(x, y, z, first, nc, C, faces, planes, far));
         Hull3Ctl hc;
         HIPCHECK(hipMemcpyAsync(&hc, C, sizeof(hc), hipMemcpyDeviceToHost, st));
         HIPCHECK(hipStreamSynchronize(st));
