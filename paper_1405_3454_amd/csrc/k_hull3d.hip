@@ -618,10 +618,11 @@ struct Hull3Ctl {
 
 // An earlier launch ran out of face room (nfaces is then past fcap, and faces
 // below it may be unmade) or found the mesh open: the rounds that the host has
-// launched in the meantime leave everything as it is.
-__device__ __forceinline__ bool mesh_over(const Hull3Ctl *C) {
-    return __builtin_amdgcn_readfirstlane(C->overflow) != 0;
-}
+// launched in the meantime leave everything as it is: their lists count as
+// empty (a count read together with the flag, since a solid's 300 launches are
+// bound by latency: returns ahead of the other loads took 0.5 to 1 % more).
+__device__ __forceinline__ bool mesh_over(const Hull3Ctl *C) { return C->overflow != 0; }
+__device__ __forceinline__ int mesh_count(const Hull3Ctl *C, int count) { return mesh_over(C) ? 0 : count; }
 
 __device__ __forceinline__ double pdx(const float *v, uint32_t i) { return (double)truncf(v[i] * GRIDF); }
 
@@ -968,11 +969,10 @@ __global__ __launch_bounds__(256) void k3_assign(const float4 *__restrict__ cin,
                                                  const Plane3 *__restrict__ planes, const int2 *__restrict__ repl,
                                                  unsigned long long *__restrict__ far, int round) {
     __shared__ int bcnt, bbase;
-    if (mesh_over(C)) return;
-    const int64_t nc = C->nlist[round & 1];
-    const bool first = round == 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) C->npair = 0;      // for k3_pick
     const int nfaces = C->nfaces;
+    const int64_t nc = mesh_count(C, C->nlist[round & 1]);
+    const bool first = round == 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !mesh_over(C)) C->npair = 0;      // for k3_pick
     const int lane = lane_id();
     constexpr int STEP = 256 * AS_ITEMS;
     if (threadIdx.x == 0) bcnt = 0;
@@ -1108,12 +1108,11 @@ constexpr int INS_PASSES = 4;       // claim-and-insert passes per assignment
 // Round start: the proposals.  Clears far[] for the next assignment.
 __global__ __launch_bounds__(256) void k3_pick(Hull3Ctl *__restrict__ C, unsigned long long *__restrict__ far,
                                                Pair3 *__restrict__ pairs, int round) {
-    if (mesh_over(C)) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int F = mesh_count(C, C->nfaces);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !mesh_over(C)) {
         C->inserted = 0;
         C->nlist[round & 1] = 0;      // read by this round's assignment, filled by the next one's
     }
-    const int F = C->nfaces;
     const int64_t Fw = (F + WAVE - 1) / WAVE * WAVE;
     for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < Fw; t += int64_t(gridDim.x) * blockDim.x) {
         const unsigned long long k = t < F ? far[t] : 0ull;
@@ -1157,9 +1156,8 @@ __global__ __launch_bounds__(64) void k3_visible(const float *__restrict__ x, co
     __shared__ int vl[PV_CAP];
     __shared__ int hl[PV_CAP];
     __shared__ int tmp[WAVE];
-    if (mesh_over(C)) return;
     const int lane = threadIdx.x;
-    const int np = min(C->npair, PAIR_CAP);
+    const int np = mesh_count(C, min(C->npair, PAIR_CAP));
     for (int p = blockIdx.x; p < np; p += gridDim.x) {
         const Pair3 P = pairs[p];
         if (!faces[P.f].alive) {
@@ -1235,9 +1233,8 @@ __global__ __launch_bounds__(64) void k3_apply(const float *__restrict__ x, cons
                                                const unsigned long long *__restrict__ claim_out, int stamp) {
     __shared__ int ha[PV_CAP], hb[PV_CAP], ho[PV_CAP];
     __shared__ int base;
-    if (mesh_over(C)) return;
     const int lane = threadIdx.x;
-    const int np = min(C->npair, PAIR_CAP);
+    const int np = mesh_count(C, min(C->npair, PAIR_CAP));
     const int fcap = C->fcap;
     for (int p = blockIdx.x; p < np; p += gridDim.x) {
         const int2 cnt = pn[p];
