@@ -6,11 +6,11 @@
 // several, 2 to 12 us each) and the latency of each kernel's few loads, not
 // bandwidth, so the steps of the general path run here one after another on
 // one CU with a barrier between them: 1000 points 97 -> 20 us, 64 sets of 500
-// to 8000 points 232 -> 55 us.  What is left is the latency of each step's
+// to 8000 points 232 -> 52 us.  What is left is the latency of each step's
 // chain of LDS reads, and instructions fetched for the first time: code that
-// runs once is kept in loops rather than unrolled.  The results, and the candidate counts
-// of every stage, are the general path's: the same predicates on the same
-// slots, edges and farthest keys.
+// runs once is kept in loops rather than unrolled.  The results, and the
+// candidate counts of every stage, are the general path's: the same predicates
+// on the same slots, edges and farthest keys.
 //
 // A set has at most SM_CAP survivors here, and so candidates, which fit the
 // block's LDS; in batches that may hold larger sets, those with more survivors
